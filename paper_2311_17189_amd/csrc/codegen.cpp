@@ -29,6 +29,12 @@ namespace {
 // every fused multiply-add written out, so they do not change.
 const char *const kReverseContract = "#pragma clang fp contract(fast)\n";
 
+// First statement of every function that reaches the workspace: the lane's
+// byte offset through an empty asm in the accesses' own basic block, where the
+// compiler sees its zero extension and takes it as the 32-bit offset of a
+// scalar base (else each load adds a 64-bit vector address).
+const char *const kOffsetHere = "  AMI_OPAQUE(off);\n";
+
 std::string num(double v) {
     char b[40];
     std::snprintf(b, sizeof(b), "%.17g", v);
@@ -604,6 +610,7 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
     if (kernels & 16) {
         o << "__device__ __forceinline__ void group_sums_store(const double (&F)[L], double *ws, int64_t ld, "
              "uint32_t off) {\n";
+        o << kOffsetHere;
         group_sums_body("ami::ws_store(ws, ld, ", ", off, ft)", true);
         o << "}\n";
     }
@@ -659,6 +666,7 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
     if (kernels & 512) {
         o << "__device__ __forceinline__ void group_sums_c_store(const double (&Fr)[L], const double (&Fi)[L], "
              "double *ws, int64_t ld, uint32_t off) {\n";
+        o << kOffsetHere;
         group_sums_c_body(true);
         o << "}\n";
     }
@@ -807,6 +815,7 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
     if (kernels & 32) {
         o << "__device__ __forceinline__ void group_accumulate(const double (&xr)[D], const double (&xi)[D], "
              "const double *ws, int64_t ld, uint32_t off, double &acc_re, double &acc_im) {\n";
+        o << kOffsetHere;
         // sum_g FT_g R_g nested over the reciprocals (factor k < D: z_k; factor
         // D + g: the stored FT_g, read where the nesting first needs it)
         std::vector<HornerTerm> ts;
@@ -852,6 +861,7 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
     if (kernels & 1024) {
         o << "__device__ __forceinline__ void group_accumulate_c(const double (&xr)[D], const double (&xi)[D], "
              "const double *ws, int64_t ld, uint32_t off, double &acc_re, double &acc_im) {\n";
+        o << kOffsetHere;
         std::vector<HornerTerm> ts;
         for (int g = 0; g < G; ++g) {
             HornerTerm h{1.0, {}};
@@ -909,6 +919,7 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
           << NXA << "], const double (&wi)[" << NXA << "], double cr, double ci, double *ws, int64_t ld, uint32_t off, "
              "double &acc_re, double &acc_im, double (&gE)[NE], double (&gwr)["
           << NXA << "], double (&gwi)[" << NXA << "]) {\n";
+        o << kOffsetHere;
         const bool own = kAdjChunkOwnDens;
         if (!own)
             o << "  double xr[D], xi[D];\n  { double dr[D], di[D];\n    den_args(E, wr, wi, dr, di);\n"
@@ -1048,6 +1059,7 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
         o << "__device__ __forceinline__ void leaf_pass(const double (&E)[NE], double beta, double e_reg, const double "
              "*ws, int64_t ld, uint32_t off, double (&gE)[NE], double &gbeta) {\n";
         o << kReverseContract;
+        o << kOffsetHere;
         o << "  (void)e_reg;\n";
         // with Taylor-coefficient leaves DV holds dT/dx and DB dT/dbeta
         for (int l = 0; l < L; ++l)
@@ -1141,6 +1153,7 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
           << NXA << "], const double (&wi)[" << NXA << "], double cr, double ci, double *ws, int64_t ld, uint32_t off, "
              "double &acc_re, double &acc_im, double (&gEr)[NE], double (&gEi)[NE], double (&gwr)["
           << NXA << "], double (&gwi)[" << NXA << "]) {\n";
+        o << kOffsetHere;
         for (int g0 = 0; g0 < G; g0 += kAdjChunkGroups) {
             const int g1 = std::min(G, g0 + kAdjChunkGroups);
             std::vector<int> ks;
@@ -1233,6 +1246,7 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
              "double e_reg, const double *ws, int64_t ld, uint32_t off, double (&gEr)[NE], double (&gEi)[NE], "
              "double &gbeta) {\n";
         o << kReverseContract;
+        o << kOffsetHere;
         o << "  (void)e_reg;\n";
         for (int l = 0; l < L; ++l)
             o << "  double Fr" << l << ", Fi" << l << ", FBr" << l << ", FBi" << l << ";\n";

@@ -26,6 +26,15 @@ typedef __hip_internal::int8_t int8_t;
 #define AMI_OPAQUE(x) asm volatile("" : "+v"(x))
 #endif
 
+// The same for a wave-uniform value.
+#ifndef AMI_OPAQUE_S
+#ifdef __HIP_DEVICE_COMPILE__
+#define AMI_OPAQUE_S(x) asm volatile("" : "+s"(x))
+#else
+#define AMI_OPAQUE_S(x)
+#endif
+#endif
+
 // A scheduling fence: the compiler moves no instruction across it.  Generated
 // code puts one between chunks of independent work, so that the loads and
 // values of a later chunk do not stay live through an earlier one.
@@ -413,21 +422,29 @@ __device__ __forceinline__ double wave_sum(double v) {
 
 // Element (column c, sample at byte offset off) of a [column][sample]
 // workspace with leading dimension ld: the column's base is wave-uniform and
-// the offset a 32-bit lane value, which the compiler turns into a load or store
-// with a scalar base and no vector address arithmetic.
+// the offset a 32-bit lane value, in the global address space, so each access
+// is one global_load/store with a scalar base and no vector address arithmetic
+// (a generic pointer made them flat accesses with a 64-bit vector add each, and
+// the LDS counter to wait for).  The leading dimension is taken through an
+// empty asm per access: the bases are then formed where they are used, on the
+// scalar unit, instead of being kept for the whole kernel in spilled SGPRs.
+typedef __attribute__((address_space(1))) char *gchar;
+typedef const __attribute__((address_space(1))) char *cgchar;
+
 __device__ __forceinline__ uint64_t ws_column(const double *ws, int64_t ld, int c) {
-    const uint64_t p = reinterpret_cast<uint64_t>(ws + c * ld);
+    AMI_OPAQUE_S(ld);
+    const uint64_t p = reinterpret_cast<uint64_t>(ws) + 8u * static_cast<uint64_t>(c) * static_cast<uint64_t>(ld);
     const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(p));
     const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(p >> 32));
     return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
 __device__ __forceinline__ double ws_load(const double *ws, int64_t ld, int c, uint32_t off) {
-    return *reinterpret_cast<const double *>(ws_column(ws, ld, c) + off);
+    return *(const __attribute__((address_space(1))) double *)((cgchar)ws_column(ws, ld, c) + off);
 }
 
 __device__ __forceinline__ void ws_store(double *ws, int64_t ld, int c, uint32_t off, double v) {
-    *reinterpret_cast<double *>(ws_column(ws, ld, c) + off) = v;
+    *(__attribute__((address_space(1))) double *)((gchar)ws_column(ws, ld, c) + off) = v;
 }
 
 // gfx950 lane exchanges of a double, as two 32-bit halves: swap32 exchanges
