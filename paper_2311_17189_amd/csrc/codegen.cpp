@@ -354,6 +354,8 @@ constexpr bool kAdjChunkOwnDens = true;
 // between scheduling fences.
 constexpr int kAdjLeafPartTerms = 32;
 constexpr int kAdjLeafFenceParts = 1;
+// Terms per nested part of a group in the block adjoint's leaf sweep.
+constexpr int kBlockPartTerms = 32;
 
 }  // namespace
 
@@ -427,6 +429,170 @@ int jit_nested_override() {
     if (!e) return -1;
     const int v = std::atoi(e);
     return v >= 0 && v <= 64 ? v : 0;
+}
+
+namespace {
+// ---- block adjoint: a block's waves split the work of 64 samples -----------
+//
+// The split of a solution over the waves of a block: wave w takes the groups
+// [first[w], first[w + 1]) (consecutive in canonical order, so that a wave's
+// groups share denominators), balanced by the operations of their nested sums,
+// their reverse sweep and their products.
+struct BlockPlan {
+    int waves = 0;                        // 0: no split worth having
+    std::vector<int> first;
+    int max_groups = 0;
+    double imbalance = 1.0;               // largest wave's cost over the mean
+    // reduction of the leaf cotangents over the waves, in rounds: round r holds
+    // the leaves [round[r], round[r + 1]); slot[l][w] is wave w's column of leaf l
+    // in its round (-1: the wave does not read the leaf)
+    std::vector<int> round;
+    std::vector<std::vector<int>> slot;
+    // LDS columns (64 doubles each): energies, a row's sums, slopes (-1: formed
+    // again where they are needed), then a region that holds leaves and group
+    // sums (-1: in the wave's registers), then the reductions
+    int c_e = 0, c_acc = 0, c_slope = -1, c_union = 0, c_leaf = 0, c_group = -1, columns = 0;
+};
+
+// Columns of LDS of one of two blocks on a CU, and of a block alone (160 KB
+// less a margin).
+constexpr int kBlockHalfColumns = 158;
+constexpr int kBlockMaxColumns = 316;
+// Groups whose sums and cotangents a wave holds in registers at most.
+constexpr int kBlockRegisterGroups = 12;
+
+BlockPlan block_plan(const AmiTerms *t, bool hub, bool cplx, int waves) {
+    const Tables &tb = t->tab;
+    const int G = tb.G, L = tb.L, ni = t->n_int, ne = t->n_eps, nx = t->n_ext;
+    const int cw = cplx ? 2 : 1;          // columns of a value
+    BlockPlan p;
+    if (waves < 2 || G < waves) return p;
+    std::vector<double> cost(static_cast<size_t>(G));
+    double total = 0.0;
+    for (int g = 0; g < G; ++g) {
+        std::vector<HornerTerm> ts;
+        for (int ti = tb.group_start[g]; ti < tb.group_start[g + 1]; ++ti) {
+            HornerTerm h{tb.term_sign[ti], {}};
+            for (int j = 0; j < ni; ++j) h.leaves.push_back(tb.term_leaf[static_cast<size_t>(ti) * ni + j]);
+            ts.push_back(std::move(h));
+        }
+        std::vector<HNode> nodes;
+        horner_build(std::move(ts), nodes);
+        const int dens = tb.group_den_start[g + 1] - tb.group_den_start[g];
+        cost[g] = 3.6 * (cplx ? 3.5 : 1.0) * static_cast<double>(nodes.size()) + 3.0 * dens + 8.0;
+        total += cost[g];
+    }
+    // the smallest bound under which consecutive ranges fit `waves` waves
+    auto ranges = [&](double bound, std::vector<int> &first) {
+        first.assign(1, 0);
+        double c = 0.0;
+        for (int g = 0; g < G; ++g) {
+            const int left_waves = waves - static_cast<int>(first.size());
+            if (g > first.back() && (c + cost[g] > bound || G - g <= left_waves)) {
+                if (left_waves == 0) return false;
+                first.push_back(g);
+                c = 0.0;
+            }
+            c += cost[g];
+        }
+        while (static_cast<int>(first.size()) < waves) first.push_back(G);
+        first.push_back(G);
+        return c <= bound;
+    };
+    double lo = total / waves, hi = total;
+    std::vector<int> first;
+    for (int it = 0; it < 40; ++it) {
+        const double mid = 0.5 * (lo + hi);
+        if (ranges(mid, first)) hi = mid;
+        else lo = mid;
+    }
+    if (!ranges(hi, p.first)) return p;
+    double most = 0.0;
+    for (int w = 0; w < waves; ++w) {
+        double c = 0.0;
+        for (int g = p.first[w]; g < p.first[w + 1]; ++g) c += cost[g];
+        most = std::max(most, c);
+        p.max_groups = std::max(p.max_groups, p.first[w + 1] - p.first[w]);
+    }
+    p.imbalance = most * waves / total;
+    // Two blocks per CU hide each other's barriers and start, so four waves in
+    // half the LDS where the solution fits there, else eight in all of it.
+    // Columns that are optional, in the order of what they save: the group sums
+    // (a wave with many groups spills without them), the slopes.
+    const int limit = waves <= 4 ? kBlockHalfColumns : kBlockMaxColumns;
+    bool fits = false;
+    for (int option = 3; option >= 0 && !fits; --option) {
+        const bool group = option & 2, slope = option & 1;
+        if (!group && p.max_groups > kBlockRegisterGroups) continue;
+        p.c_e = 0;
+        p.c_acc = cw * ne;
+        p.c_slope = slope ? p.c_acc + (2 + 2 * nx) * waves : -1;
+        p.c_union = p.c_acc + (2 + 2 * nx) * waves + (slope ? cw * L : 0);
+        p.c_leaf = p.c_union;
+        p.c_group = group ? p.c_leaf + cw * L : -1;
+        p.columns = p.c_leaf + cw * L + (group ? cw * G : 0);
+        // the reduction of the energies' cotangents and what follows it; the
+        // staged gradient rows at the start
+        p.columns = std::max(p.columns, p.c_union + (cw * ne + 1) * waves + 2 * ne + 2 * waves);
+        p.columns = std::max(p.columns, hub ? 2 * ni + 1 : cw * ne + 1);
+        fits = p.columns <= limit;
+    }
+    if (!fits) return p;
+    // rounds of the leaf reduction within the columns there are
+    std::vector<std::vector<char>> reads(static_cast<size_t>(L), std::vector<char>(static_cast<size_t>(waves), 0));
+    for (int w = 0; w < waves; ++w)
+        for (int g = p.first[w]; g < p.first[w + 1]; ++g)
+            for (int ti = tb.group_start[g]; ti < tb.group_start[g + 1]; ++ti)
+                for (int j = 0; j < ni; ++j) reads[tb.term_leaf[static_cast<size_t>(ti) * ni + j]][w] = 1;
+    {
+        p.round.assign(1, 0);
+        p.slot.assign(static_cast<size_t>(L), std::vector<int>(static_cast<size_t>(waves), -1));
+        int used = 0, top = 0;
+        for (int l = 0; l < L; ++l) {
+            int n = 0;
+            for (int w = 0; w < waves; ++w) n += reads[l][w] ? cw : 0;
+            if (used > 0 && p.c_union + used + n > limit) {
+                p.round.push_back(l);
+                used = 0;
+            }
+            for (int w = 0; w < waves; ++w)
+                if (reads[l][w]) {
+                    p.slot[l][w] = used;
+                    used += cw;
+                }
+            top = std::max(top, used);
+        }
+        p.round.push_back(L);
+        p.columns = std::max(p.columns, p.c_union + top);
+    }
+    if (p.columns > limit) return p;
+    p.waves = waves;
+    return p;
+}
+
+}  // namespace
+
+// Waves per block of the block adjoint (AMIGPU_JIT_BLOCK_WAVES overrides): as
+// few as leave each wave a part that fits its registers, since every wave more
+// is another partner at each barrier.  Two up to 200 terms (136 terms, 2 10^5
+// samples: 41.6 us a step, four waves 50.4; 264 terms at four rows and 5 10^4
+// samples: 38.0 and 35.8), else four (560 terms 78.7, 76.9 and with eight 119;
+// 2804 terms 233, 190 and 233), and eight, alone on its CU, where the columns of
+// four do not fit half its LDS.
+int jit_block_waves(const AmiTerms *t, bool hub, bool cplx) {
+    for (int o : t->tab.leaf_order)
+        if (o > 0) return 0;              // Taylor-coefficient leaves: the passes over a workspace
+    if (t->tab.T > kJitTwoPassMaxTerms) return 0;
+    if (const char *e = std::getenv("AMIGPU_JIT_BLOCK_WAVES")) {
+        const int v = std::atoi(e);
+        return v == 2 || v == 4 || v == 8 ? block_plan(t, hub, cplx, v).waves : 0;
+    }
+    for (int w : {2, 4, 8}) {
+        if (w == 2 && t->tab.T > 200) continue;
+        const BlockPlan p = block_plan(t, hub, cplx, w);
+        if (p.waves > 0 && p.imbalance <= 1.6) return w;
+    }
+    return 0;
 }
 
 namespace {
@@ -1133,6 +1299,234 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
         o << "}\n";
     }
 
+    if (kernels & 8192) {
+        // The block adjoint's per-wave functions (wave WV of a block of NW
+        // waves that share 64 samples; LDS columns are passed as the address
+        // of the lane's element in the first column of a region, column c of
+        // it at [64 c]).
+        const BlockPlan bp = block_plan(t, hub, false, jit_block_waves(t, hub, false));
+        const int W = bp.waves;
+        o << "constexpr int NW = " << W << ", GW = " << bp.max_groups << ", kRounds = " << bp.round.size() - 1
+          << ", kBlockCols = " << bp.columns << ";\n";
+        o << "constexpr int kBE = " << bp.c_e << ", kBS = " << bp.c_slope << ", kBU = " << bp.c_union << ", kBF = "
+          << bp.c_leaf << ", kBT = " << bp.c_group << ", kBA = " << bp.c_acc << ";\n";
+        const bool group_cols = bp.c_group >= 0, slope_cols = bp.c_slope >= 0;
+        // group g's sum (before the leaf sweep) or cotangent (in it) of wave w
+        auto gsum = [&](int w, int g, const char *reg) {
+            return group_cols ? "sT[" + std::to_string(64 * g) + "]" : idx(reg, g - bp.first[w]);
+        };
+        auto wave_fn = [&](const std::string &name, const std::string &args, bool reverse, const auto &body) {
+            o << "template <int WV" << (name == "blk_freq" ? ", bool ONE" : "") << "> __device__ __forceinline__ void " << name << "(" << args << ") {\n";
+            if (reverse) o << kReverseContract;
+            for (int w = 0; w < W; ++w) {
+                o << "  if constexpr (WV == " << w << ") {\n";
+                body(w);
+                o << "  }\n";
+            }
+            o << "}\n";
+        };
+        // the leaves that terms [t0, t1) read, as "const double f<l>" from the
+        // columns of a pointer taken through an empty asm (so that the compiler
+        // loads them again here instead of holding every leaf)
+        auto load_leaves = [&](int t0, int t1) {
+            std::vector<int> used;
+            for (int ti = t0; ti < t1; ++ti)
+                for (int j = 0; j < ni; ++j) used.push_back(tb.term_leaf[static_cast<size_t>(ti) * ni + j]);
+            std::sort(used.begin(), used.end());
+            used.erase(std::unique(used.begin(), used.end()), used.end());
+            o << "    ami::clds p = sF; AMI_OPAQUE(p);\n   ";
+            for (int l : used) o << " const double f" << l << " = p[" << 64 * l << "];";
+            o << "\n";
+        };
+        o << "__device__ __forceinline__ void blk_rho(double dr, double di, double &xr, double &xi) {\n"
+             "  const double inv = ami::rcp_nr(fma(dr, dr, di * di));\n  xr = dr * inv;\n  xi = -di * inv;\n}\n";
+        auto fname = [](int l) { return "f" + std::to_string(l); };
+        auto terms_of = [&](int t0, int t1) {
+            std::vector<HornerTerm> ts;
+            for (int ti = t0; ti < t1; ++ti) {
+                HornerTerm h{tb.term_sign[ti], {}};
+                for (int j = 0; j < ni; ++j) h.leaves.push_back(tb.term_leaf[static_cast<size_t>(ti) * ni + j]);
+                ts.push_back(std::move(h));
+            }
+            return ts;
+        };
+        // group sums of the wave's groups
+        wave_fn("blk_sums", "ami::clds sF, ami::lds sT, double (&ft)[GW]", false, [&](int w) {
+            o << "    (void)sT; (void)ft;\n";
+            for (int g = bp.first[w]; g < bp.first[w + 1]; ++g) {
+                if (g > bp.first[w]) o << "  AMI_SCHED_FENCE();\n";
+                o << "  {\n";
+                load_leaves(tb.group_start[g], tb.group_start[g + 1]);
+                std::vector<HNode> nodes;
+                const HRef v = horner_build(terms_of(tb.group_start[g], tb.group_start[g + 1]), nodes);
+                horner_emit(nodes, fname, o);
+                o << "    " << gsum(w, g, "ft") << " = " << href_expr(v, fname) << "; }\n";
+            }
+        });
+        // one frequency row of the wave's groups: the reciprocals of their
+        // denominators, R_g, the value's part sum FT_g R_g, FTB_g +=
+        // Re(conj(c) R_g), and per denominator -conj(c) rho_k sum FT_g R_g,
+        // scattered to the energies and frequencies
+        // ONE: the only row, whose FTB_g takes FT_g's column at once
+        wave_fn("blk_freq",
+                "ami::clds sE, const double (&wr)[" + NXA + "], const double (&wi)[" + NXA +
+                    "], ami::lds sT, const double (&ft)[GW], double cr, double ci, double (&ftb)[GW], double &acc_re, "
+                    "double &acc_im, double (&gE)[NE], double (&gwr)[" + NXA + "], double (&gwi)[" + NXA + "]",
+                true, [&](int w) {
+            std::vector<int> ks;
+            for (int g = bp.first[w]; g < bp.first[w + 1]; ++g)
+                for (int j = gbegin(g); j < gend(g); ++j) ks.push_back(tb.group_den_list[j]);
+            std::sort(ks.begin(), ks.end());
+            ks.erase(std::unique(ks.begin(), ks.end()), ks.end());
+            // the columns through an empty asm: the sums are read here, not
+            // held in registers since they were written
+            o << "    AMI_OPAQUE(sT); (void)ft; (void)ftb;\n    double E[NE];\n#pragma unroll\n    for (int i = 0; i < NE; ++i) E[i] = sE[64 * i];\n";
+            for (int k : ks) {
+                Lin re, im;
+                for (int i = 0; i < ne; ++i) re.add(tb.den_coef[static_cast<size_t>(k) * nc + i], idx("E", i));
+                for (int x = 0; x < nx; ++x) {
+                    const double a = tb.den_coef[static_cast<size_t>(k) * nc + ne + x];
+                    re.add(a, idx("wr", x));
+                    im.add(a, idx("wi", x));
+                }
+                o << "    double xr" << k << ", xi" << k << ", Ur" << k << " = 0.0, Ui" << k << " = 0.0;\n    blk_rho("
+                  << re.str() << ", " << im.str() << ", xr" << k << ", xi" << k << ");\n";
+            }
+            for (int g = bp.first[w]; g < bp.first[w + 1]; ++g) {
+                const std::string j0 = std::to_string(g - bp.first[w]);
+                o << "    { double rr = 1.0, ri = 0.0, nr = 0.0;\n";
+                for (int j = gbegin(g); j < gend(g); ++j) {
+                    const std::string k = std::to_string(tb.group_den_list[j]);
+                    if (j == gbegin(g)) o << "      rr = xr" << k << "; ri = xi" << k << ";\n";
+                    else
+                        o << "      nr = fma(rr, xr" << k << ", -ri * xi" << k << "); ri = fma(rr, xi" << k << ", ri * xr"
+                          << k << "); rr = nr;\n";
+                }
+                o << "      (void)nr;\n      const double t = " << gsum(w, g, "ft")
+                  << ", qr = t * rr, qi = t * ri, tb = fma(cr, rr, ci * ri);\n";
+                if (group_cols) o << "      if constexpr (ONE) sT[" << 64 * g << "] = tb;\n      else ";
+                o << "ftb[" << j0 << "] += tb;\n      acc_re += qr; acc_im += qi;\n";
+                for (int j = gbegin(g); j < gend(g); ++j) {
+                    const std::string k = std::to_string(tb.group_den_list[j]);
+                    o << "      Ur" << k << " += qr; Ui" << k << " += qi;\n";
+                }
+                o << "    }\n";
+            }
+            for (int k : ks) {
+                const std::string K = std::to_string(k);
+                o << "    { const double vr = -fma(Ur" << K << ", cr, Ui" << K << " * ci), vi = -fma(Ui" << K << ", cr, -Ur"
+                  << K << " * ci);\n      const double dR = fma(vr, xr" << K << ", -vi * xi" << K << "), dI = fma(vr, xi"
+                  << K << ", vi * xr" << K << ");\n      (void)dI;\n";
+                for (int i = 0; i < ne; ++i) {
+                    const double c = tb.den_coef[static_cast<size_t>(k) * nc + i];
+                    if (c == 1.0) o << "      gE[" << i << "] += dR;\n";
+                    else if (c == -1.0) o << "      gE[" << i << "] -= dR;\n";
+                    else if (c != 0.0) o << "      gE[" << i << "] = fma(" << num(c) << ", dR, gE[" << i << "]);\n";
+                }
+                for (int x = 0; x < nx; ++x) {
+                    const double a = tb.den_coef[static_cast<size_t>(k) * nc + ne + x];
+                    if (a == 0.0) continue;
+                    o << "      gwr[" << x << "] = fma(" << num(a) << ", dR, gwr[" << x << "]);\n";
+                    o << "      gwi[" << x << "] = fma(" << num(a) << ", dI, gwi[" << x << "]);\n";
+                }
+                o << "    }\n";
+            }
+        });
+        // leaf cotangents of the wave's groups by the reverse sweep of each
+        // group's nested sum, in parts of at most kBlockPartTerms terms
+        if (group_cols)
+            wave_fn("blk_keep", "ami::lds sT, const double (&ftb)[GW]", false, [&](int w) {
+                for (int g = bp.first[w]; g < bp.first[w + 1]; ++g)
+                    o << "    sT[" << 64 * g << "] = ftb[" << g - bp.first[w] << "];\n";
+            });
+        else
+            wave_fn("blk_keep", "ami::lds, const double (&)[GW]", false, [&](int) {});
+        wave_fn("blk_leaf", "ami::clds sF, ami::clds sT, const double (&ftb)[GW], double (&FB)[L]", true, [&](int w) {
+            o << "    (void)sT; (void)ftb;\n";
+            for (int g = bp.first[w]; g < bp.first[w + 1]; ++g)
+                for (int t0 = tb.group_start[g]; t0 < tb.group_start[g + 1]; t0 += kBlockPartTerms) {
+                    const int t1 = std::min(tb.group_start[g + 1], t0 + kBlockPartTerms);
+                    std::vector<HNode> nodes;
+                    const HRef root = horner_build(terms_of(t0, t1), nodes);
+                    if (g > bp.first[w] || t0 > tb.group_start[g]) o << "  AMI_SCHED_FENCE();\n";
+                    o << "  {\n";
+                    load_leaves(t0, t1);
+                    horner_emit(nodes, fname, o);
+                    const size_t nn = nodes.size();
+                    for (size_t k = 0; k < nn; ++k) o << "    double hb" << k << " = 0.0;\n";
+                    auto pass = [&](const HRef &r, const std::string &c) {
+                        if (r.kind == HRef::NODE) o << "    hb" << r.idx << (r.neg ? " -= " : " += ") << c << ";\n";
+                        else if (r.kind == HRef::LEAF)
+                            o << "    FB[" << r.idx << "]" << (r.neg ? " -= " : " += ") << c << ";\n";
+                    };
+                    pass(root, gsum(w, g, "ftb"));
+                    for (size_t kk = nn; kk-- > 0;) {
+                        const HNode &n = nodes[kk];
+                        const std::string hb = "hb" + std::to_string(kk), fa = fname(n.a),
+                                          fb = "FB[" + std::to_string(n.a) + "]";
+                        if (n.w.kind == HRef::CONST) {
+                            if (n.w.c == 1.0) o << "    " << fb << " += " << hb << ";\n";
+                            else if (n.w.c == -1.0) o << "    " << fb << " -= " << hb << ";\n";
+                            else o << "    " << fb << " = fma(" << num(n.w.c) << ", " << hb << ", " << fb << ");\n";
+                        } else {
+                            o << "    " << fb << " = fma(" << (n.w.neg ? "-" : "") << href_name(n.w, fname) << ", " << hb
+                              << ", " << fb << ");\n";
+                            pass(n.w, fa + " * " + hb);
+                        }
+                        pass(n.u, hb);
+                    }
+                    o << "  }\n";
+                }
+        });
+        // the reduction of the leaf cotangents: round r's leaves of the wave to
+        // their columns; then each leaf's sum over the waves (in their order)
+        // by wave l mod NW: times the leaf's slope, to beta and the energies
+        for (size_t r = 0; r + 1 < bp.round.size(); ++r) {
+            const std::string R = std::to_string(r);
+            wave_fn("blk_put" + R, "const double (&FB)[L], ami::lds sR", false, [&](int w) {
+                for (int l = bp.round[r]; l < bp.round[r + 1]; ++l)
+                    if (bp.slot[l][w] >= 0) o << "    sR[" << 64 * bp.slot[l][w] << "] = FB[" << l << "];\n";
+            });
+            wave_fn("blk_take" + R,
+                    "double beta, double e_reg, ami::clds sE, ami::clds sR, ami::clds sS, double (&gE)[NE], double &gbeta",
+                    true, [&](int w) {
+                o << "    (void)e_reg; (void)sS;\n";
+                for (int l = bp.round[r]; l < bp.round[r + 1]; ++l) {
+                    if (l % W != w) continue;
+                    Lin sum;
+                    for (int v = 0; v < W; ++v)
+                        if (bp.slot[l][v] >= 0) sum.add(1.0, "sR[" + std::to_string(64 * bp.slot[l][v]) + "]");
+                    Lin x;
+                    for (int i = 0; i < ne; ++i)
+                        x.add(tb.leaf_coef[static_cast<size_t>(l) * ne + i], "sE[" + std::to_string(64 * i) + "]");
+                    o << "    { const double x = " << x.str() << (tb.leaf_sigma[l] < 0 ? " + e_reg" : "") << ";\n";
+                    if (slope_cols) {
+                        o << "      const double dv = sS[" << 64 * l << "];\n";
+                    } else {
+                        o << "      double f, dv;\n      ami::leaf_and_slope(" << (tb.leaf_sigma[l] < 0 ? "true" : "false")
+                          << ", beta * x, f, dv);\n";
+                    }
+                    o << "      const double fb = " << sum.str()
+                      << " * dv, v = fb * beta;\n      gbeta = fma(fb, x, gbeta);\n";
+                    for (int i = 0; i < ne; ++i) {
+                        const double c = tb.leaf_coef[static_cast<size_t>(l) * ne + i];
+                        if (c == 1.0) o << "      gE[" << i << "] += v;\n";
+                        else if (c == -1.0) o << "      gE[" << i << "] -= v;\n";
+                        else if (c != 0.0) o << "      gE[" << i << "] = fma(" << num(c) << ", v, gE[" << i << "]);\n";
+                    }
+                    o << "    }\n";
+                }
+            });
+        }
+        // the rounds, each between two barriers that every wave passes
+        o << "template <int WV> __device__ __forceinline__ void blk_rounds(const double (&FB)[L], double beta, double "
+             "e_reg, ami::clds sE, ami::lds sR, ami::clds sS, double (&gE)[NE], double &gbeta) {\n";
+        for (size_t r = 0; r + 1 < bp.round.size(); ++r)
+            o << "  __syncthreads();\n  blk_put" << r << "<WV>(FB, sR);\n  __syncthreads();\n  blk_take" << r
+              << "<WV>(beta, e_reg, sE, sR, sS, gE, gbeta);\n";
+        o << "}\n";
+    }
+
     // The adjoint at complex energies in passes (after the complex two-pass
     // forward's first pass stored FT_g and E_j, both complex, in the
     // workspace: columns [0, G) Re FT, [G, 2G) Im FT, [2G, 2G + NE) Re E,
@@ -1601,7 +1995,7 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
 
     // the leaves' and lines' scatters: every adjoint kernel (one pass, or the
     // leaf pass of large solutions)
-    if (adj_fns || (kernels & 128)) {
+    if (adj_fns || (kernels & (128 | 8192))) {
     auto scatter = [&](std::ostream &os, double c, const std::string &dst, const std::string &v) {
         if (c == 0.0) return;
         if (c == 1.0) os << "  " << dst << " += " << v << ";\n";

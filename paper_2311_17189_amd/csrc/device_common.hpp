@@ -49,6 +49,11 @@ typedef const __attribute__((address_space(4))) uint32_t *cu32;
 typedef const __attribute__((address_space(4))) double *cdbl;
 typedef const __attribute__((address_space(4))) int32_t *ci32;
 
+// LDS columns, by pointers in their own address space (a pointer that went
+// through AMI_OPAQUE stays an LDS pointer).
+typedef __attribute__((address_space(3))) double *lds;
+typedef const __attribute__((address_space(3))) double *clds;
+
 constexpr int kMaxExtDev = 4;
 
 // Packed evaluation tables (built by the host, see construct.cpp):

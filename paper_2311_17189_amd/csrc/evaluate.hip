@@ -331,7 +331,7 @@ bool timer_pair(hipEvent_t &start, hipEvent_t &stop) {
     return true;
 }
 
-enum class Path { TABLES, PACKED, SPECIALIZED, TWO_PASS, ADJ_PASSES };
+enum class Path { TABLES, PACKED, SPECIALIZED, TWO_PASS, ADJ_PASSES, ADJ_BLOCK };
 
 // Workspace of one chunk of the two-pass forward and of the adjoint in passes
 // (group sums, energies and their cotangents): 1 GiB unless
@@ -347,8 +347,10 @@ constexpr int kTwoPassMaxFreqs = 65535;
 // With no_load the specialized kernels must already be loaded on the device
 // (jit_loaded): nothing is compiled, loaded or allocated, and a kernel that
 // the call would use but that is not loaded yet is an error, not a fallback.
-// The adjoint of a large solution in passes (Path::ADJ_PASSES) takes three
-// kernels: jit_fn (sums pass), jit_fn2 (frequency pass), jit_fn3 (leaf pass).
+// The adjoint of a large solution takes the block kernel under AUTO where the
+// solution splits over the waves of a block (Path::ADJ_BLOCK), else three
+// kernels over a workspace (Path::ADJ_PASSES): jit_fn (sums pass), jit_fn2
+// (frequency pass), jit_fn3 (leaf pass).
 AmiStatus choose_path(AmiTerms *t, bool hub, bool adjoint, Path &p, void **jit_fn, std::string &note,
                       void **jit_fn2 = nullptr, int n_f = 1, int variant = -1, bool no_load = false,
                       void **jit_fn3 = nullptr) {
@@ -367,6 +369,16 @@ AmiStatus choose_path(AmiTerms *t, bool hub, bool adjoint, Path &p, void **jit_f
     if (v == AMI_VARIANT_TWO_PASS && !two && !passes)
         return fail(AMI_E_UNSUPPORTED, adjoint ? "the two-pass variant of the adjoint runs in passes only"
                                                : "the two-pass variant takes at most 65535 frequency rows");
+    if (passes && v == AMI_VARIANT_AUTO && jit_block_waves_of(t, hub) > 0) {
+        const AmiStatus st = get(kJitBlockAdjoint, jit_fn);
+        if (st == AMI_OK) {
+            p = Path::ADJ_BLOCK;
+            return AMI_OK;
+        }
+        if (no_load && st != AMI_E_UNSUPPORTED) return st;
+        note = std::string(" (not in a block: ") + amiLastError() + ")";
+        clear_error();
+    }
     if (passes) {
         std::string why;
         AmiStatus st = AMI_OK;
@@ -628,6 +640,21 @@ struct AdjOut {
     double *out_sum = nullptr;   // forward row sums computed on the way (optional)
 };
 
+// Whether the adjoint of n_e samples with ncols columns of per-wave partial sums
+// fits the allocation-free scratch beside one chunk of samples of the passes
+// (in *chunk, if given, the samples of the chunk that is left).
+AmiStatus adjoint_scratch_fits(const AmiTerms *t, bool hub, int64_t n_e, int ncols, int64_t *chunk = nullptr) {
+    const int B = jit_block(t, hub);
+    const int64_t rows = (n_e + B - 1) / B * (B / 64);
+    const int64_t cols = 2 * static_cast<int64_t>(t->tab.G) + 2 * t->n_eps;
+    const int64_t left = static_cast<int64_t>(kScratchBytes / sizeof(double)) - rows * ncols;
+    const int64_t ld = left > 0 ? left / cols / B * B : 0;
+    if (chunk) *chunk = ld;
+    if (ld >= B) return AMI_OK;
+    return fail(AMI_E_ARG, "the partial sums and one chunk of samples do not fit the " + std::to_string(kScratchBytes) +
+                               "-byte scratch of the allocation-free entry point: split the samples");
+}
+
 // The adjoint of a large solution in passes, per chunk of samples: the
 // two-pass forward's sums pass (FT_g and E_j into the workspace), the
 // frequency pass (values, FTB_g and the denominators' energy cotangents into
@@ -653,12 +680,8 @@ AmiStatus launch_adjoint_passes(AmiTerms *t, DeviceTables *dt, bool hub, KArgs &
     int64_t ld = 0;
     double *ws = nullptr;
     if (fixed_ws) {
-        const int64_t left = static_cast<int64_t>(kScratchBytes / sizeof(double)) - static_cast<int64_t>(n_part);
-        ld = left > 0 ? left / cols / B * B : 0;
-        if (ld < B)
-            return fail(AMI_E_ARG, "the partial sums and one chunk of samples do not fit the " +
-                                       std::to_string(kScratchBytes) +
-                                       "-byte scratch of the allocation-free entry point: split the samples");
+        const AmiStatus st = adjoint_scratch_fits(t, hub, a.n_e, ncols + nval, &ld);
+        if (st != AMI_OK) return st;
         ld = std::min<int64_t>(ld, tiles * B);
         ws = fixed_ws;
     } else {
@@ -694,6 +717,37 @@ AmiStatus launch_adjoint_passes(AmiTerms *t, DeviceTables *dt, bool hub, KArgs &
     return e == hipSuccess ? AMI_OK : hip_fail(e, "adjoint reduction launch");
 }
 
+// The adjoint of a large solution in one launch: blocks of 64 samples whose
+// waves split the solution, each block one row of the partial sums.  fixed_ws:
+// the partial sums in the allocation-free scratch, under the size limit of the
+// passes (the entry point's documented one).
+AmiStatus launch_adjoint_block(AmiTerms *t, DeviceTables *dt, bool hub, KArgs &a, const AdjOut &o, void *fn,
+                               hipStream_t stream, double *fixed_ws) {
+    const int64_t rows = (a.n_e + 63) / 64;
+    if (rows > 0x7fffffffLL) return fail(AMI_E_ARG, "n_e too large");
+    const int ncols = kAdjScalars + 2 * a.n_f * t->n_ext;
+    const int nval = o.out_sum ? 2 * a.n_f : 0;
+    double *ws = fixed_ws;
+    if (fixed_ws) {
+        const AmiStatus st = adjoint_scratch_fits(t, hub, a.n_e, ncols + nval);
+        if (st != AMI_OK) return st;
+    } else {
+        const AmiStatus st = workspace(t, dt, stream, static_cast<size_t>(rows) * (ncols + nval) * sizeof(double), &ws);
+        if (st != AMI_OK) return st;
+    }
+    a.gpartial = ws;
+    a.partial = o.out_sum ? ws + static_cast<size_t>(rows) * ncols : nullptr;
+    a.nrows = rows;
+    hipError_t e = launch_jit(fn, rows, 64 * jit_block_waves_of(t, hub), stream, a);
+    if (e == hipSuccess) e = hipGetLastError();
+    g_last_variant = "specialized passes";
+    if (e != hipSuccess) return hip_fail(e, "block adjoint launch");
+    hipLaunchKernelGGL(ami_adj_finalize_kernel, dim3(ncols + nval), dim3(kRedThreads), 0, stream, a.gpartial, rows,
+                       ncols, 1, o.grad_beta, o.grad_mu, o.grad_t, o.grad_freqs, 2 * a.n_f, o.out_sum);
+    e = hipGetLastError();
+    return e == hipSuccess ? AMI_OK : hip_fail(e, "adjoint reduction launch");
+}
+
 // fixed_ws: the partial sums go there (at most kScratchBytes), and nothing is
 // uploaded, compiled, loaded or allocated (the allocation-free entry point);
 // NULL: the handle's per-stream workspace.
@@ -721,6 +775,7 @@ AmiStatus launch_adjoint(AmiTerms *t, bool hub, KArgs &a, const AdjOut &o, hipSt
     if (st != AMI_OK) return st;
     if (path == Path::ADJ_PASSES)
         return launch_adjoint_passes(t, dt, hub, a, o, jit_fn, jit_fn2, jit_fn3, stream, fixed_ws);
+    if (path == Path::ADJ_BLOCK) return launch_adjoint_block(t, dt, hub, a, o, jit_fn, stream, fixed_ws);
     LaunchShape ls;
     if (path == Path::SPECIALIZED) {
         ls.block = jit_block(t, hub);
@@ -1262,6 +1317,7 @@ AmiStatus amiTermsSpecialize(AmiTerms *t, int32_t momentum) {
         if (!jit_prefers_two_pass(t)) kinds.push_back(kJitSumsPass);
         kinds.push_back(kJitAdjFreq);
         kinds.push_back(kJitAdjLeaf);
+        if (jit_block_waves_of(t, hub) > 0) kinds.push_back(kJitBlockAdjoint);
     }
     // the complex-energy kernels AUTO uses: forward in one pass up to 1024
     // terms, in two above; the adjoint in one pass up to 512 terms, in passes

@@ -29,6 +29,13 @@ constexpr int kJitAutoComplexAdjointTerms = 512;
 // passes (the two-pass form, no Taylor-coefficient leaves).
 bool jit_adjoint_passes_supported(const AmiTerms *t, bool hub, std::string *why);
 
+// Waves per block of the block adjoint for this input, 0 when the solution has
+// none (Taylor-coefficient leaves, too few groups to split evenly, or more
+// columns than the LDS of a CU holds).  jit_block_waves computes it;
+// jit_block_waves_of keeps it with the handle.
+int jit_block_waves(const AmiTerms *t, bool hub, bool cplx);
+int jit_block_waves_of(AmiTerms *t, bool hub);
+
 // Whether the diagram can be specialized for the energy (hub = false) or
 // momentum (hub = true) input; *why says why not.
 bool jit_supported(const AmiTerms *t, bool hub, std::string *why, bool two_pass = false);
@@ -54,7 +61,8 @@ int jit_block(const AmiTerms *t, bool hub);
 // stored per sample; kernels & 1024: per frequency, against them), and the
 // passes of the adjoint at complex energies that follow the first of those
 // (kernels & 2048: per frequency, the complex group-sum and denominator
-// cotangents; kernels & 4096: the complex leaf cotangents and the gradients).
+// cotangents; kernels & 4096: the complex leaf cotangents and the gradients),
+// and the block adjoint (kernels & 8192).
 // nested_part: terms per part of the one-pass adjoint's leaf cotangents as a
 // reverse sweep of the nested group sums (0: per-term prefix/suffix products;
 // -1: the AMIGPU_JIT_NESTED_COTANGENTS override, else per-term products).
@@ -100,7 +108,8 @@ int64_t code_meta(const std::vector<char> &code, const char *key);
 // kJitComplexSums and kJitComplexFreq the two passes of the forward at complex
 // energies (solutions above kJitMaxTerms terms); kJitComplexAdjFreq and
 // kJitComplexAdjLeaf the frequency and leaf passes of the adjoint at complex
-// energies (after kJitComplexSums).
+// energies (after kJitComplexSums); kJitBlockAdjoint the adjoint of large
+// solutions whose work the waves of a block split (no workspace).
 enum JitKind {
     kJitForward = 0,
     kJitAdjoint = 1,
@@ -114,9 +123,10 @@ enum JitKind {
     kJitComplexSums = 9,
     kJitComplexFreq = 10,
     kJitComplexAdjFreq = 11,
-    kJitComplexAdjLeaf = 12
+    kJitComplexAdjLeaf = 12,
+    kJitBlockAdjoint = 13
 };
-constexpr int kJitKinds = 13;
+constexpr int kJitKinds = 14;
 
 // Kinds for the energy input only (complex energies).
 inline bool jit_kind_complex(int kind) {

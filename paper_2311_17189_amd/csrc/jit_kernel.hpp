@@ -171,3 +171,14 @@ extern "C" __global__ __launch_bounds__(AMI_JIT_BLOCK) void ami_jit_cadjl(ami::K
     amijit::cadjl_tile(a, blockIdx.x);
 }
 #endif
+
+#if AMI_JIT_KERNELS & 8192
+// 64 samples per block of NW waves; two waves per SIMD (one alone issues an
+// FP64 instruction every eight cycles instead of four): two blocks of four
+// waves, or one of eight, on a CU
+extern "C" __global__ __launch_bounds__(64 * amijit::NW) __attribute__((amdgpu_waves_per_eu(2))) void ami_jit_badj(ami::KArgs a) {
+    __shared__ double sm[64 * amijit::kBlockCols];
+    if (a.n_f == 1) amijit::badj_tile<AMI_JIT_HUB, true>(a, blockIdx.x, sm);
+    else amijit::badj_tile<AMI_JIT_HUB, false>(a, blockIdx.x, sm);
+}
+#endif

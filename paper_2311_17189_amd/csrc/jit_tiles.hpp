@@ -1214,4 +1214,283 @@ __device__ __forceinline__ void cadj_tile(const KArgs &a, int64_t blk, double *p
 }
 #endif
 
+#if AMI_JIT_KERNELS & 8192
+// Block adjoint of large solutions: NW waves share 64 samples (lane i of every
+// wave is sample i), each wave with its own part of the solution, and what the
+// waves exchange lives in LDS columns (column c of lane i at [64 c + i]):
+//   energies and leaves   wave j mod NW forms line j and leaf j
+//   group sums, products, values and leaf sweep: each wave its own groups,
+//                         whose FT_g and FTB_g never leave its registers
+//   leaf cotangents       summed over the waves in rounds (blk_rounds), then
+//                         energies' cotangents, then the momenta's
+// What bounded the passes over a workspace that it replaces was not arithmetic
+// but waiting: the leaf pass held 50 leaves, their slopes and cotangents (1.4 KB
+// per lane more than its registers) and spent 82% of its wave cycles on spills,
+// the frequency pass 71% on one group's stored sum after another.  Split over
+// the waves, a wave's part fits its registers, the leaves come from LDS where
+// they are read, and nothing but inputs and results touches HBM; few samples
+// fill the chip, too.  Gradient step, one row (passes, here): 2804 terms 512 ->
+// 190 us at 2 10^5 samples, 142 -> 34 at 2 10^4, 87 -> 23 at 10^3; 560 terms
+// 113 -> 77 us, 264 terms 78 -> 64, 136 terms 57 -> 42 at 2 10^5.  What is left
+// of it is issue (2.1 10^4 VALU instructions per block, 115 us of the 190) and
+// the barriers of unequal waves.
+// The line momenta of a sample (a wave keeps those it uses).
+__device__ __forceinline__ void blk_lines(const KArgs &a, int64_t sc, double (&Kx)[NGA], double (&Ky)[NGA]) {
+    double in[NIN], kx[NIA], ky[NIA];
+    load_inputs<true>(a, sc, in);
+#pragma unroll
+    for (int l = 0; l < NI; ++l) {
+        kx[l] = ami::reduce_2pi(in[2 * l]);
+        ky[l] = ami::reduce_2pi(in[2 * l + 1]);
+    }
+    lines(kx, ky, a.q, Kx, Ky);
+}
+
+// The wave's energies to their columns.
+template <bool HUB, int WV>
+__device__ __forceinline__ void blk_energies(const KArgs &a, int64_t sc, ami::lds col) {
+    if constexpr (HUB) {
+        double Kx[NGA], Ky[NGA];
+        blk_lines(a, sc, Kx, Ky);
+#pragma unroll
+        for (int j = WV; j < NG; j += NW)
+            col[64 * (kBE + j)] = fma(2.0 * a.hop_t, ami::cos_red(Kx[j]) + ami::cos_red(Ky[j]), a.mu);
+    } else {
+        const double *row = a.energies + sc * a.stride_s;
+#pragma unroll
+        for (int i = WV; i < NE; i += NW) col[64 * (kBE + i)] = row[i * a.stride_i];
+    }
+}
+
+// The energies from their columns, read where they are needed.
+__device__ __forceinline__ void blk_read_energies(ami::clds col, double (&E)[NE]) {
+#pragma unroll
+    for (int i = 0; i < NE; ++i) E[i] = col[64 * (kBE + i)];
+}
+
+template <int WV>
+__device__ __forceinline__ void blk_leaves(const KArgs &a, ami::lds col) {
+    double E[NE], x[L];
+    blk_read_energies(col, E);
+    leaf_args(E, x);
+#pragma unroll
+    for (int l = WV; l < L; l += NW) {
+        double f, dv;
+        ami::leaf_and_slope(kBose[l], a.beta * (kBose[l] ? x[l] + a.e_reg : x[l]), f, dv);
+        col[64 * (kBF + l)] = f;
+        if constexpr (kBS >= 0) col[64 * (kBS + l)] = dv;
+    }
+}
+
+// sum over the waves of the columns first, first + 1, ... (in wave order)
+__device__ __forceinline__ double blk_wave_total(ami::clds col, int first) {
+    double v = col[64 * first];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v += col[64 * (first + w)];
+    return v;
+}
+
+// Columns of the last steps, from kBU: NW per energy (and beta) of the energies'
+// cotangents, then dL/dK_x and dL/dK_y per line and NW each for dL/dmu, dL/dt.
+constexpr int kBG = kBU + (NE + 1) * NW, kBM = kBG + 2 * NE;
+
+// The sums of the energies' cotangents that wave WV finishes, with the chain
+// rule's step to the lines on the momentum input (their sin and cos formed
+// here: three columns per line through the whole tile would cost a block its
+// neighbour on the CU); on the energy input the gradient rows go to the
+// staging area (row stride NE + 1).
+template <bool HUB, int WV>
+__device__ __forceinline__ void blk_energy_grads(const KArgs &a, int64_t sc, int lane, ami::lds col, double *stage,
+                                                 double &gmu, double &gt) {
+    double Kx[NGA], Ky[NGA];
+    if constexpr (HUB) blk_lines(a, sc, Kx, Ky);
+#pragma unroll
+    for (int i = WV; i < NE; i += NW) {
+        const double g = blk_wave_total(col, kBU + i * NW);
+        if constexpr (HUB) {
+            double sx, cx, sy, cy;
+            ami::sincos_red(Kx[i], sx, cx);
+            ami::sincos_red(Ky[i], sy, cy);
+            gmu += g;
+            gt = fma(g, 2.0 * (cx + cy), gt);
+            col[64 * (kBG + i)] = -2.0 * a.hop_t * g * sx;
+            col[64 * (kBG + NE + i)] = -2.0 * a.hop_t * g * sy;
+        } else {
+            stage[lane * (NE + 1) + i] = g;
+        }
+    }
+}
+
+template <int WV>
+__device__ __forceinline__ void blk_momentum_grads(int lane, ami::clds col, double *stage) {
+    double gx[NGA], gy[NGA], gkx[NIA], gky[NIA];
+#pragma unroll
+    for (int j = 0; j < NG; ++j) {
+        gx[j] = col[64 * (kBG + j)];
+        gy[j] = col[64 * (kBG + NE + j)];
+    }
+#pragma unroll
+    for (int l = 0; l < NIA; ++l) gkx[l] = gky[l] = 0.0;
+    line_scatter(gx, gy, gkx, gky);
+#pragma unroll
+    for (int c = WV; c < 2 * NI; c += NW) stage[lane * (2 * NI + 1) + c] = (c & 1) ? gky[c / 2] : gkx[c / 2];
+}
+
+// rows of W doubles staged at a stride of W + 1, the first n of them to dst
+template <int W>
+__device__ __forceinline__ void blk_store_rows(const double *stage, double *dst, int64_t n) {
+    for (int e = threadIdx.x; e < 64 * W; e += 64 * NW) {
+        const int r = e / W;
+        if (r < n) dst[e] = stage[e + r];
+    }
+}
+
+// Wave WV of the block.  The waves run copies of this function of their own
+// (badj_tile's uniform switch), which pass the same barriers.
+// ONE: one frequency row.
+template <bool HUB, int WV, bool ONE>
+__device__ __forceinline__ void badj_wave(const KArgs &a, int64_t tile, double *sm) {
+    constexpr int wv = WV;
+    const int lane = threadIdx.x & 63;
+    const int64_t s0 = tile * 64, s = s0 + lane;
+    const bool active = s < a.n_e;
+    const int64_t sc = active ? s : a.n_e - 1;
+    const ami::lds col = (ami::lds)sm + lane;
+
+    blk_energies<HUB, WV>(a, sc, col);
+    __syncthreads();
+    blk_leaves<WV>(a, col);
+    __syncthreads();
+    double ft[GW], ftb[GW], gE[NE];
+#pragma unroll
+    for (int g = 0; g < GW; ++g) ft[g] = ftb[g] = 0.0;
+#pragma unroll
+    for (int i = 0; i < NE; ++i) gE[i] = 0.0;
+    blk_sums<WV>(col + 64 * kBF, col + 64 * kBT, ft);
+
+    double *gp = a.gpartial + tile;                  // column c at gp[c * nrows]
+    // a row's values and sums from the waves' parts
+    auto finish_row = [&](int f) __attribute__((always_inline)) {
+                    const double re = blk_wave_total(col, kBA), im = blk_wave_total(col, kBA + NW);
+                    if (active && a.out) {
+                        double2 v;
+                        v.x = re;
+                        v.y = im;
+                        reinterpret_cast<double2 *>(a.out)[static_cast<int64_t>(f) * a.n_e + s] = v;
+                    }
+                    constexpr int NV = 2 * NX + 2, NV4 = (NV + 3) / 4 * 4;
+                    double vv[NV4];
+                    double *pp[NV4];
+        #pragma unroll
+                    for (int x = 0; x < NX; ++x) {
+                        const double r = blk_wave_total(col, kBA + (2 + 2 * x) * NW);
+                        const double i = blk_wave_total(col, kBA + (3 + 2 * x) * NW);
+                        vv[2 * x] = active ? r : 0.0;
+                        vv[2 * x + 1] = active ? -i : 0.0;
+                        pp[2 * x] = gp + (ami::kAdjScalars + 2 * (f * NX + x)) * a.nrows;
+                        pp[2 * x + 1] = pp[2 * x] + a.nrows;
+                    }
+                    vv[2 * NX] = active ? re : 0.0;
+                    vv[2 * NX + 1] = active ? im : 0.0;
+                    pp[2 * NX] = a.partial ? a.partial + 2 * f * a.nrows + tile : nullptr;
+                    pp[2 * NX + 1] = a.partial ? pp[2 * NX] + a.nrows : nullptr;
+        #pragma unroll
+                    for (int c = NV; c < NV4; ++c) {
+                        vv[c] = 0.0;
+                        pp[c] = nullptr;
+                    }
+        #pragma unroll
+                    for (int c = 0; c < NV4; c += 4)
+                        ami::wave_store4(vv[c], vv[c + 1], vv[c + 2], vv[c + 3], lane, pp[c], pp[c + 1], pp[c + 2], pp[c + 3]);
+    };
+    const int nf = ONE ? 1 : a.n_f;
+    for (int f = 0; f < nf; ++f) {
+        double cr = 0.0, ci = 0.0;
+        if (active) {
+            if (a.g_out) {
+                cr = a.g_out[2 * (static_cast<int64_t>(f) * a.n_e + s)];
+                ci = a.g_out[2 * (static_cast<int64_t>(f) * a.n_e + s) + 1];
+            }
+            if (a.g_sum) {
+                cr += a.g_sum[2 * f];
+                ci += a.g_sum[2 * f + 1];
+            }
+        }
+        double wr[NXA], wi[NXA], gwr[NXA], gwi[NXA], acc_re = 0.0, acc_im = 0.0;
+        load_freq(a, f, wr, wi);
+#pragma unroll
+        for (int x = 0; x < NXA; ++x) gwr[x] = gwi[x] = 0.0;
+        blk_freq<WV, ONE>(col + 64 * kBE, wr, wi, col + 64 * kBT, ft, cr, ci, ftb, acc_re, acc_im, gE, gwr, gwi);
+        if (f > 0) __syncthreads();                  // the last row's sums have been read
+        col[64 * (kBA + wv)] = acc_re;
+        col[64 * (kBA + NW + wv)] = acc_im;
+#pragma unroll
+        for (int x = 0; x < NX; ++x) {
+            col[64 * (kBA + (2 + 2 * x) * NW + wv)] = gwr[x];
+            col[64 * (kBA + (3 + 2 * x) * NW + wv)] = gwi[x];
+        }
+        if constexpr (!ONE) {
+            __syncthreads();
+            if (wv == f % NW) finish_row(f);
+        }
+    }
+
+    double FB[L], gbeta = 0.0;
+#pragma unroll
+    for (int l = 0; l < L; ++l) FB[l] = 0.0;
+    if constexpr (!ONE) blk_keep<WV>(col + 64 * kBT, ftb);
+    blk_leaf<WV>(col + 64 * kBF, col + 64 * kBT, ftb, FB);
+    blk_rounds<WV>(FB, a.beta, a.e_reg, col + 64 * kBE, col + 64 * kBU, col + 64 * kBS, gE, gbeta);
+    // one row: its parts have waited in their columns, so that a wave goes from
+    // its groups' products to their leaf sweep without meeting the others
+    if constexpr (ONE && WV == 0) finish_row(0);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NE; ++i) col[64 * (kBU + i * NW + wv)] = gE[i];
+    col[64 * (kBU + NE * NW + wv)] = gbeta;
+    __syncthreads();
+
+    double gmu = 0.0, gt = 0.0;
+    const int64_t n_rows = a.n_e - s0 < 64 ? a.n_e - s0 : 64;
+    // the staged gradient rows: over the first columns, which nothing reads any
+    // more once the momenta's are formed, or in the momentum input's own columns
+    double *const stage = sm + 64 * (HUB ? kBE : kBG);
+    if constexpr (HUB) {
+        blk_energy_grads<HUB, WV>(a, sc, lane, col, nullptr, gmu, gt);
+        col[64 * (kBM + wv)] = gmu;
+        col[64 * (kBM + NW + wv)] = gt;
+        __syncthreads();
+        blk_momentum_grads<WV>(lane, col, stage);
+    } else {
+        blk_energy_grads<HUB, WV>(a, sc, lane, col, stage, gmu, gt);
+    }
+    if constexpr (WV == NW - 1) {
+        const double b = blk_wave_total(col, kBU + NE * NW);
+        const double m = HUB ? blk_wave_total(col, kBM) : 0.0, t = HUB ? blk_wave_total(col, kBM + NW) : 0.0;
+        ami::wave_store4(active ? b : 0.0, active ? m : 0.0, active ? t : 0.0, 0.0, lane, gp, gp + a.nrows,
+                         gp + 2 * a.nrows, nullptr);
+    }
+    __syncthreads();
+    if constexpr (HUB) {
+        if (a.grad_k) blk_store_rows<2 * NI>(stage, a.grad_k + s0 * (2 * NI), n_rows);
+    } else {
+        if (a.grad_e) blk_store_rows<NE>(stage, a.grad_e + s0 * NE, n_rows);
+    }
+}
+
+template <bool HUB, bool ONE>
+__device__ __forceinline__ void badj_tile(const KArgs &a, int64_t tile, double *sm) {
+    switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
+    case 0: badj_wave<HUB, 0, ONE>(a, tile, sm); break;
+    case 1: badj_wave<HUB, 1, ONE>(a, tile, sm); break;
+    case 2: if constexpr (NW > 2) badj_wave<HUB, 2, ONE>(a, tile, sm); break;
+    case 3: if constexpr (NW > 2) badj_wave<HUB, 3, ONE>(a, tile, sm); break;
+    case 4: if constexpr (NW > 4) badj_wave<HUB, 4, ONE>(a, tile, sm); break;
+    case 5: if constexpr (NW > 4) badj_wave<HUB, 5, ONE>(a, tile, sm); break;
+    case 6: if constexpr (NW > 4) badj_wave<HUB, 6, ONE>(a, tile, sm); break;
+    case 7: if constexpr (NW > 4) badj_wave<HUB, 7, ONE>(a, tile, sm); break;
+    }
+}
+#endif
+
 }  // namespace amijit
