@@ -364,6 +364,11 @@ bool jit_prefers_two_pass(const AmiTerms *t) {
     return tb.T > kJitMaxTerms || 2 * tb.G + 4 * tb.D > 128;
 }
 
+bool jit_prefers_block_adjoint(const AmiTerms *t) {
+    const Tables &tb = t->tab;
+    return tb.T > kJitAutoAdjointTerms || tb.L + 4 * tb.G + 4 * tb.D + 2 * t->n_eps > 100;
+}
+
 bool jit_supported(const AmiTerms *t, bool hub, std::string *why, bool two_pass) {
     const Tables &tb = t->tab;
     auto no = [&](const std::string &m) {
@@ -531,9 +536,9 @@ BlockPlan block_plan(const AmiTerms *t, bool hub, bool cplx, int waves) {
         p.c_leaf = p.c_union;
         p.c_group = group ? p.c_leaf + cw * L : -1;
         p.columns = p.c_leaf + cw * L + (group ? cw * G : 0);
-        // the reduction of the energies' cotangents and what follows it; the
-        // staged gradient rows at the start
-        p.columns = std::max(p.columns, p.c_union + (cw * ne + 1) * waves + 2 * ne + 2 * waves);
+        // the reduction of the energies' cotangents, on the momentum input
+        // beside the lines'; the staged gradient rows lie over the first columns
+        p.columns = std::max(p.columns, p.c_union + (cw * ne + 1) * waves + (hub ? 2 * ne + 2 * waves : 0));
         p.columns = std::max(p.columns, hub ? 2 * ni + 1 : cw * ne + 1);
         fits = p.columns <= limit;
     }
@@ -574,11 +579,13 @@ BlockPlan block_plan(const AmiTerms *t, bool hub, bool cplx, int waves) {
 
 // Waves per block of the block adjoint (AMIGPU_JIT_BLOCK_WAVES overrides): as
 // few as leave each wave a part that fits its registers, since every wave more
-// is another partner at each barrier.  Two up to 200 terms (136 terms, 2 10^5
-// samples: 41.6 us a step, four waves 50.4; 264 terms at four rows and 5 10^4
-// samples: 38.0 and 35.8), else four (560 terms 78.7, 76.9 and with eight 119;
-// 2804 terms 233, 190 and 233), and eight, alone on its CU, where the columns of
-// four do not fit half its LDS.
+// is another partner at each barrier.  Real energies: two up to 200 terms (76
+// terms, 2 10^5 samples: 38.8 us a step, four waves 40.8; 136 terms 41.6 and
+// 50.4; 264 terms at four rows and 5 10^4 samples: 38.0 and 35.8), else four (560
+// terms 78.7, 76.9 and with eight 119; 2804 terms 233, 190 and 233).  Complex
+// energies, whose parts are twice as large: four (136 terms 78.7 and 65.8, 560
+// terms 168, 134 and with eight 172).  Eight, alone on its CU, where the columns
+// of four do not fit half its LDS.
 int jit_block_waves(const AmiTerms *t, bool hub, bool cplx) {
     for (int o : t->tab.leaf_order)
         if (o > 0) return 0;              // Taylor-coefficient leaves: the passes over a workspace
@@ -588,7 +595,7 @@ int jit_block_waves(const AmiTerms *t, bool hub, bool cplx) {
         return v == 2 || v == 4 || v == 8 ? block_plan(t, hub, cplx, v).waves : 0;
     }
     for (int w : {2, 4, 8}) {
-        if (w == 2 && t->tab.T > 200) continue;
+        if (w == 2 && (cplx || t->tab.T > 200)) continue;
         const BlockPlan p = block_plan(t, hub, cplx, w);
         if (p.waves > 0 && p.imbalance <= 1.6) return w;
     }
@@ -1299,57 +1306,80 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
         o << "}\n";
     }
 
+    // Shared by the block adjoints: the plan's constants, per-wave functions
+    // (wave WV of a block), a range of terms, and the reads of a range's leaves.
+    const bool blk_cplx = (kernels & 16384) != 0;
+    BlockPlan bp;
+    if (kernels & (8192 | 16384)) bp = block_plan(t, hub, blk_cplx, jit_block_waves(t, hub, blk_cplx));
+    auto wave_fn = [&](const std::string &name, const std::string &args, bool reverse, const auto &body) {
+        o << "template <int WV" << (name == "blk_freq" ? ", bool ONE" : "") << "> __device__ __forceinline__ void " << name << "(" << args << ") {\n";
+        if (reverse) o << kReverseContract;
+        for (int w = 0; w < bp.waves; ++w) {
+            o << "  if constexpr (WV == " << w << ") {\n";
+            body(w);
+            o << "  }\n";
+        }
+        o << "}\n";
+    };
+    auto terms_of = [&](int t0, int t1) {
+        std::vector<HornerTerm> ts;
+        for (int ti = t0; ti < t1; ++ti) {
+            HornerTerm h{tb.term_sign[ti], {}};
+            for (int j = 0; j < ni; ++j) h.leaves.push_back(tb.term_leaf[static_cast<size_t>(ti) * ni + j]);
+            ts.push_back(std::move(h));
+        }
+        return ts;
+    };
+    auto leaves_of = [&](int t0, int t1) {
+        std::vector<int> used;
+        for (int ti = t0; ti < t1; ++ti)
+            for (int j = 0; j < ni; ++j) used.push_back(tb.term_leaf[static_cast<size_t>(ti) * ni + j]);
+        std::sort(used.begin(), used.end());
+        used.erase(std::unique(used.begin(), used.end()), used.end());
+        return used;
+    };
+    auto dens_of = [&](int w) {
+        std::vector<int> ks;
+        for (int g = bp.first[w]; g < bp.first[w + 1]; ++g)
+            for (int j = gbegin(g); j < gend(g); ++j) ks.push_back(tb.group_den_list[j]);
+        std::sort(ks.begin(), ks.end());
+        ks.erase(std::unique(ks.begin(), ks.end()), ks.end());
+        return ks;
+    };
+    if (kernels & 16384)
+        // f(y) and conj(f'(y)) = -conj(f(y) f(-y))
+        o << "__device__ __forceinline__ void blk_cleaf(bool bose, double yr, double yi, double &fr, double &fi, double "
+             "&Sr, double &Si) {\n  double mr, mi;\n  ami::leaf_complex_pair(bose, yr, yi, fr, fi, mr, mi);\n"
+             "  Sr = -fma(fr, mr, -fi * mi);\n  Si = fma(fr, mi, fi * mr);\n}\n";
+    if (kernels & (8192 | 16384)) {
+        o << "constexpr int NW = " << bp.waves << ", GW = " << bp.max_groups << ", kRounds = " << bp.round.size() - 1
+          << ", kBlockCols = " << bp.columns << ";\n";
+        o << "constexpr int kBE = " << bp.c_e << ", kBS = " << bp.c_slope << ", kBU = " << bp.c_union << ", kBF = "
+          << bp.c_leaf << ", kBT = " << bp.c_group << ", kBA = " << bp.c_acc << ";\n";
+        o << "__device__ __forceinline__ void blk_rho(double dr, double di, double &xr, double &xi) {\n"
+             "  const double inv = ami::rcp_nr(fma(dr, dr, di * di));\n  xr = dr * inv;\n  xi = -di * inv;\n}\n";
+    }
     if (kernels & 8192) {
         // The block adjoint's per-wave functions (wave WV of a block of NW
         // waves that share 64 samples; LDS columns are passed as the address
         // of the lane's element in the first column of a region, column c of
         // it at [64 c]).
-        const BlockPlan bp = block_plan(t, hub, false, jit_block_waves(t, hub, false));
         const int W = bp.waves;
-        o << "constexpr int NW = " << W << ", GW = " << bp.max_groups << ", kRounds = " << bp.round.size() - 1
-          << ", kBlockCols = " << bp.columns << ";\n";
-        o << "constexpr int kBE = " << bp.c_e << ", kBS = " << bp.c_slope << ", kBU = " << bp.c_union << ", kBF = "
-          << bp.c_leaf << ", kBT = " << bp.c_group << ", kBA = " << bp.c_acc << ";\n";
         const bool group_cols = bp.c_group >= 0, slope_cols = bp.c_slope >= 0;
         // group g's sum (before the leaf sweep) or cotangent (in it) of wave w
         auto gsum = [&](int w, int g, const char *reg) {
             return group_cols ? "sT[" + std::to_string(64 * g) + "]" : idx(reg, g - bp.first[w]);
         };
-        auto wave_fn = [&](const std::string &name, const std::string &args, bool reverse, const auto &body) {
-            o << "template <int WV" << (name == "blk_freq" ? ", bool ONE" : "") << "> __device__ __forceinline__ void " << name << "(" << args << ") {\n";
-            if (reverse) o << kReverseContract;
-            for (int w = 0; w < W; ++w) {
-                o << "  if constexpr (WV == " << w << ") {\n";
-                body(w);
-                o << "  }\n";
-            }
-            o << "}\n";
-        };
         // the leaves that terms [t0, t1) read, as "const double f<l>" from the
         // columns of a pointer taken through an empty asm (so that the compiler
         // loads them again here instead of holding every leaf)
         auto load_leaves = [&](int t0, int t1) {
-            std::vector<int> used;
-            for (int ti = t0; ti < t1; ++ti)
-                for (int j = 0; j < ni; ++j) used.push_back(tb.term_leaf[static_cast<size_t>(ti) * ni + j]);
-            std::sort(used.begin(), used.end());
-            used.erase(std::unique(used.begin(), used.end()), used.end());
+            const std::vector<int> used = leaves_of(t0, t1);
             o << "    ami::clds p = sF; AMI_OPAQUE(p);\n   ";
             for (int l : used) o << " const double f" << l << " = p[" << 64 * l << "];";
             o << "\n";
         };
-        o << "__device__ __forceinline__ void blk_rho(double dr, double di, double &xr, double &xi) {\n"
-             "  const double inv = ami::rcp_nr(fma(dr, dr, di * di));\n  xr = dr * inv;\n  xi = -di * inv;\n}\n";
         auto fname = [](int l) { return "f" + std::to_string(l); };
-        auto terms_of = [&](int t0, int t1) {
-            std::vector<HornerTerm> ts;
-            for (int ti = t0; ti < t1; ++ti) {
-                HornerTerm h{tb.term_sign[ti], {}};
-                for (int j = 0; j < ni; ++j) h.leaves.push_back(tb.term_leaf[static_cast<size_t>(ti) * ni + j]);
-                ts.push_back(std::move(h));
-            }
-            return ts;
-        };
         // group sums of the wave's groups
         wave_fn("blk_sums", "ami::clds sF, ami::lds sT, double (&ft)[GW]", false, [&](int w) {
             o << "    (void)sT; (void)ft;\n";
@@ -1373,11 +1403,7 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
                     "], ami::lds sT, const double (&ft)[GW], double cr, double ci, double (&ftb)[GW], double &acc_re, "
                     "double &acc_im, double (&gE)[NE], double (&gwr)[" + NXA + "], double (&gwi)[" + NXA + "]",
                 true, [&](int w) {
-            std::vector<int> ks;
-            for (int g = bp.first[w]; g < bp.first[w + 1]; ++g)
-                for (int j = gbegin(g); j < gend(g); ++j) ks.push_back(tb.group_den_list[j]);
-            std::sort(ks.begin(), ks.end());
-            ks.erase(std::unique(ks.begin(), ks.end()), ks.end());
+            const std::vector<int> ks = dens_of(w);
             // the columns through an empty asm: the sums are read here, not
             // held in registers since they were written
             o << "    AMI_OPAQUE(sT); (void)ft; (void)ftb;\n    double E[NE];\n#pragma unroll\n    for (int i = 0; i < NE; ++i) E[i] = sE[64 * i];\n";
@@ -1524,6 +1550,248 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
         for (size_t r = 0; r + 1 < bp.round.size(); ++r)
             o << "  __syncthreads();\n  blk_put" << r << "<WV>(FB, sR);\n  __syncthreads();\n  blk_take" << r
               << "<WV>(beta, e_reg, sE, sR, sS, gE, gbeta);\n";
+        o << "}\n";
+    }
+
+    if (kernels & 16384) {
+        // The block adjoint at complex energies: the same split, every value of
+        // a leaf, a group sum or an energy two columns (real, imaginary) or two
+        // registers; cotangents Xbar = dL/dRe X + i dL/dIm X.
+        const int W = bp.waves;
+        const bool group_cols = bp.c_group >= 0, slope_cols = bp.c_slope >= 0;
+        auto gsum = [&](int w, int g, int im, const char *reg) {
+            return group_cols ? "sT[" + std::to_string(64 * (2 * g + im)) + "]"
+                              : std::string(reg) + (im ? "i[" : "r[") + std::to_string(g - bp.first[w]) + "]";
+        };
+        auto load_leaves = [&](int t0, int t1) {
+            o << "    ami::clds p = sF; AMI_OPAQUE(p);\n   ";
+            for (int l : leaves_of(t0, t1))
+                o << " const double fr" << l << " = p[" << 128 * l << "], fi" << l << " = p[" << 128 * l + 64 << "];";
+            o << "\n";
+        };
+        auto scatter2 = [&](const double *coef, const std::string &vr, const std::string &vi, double sr, double si) {
+            for (int i = 0; i < ne; ++i) {
+                const double c = coef[i];
+                if (c == 0.0) continue;
+                o << "      gEr[" << i << "] = fma(" << num(sr * c) << ", " << vr << ", gEr[" << i << "]); gEi[" << i
+                  << "] = fma(" << num(si * c) << ", " << vi << ", gEi[" << i << "]);\n";
+            }
+        };
+        wave_fn("blk_sums", "ami::clds sF, ami::lds sT, double (&ftr)[GW], double (&fti)[GW]", false, [&](int w) {
+            o << "    (void)sT; (void)ftr; (void)fti;\n";
+            for (int g = bp.first[w]; g < bp.first[w + 1]; ++g) {
+                if (g > bp.first[w]) o << "  AMI_SCHED_FENCE();\n";
+                o << "  {\n";
+                load_leaves(tb.group_start[g], tb.group_start[g + 1]);
+                auto leaf = [&](int l) {
+                    CVal v;
+                    v.kind = CVal::CPLX;
+                    v.re = "fr" + std::to_string(l);
+                    v.im = "fi" + std::to_string(l);
+                    return v;
+                };
+                int temps = 0;
+                CMemo memo;
+                const CVal v = horner_c(terms_of(tb.group_start[g], tb.group_start[g + 1]), leaf, o, temps, memo);
+                const std::string re = v.kind == CVal::ZERO ? "0.0" : v.kind == CVal::CONST ? num(v.c) : v.re;
+                o << "    " << gsum(w, g, 0, "ft") << " = " << re << "; " << gsum(w, g, 1, "ft") << " = "
+                  << (v.kind == CVal::CPLX ? v.im : "0.0") << "; }\n";
+            }
+        });
+        wave_fn("blk_freq",
+                "ami::clds sE, const double (&wr)[" + NXA + "], const double (&wi)[" + NXA +
+                    "], ami::lds sT, const double (&ftr)[GW], const double (&fti)[GW], double cr, double ci, double "
+                    "(&ftbr)[GW], double (&ftbi)[GW], double &acc_re, double &acc_im, double (&gEr)[NE], double "
+                    "(&gEi)[NE], double (&gwr)[" + NXA + "], double (&gwi)[" + NXA + "]",
+                true, [&](int w) {
+            const std::vector<int> ks = dens_of(w);
+            o << "    AMI_OPAQUE(sT); (void)ftr; (void)fti; (void)ftbr; (void)ftbi;\n    double Er[NE], Ei[NE];\n"
+                 "#pragma unroll\n    for (int i = 0; i < NE; ++i) {\n      Er[i] = sE[64 * i];\n      Ei[i] = sE[64 * (NE + "
+                 "i)];\n    }\n";
+            for (int k : ks) {
+                Lin re, im;
+                for (int i = 0; i < ne; ++i) {
+                    re.add(tb.den_coef[static_cast<size_t>(k) * nc + i], idx("Er", i));
+                    im.add(tb.den_coef[static_cast<size_t>(k) * nc + i], idx("Ei", i));
+                }
+                for (int x = 0; x < nx; ++x) {
+                    const double a = tb.den_coef[static_cast<size_t>(k) * nc + ne + x];
+                    re.add(a, idx("wr", x));
+                    im.add(a, idx("wi", x));
+                }
+                o << "    double xr" << k << ", xi" << k << ", Ur" << k << " = 0.0, Ui" << k << " = 0.0;\n    blk_rho("
+                  << re.str() << ", " << im.str() << ", xr" << k << ", xi" << k << ");\n";
+            }
+            for (int g = bp.first[w]; g < bp.first[w + 1]; ++g) {
+                const std::string j0 = std::to_string(g - bp.first[w]);
+                o << "    { double rr = 1.0, ri = 0.0, nr = 0.0;\n";
+                for (int j = gbegin(g); j < gend(g); ++j) {
+                    const std::string k = std::to_string(tb.group_den_list[j]);
+                    if (j == gbegin(g)) o << "      rr = xr" << k << "; ri = xi" << k << ";\n";
+                    else
+                        o << "      nr = fma(rr, xr" << k << ", -ri * xi" << k << "); ri = fma(rr, xi" << k << ", ri * xr"
+                          << k << "); rr = nr;\n";
+                }
+                o << "      (void)nr;\n      const double tr = " << gsum(w, g, 0, "ft") << ", ti = " << gsum(w, g, 1, "ft")
+                  << ";\n      const double qr = fma(tr, rr, -ti * ri), qi = fma(tr, ri, ti * rr);\n"
+                     "      const double tbr = fma(cr, rr, ci * ri), tbi = fma(ci, rr, -cr * ri);\n";
+                if (group_cols)
+                    o << "      if constexpr (ONE) { sT[" << 128 * g << "] = tbr; sT[" << 128 * g + 64
+                      << "] = tbi; }\n      else ";
+                o << "{ ftbr[" << j0 << "] += tbr; ftbi[" << j0 << "] += tbi; }\n      acc_re += qr; acc_im += qi;\n";
+                for (int j = gbegin(g); j < gend(g); ++j) {
+                    const std::string k = std::to_string(tb.group_den_list[j]);
+                    o << "      Ur" << k << " += qr; Ui" << k << " += qi;\n";
+                }
+                o << "    }\n";
+            }
+            for (int k : ks) {
+                const std::string K = std::to_string(k);
+                o << "    { const double vr = -fma(Ur" << K << ", cr, Ui" << K << " * ci), vi = -fma(Ui" << K << ", cr, -Ur"
+                  << K << " * ci);\n      const double dR = fma(vr, xr" << K << ", -vi * xi" << K << "), dI = fma(vr, xi"
+                  << K << ", vi * xr" << K << ");\n      (void)dI;\n";
+                scatter2(&tb.den_coef[static_cast<size_t>(k) * nc], "dR", "dI", 1.0, -1.0);
+                for (int x = 0; x < nx; ++x) {
+                    const double a = tb.den_coef[static_cast<size_t>(k) * nc + ne + x];
+                    if (a == 0.0) continue;
+                    o << "      gwr[" << x << "] = fma(" << num(a) << ", dR, gwr[" << x << "]);\n";
+                    o << "      gwi[" << x << "] = fma(" << num(a) << ", dI, gwi[" << x << "]);\n";
+                }
+                o << "    }\n";
+            }
+        });
+        if (group_cols)
+            wave_fn("blk_keep", "ami::lds sT, const double (&ftbr)[GW], const double (&ftbi)[GW]", false, [&](int w) {
+                for (int g = bp.first[w]; g < bp.first[w + 1]; ++g)
+                    o << "    sT[" << 128 * g << "] = ftbr[" << g - bp.first[w] << "]; sT[" << 128 * g + 64 << "] = ftbi["
+                      << g - bp.first[w] << "];\n";
+            });
+        else
+            wave_fn("blk_keep", "ami::lds, const double (&)[GW], const double (&)[GW]", false, [&](int) {});
+        // a node h = F_a w + u passes hbar conj(w) to F_a, hbar conj(F_a) to w
+        // and hbar to u
+        wave_fn("blk_leaf",
+                "ami::clds sF, ami::clds sT, const double (&ftbr)[GW], const double (&ftbi)[GW], double (&FBr)[L], double "
+                "(&FBi)[L]",
+                true, [&](int w) {
+            o << "    (void)sT; (void)ftbr; (void)ftbi;\n";
+            auto vre = [&](const HRef &r) -> std::string {
+                if (r.kind == HRef::LEAF) return "fr" + std::to_string(r.idx);
+                if (r.kind == HRef::NODE) return "h" + std::to_string(r.idx) + "r";
+                return r.kind == HRef::CONST ? num(r.c) : std::string("0.0");
+            };
+            auto vim = [&](const HRef &r) -> std::string {
+                if (r.kind == HRef::LEAF) return "fi" + std::to_string(r.idx);
+                if (r.kind == HRef::NODE) return "h" + std::to_string(r.idx) + "i";
+                return std::string("0.0");
+            };
+            auto sg = [](const HRef &r, const std::string &e) { return r.neg ? "(-" + e + ")" : e; };
+            for (int g = bp.first[w]; g < bp.first[w + 1]; ++g)
+                for (int t0 = tb.group_start[g]; t0 < tb.group_start[g + 1]; t0 += kBlockPartTerms) {
+                    const int t1 = std::min(tb.group_start[g + 1], t0 + kBlockPartTerms);
+                    std::vector<HNode> nodes;
+                    const HRef root = horner_build(terms_of(t0, t1), nodes);
+                    if (g > bp.first[w] || t0 > tb.group_start[g]) o << "  AMI_SCHED_FENCE();\n";
+                    o << "  {\n";
+                    load_leaves(t0, t1);
+                    const size_t nn = nodes.size();
+                    for (size_t k = 0; k < nn; ++k) {
+                        const HNode &n = nodes[k];
+                        const std::string far = "fr" + std::to_string(n.a), fai = "fi" + std::to_string(n.a);
+                        std::string ur, ui;
+                        if (n.u.kind == HRef::CONST) {
+                            ur = num(n.u.c);
+                        } else if (n.u.kind != HRef::ZERO) {
+                            ur = sg(n.u, vre(n.u));
+                            ui = sg(n.u, vim(n.u));
+                        }
+                        std::string hr, hi;
+                        if (n.w.kind == HRef::CONST) {
+                            hr = fused({{false, num(n.w.c), far}}, ur);
+                            hi = fused({{false, num(n.w.c), fai}}, ui);
+                        } else {
+                            const std::string wr = sg(n.w, vre(n.w)), wi = sg(n.w, vim(n.w));
+                            hr = fused({{false, far, wr}, {true, fai, wi}}, ur);
+                            hi = fused({{false, far, wi}, {false, fai, wr}}, ui);
+                        }
+                        o << "    const double h" << k << "r = " << hr << ", h" << k << "i = " << hi << ";\n";
+                    }
+                    for (size_t k = 0; k < nn; ++k) o << "    double hb" << k << "r = 0.0, hb" << k << "i = 0.0;\n";
+                    auto pass = [&](const HRef &r, const std::string &cr, const std::string &ci) {
+                        const char *op = r.neg ? " -= " : " += ";
+                        if (r.kind == HRef::NODE)
+                            o << "    hb" << r.idx << "r" << op << cr << "; hb" << r.idx << "i" << op << ci << ";\n";
+                        else if (r.kind == HRef::LEAF)
+                            o << "    FBr[" << r.idx << "]" << op << cr << "; FBi[" << r.idx << "]" << op << ci << ";\n";
+                    };
+                    pass(root, gsum(w, g, 0, "ftb"), gsum(w, g, 1, "ftb"));
+                    for (size_t kk = nn; kk-- > 0;) {
+                        const HNode &n = nodes[kk];
+                        const std::string A = std::to_string(n.a);
+                        const std::string br = "hb" + std::to_string(kk) + "r", bi = "hb" + std::to_string(kk) + "i";
+                        const std::string far = "fr" + A, fai = "fi" + A, fbr = "FBr[" + A + "]", fbi = "FBi[" + A + "]";
+                        if (n.w.kind == HRef::CONST) {
+                            o << "    " << fbr << " = fma(" << num(n.w.c) << ", " << br << ", " << fbr << "); " << fbi
+                              << " = fma(" << num(n.w.c) << ", " << bi << ", " << fbi << ");\n";
+                        } else {
+                            const std::string wr = sg(n.w, vre(n.w)), wi = sg(n.w, vim(n.w));
+                            o << "    " << fbr << " = fma(" << br << ", " << wr << ", fma(" << bi << ", " << wi << ", " << fbr
+                              << ")); " << fbi << " = fma(" << bi << ", " << wr << ", fma(-" << br << ", " << wi << ", "
+                              << fbi << "));\n";
+                            pass(n.w, "fma(" + br + ", " + far + ", " + bi + " * " + fai + ")",
+                                 "fma(" + bi + ", " + far + ", -" + br + " * " + fai + ")");
+                        }
+                        pass(n.u, br, bi);
+                    }
+                    o << "  }\n";
+                }
+        });
+        for (size_t r = 0; r + 1 < bp.round.size(); ++r) {
+            const std::string R = std::to_string(r);
+            wave_fn("blk_put" + R, "const double (&FBr)[L], const double (&FBi)[L], ami::lds sR", false, [&](int w) {
+                for (int l = bp.round[r]; l < bp.round[r + 1]; ++l)
+                    if (bp.slot[l][w] >= 0)
+                        o << "    sR[" << 64 * bp.slot[l][w] << "] = FBr[" << l << "]; sR[" << 64 * bp.slot[l][w] + 64
+                          << "] = FBi[" << l << "];\n";
+            });
+            wave_fn("blk_take" + R,
+                    "double beta, double e_reg, ami::clds sE, ami::clds sR, ami::clds sS, double (&gEr)[NE], double "
+                    "(&gEi)[NE], double &gbeta",
+                    true, [&](int w) {
+                o << "    (void)e_reg; (void)sS;\n";
+                for (int l = bp.round[r]; l < bp.round[r + 1]; ++l) {
+                    if (l % W != w) continue;
+                    Lin sr, si, xr, xi;
+                    for (int v = 0; v < W; ++v)
+                        if (bp.slot[l][v] >= 0) {
+                            sr.add(1.0, "sR[" + std::to_string(64 * bp.slot[l][v]) + "]");
+                            si.add(1.0, "sR[" + std::to_string(64 * bp.slot[l][v] + 64) + "]");
+                        }
+                    for (int i = 0; i < ne; ++i) {
+                        xr.add(tb.leaf_coef[static_cast<size_t>(l) * ne + i], "sE[" + std::to_string(64 * i) + "]");
+                        xi.add(tb.leaf_coef[static_cast<size_t>(l) * ne + i], "sE[" + std::to_string(64 * (ne + i)) + "]");
+                    }
+                    const bool bose = tb.leaf_sigma[l] < 0;
+                    o << "    { const double xr = " << xr.str() << (bose ? " + e_reg" : "") << ", xi = " << xi.str() << ";\n";
+                    if (slope_cols)
+                        o << "      const double Sr = sS[" << 128 * l << "], Si = sS[" << 128 * l + 64 << "];\n";
+                    else
+                        o << "      double Sr, Si, fr, fi;\n      blk_cleaf(" << (bose ? "true" : "false")
+                          << ", beta * xr, beta * xi, fr, fi, Sr, Si);\n";
+                    o << "      const double br = " << sr.str() << ", bi = " << si.str()
+                      << ";\n      const double Vr = fma(br, Sr, -bi * Si), Vi = fma(br, Si, bi * Sr);\n"
+                         "      gbeta = fma(Vr, xr, fma(Vi, xi, gbeta));\n      const double vr = Vr * beta, vi = Vi * beta;\n";
+                    scatter2(&tb.leaf_coef[static_cast<size_t>(l) * ne], "vr", "vi", 1.0, 1.0);
+                    o << "    }\n";
+                }
+            });
+        }
+        o << "template <int WV> __device__ __forceinline__ void blk_rounds(const double (&FBr)[L], const double (&FBi)[L], "
+             "double beta, double e_reg, ami::clds sE, ami::lds sR, ami::clds sS, double (&gEr)[NE], double (&gEi)[NE], "
+             "double &gbeta) {\n";
+        for (size_t r = 0; r + 1 < bp.round.size(); ++r)
+            o << "  __syncthreads();\n  blk_put" << r << "<WV>(FBr, FBi, sR);\n  __syncthreads();\n  blk_take" << r
+              << "<WV>(beta, e_reg, sE, sR, sS, gEr, gEi, gbeta);\n";
         o << "}\n";
     }
 

@@ -369,7 +369,8 @@ AmiStatus choose_path(AmiTerms *t, bool hub, bool adjoint, Path &p, void **jit_f
     if (v == AMI_VARIANT_TWO_PASS && !two && !passes)
         return fail(AMI_E_UNSUPPORTED, adjoint ? "the two-pass variant of the adjoint runs in passes only"
                                                : "the two-pass variant takes at most 65535 frequency rows");
-    if (passes && v == AMI_VARIANT_AUTO && jit_block_waves_of(t, hub) > 0) {
+    if (adjoint && jit_fn3 && v == AMI_VARIANT_AUTO && jit_prefers_block_adjoint(t) &&
+        jit_block_waves_of(t, hub) > 0) {
         const AmiStatus st = get(kJitBlockAdjoint, jit_fn);
         if (st == AMI_OK) {
             p = Path::ADJ_BLOCK;
@@ -641,13 +642,20 @@ struct AdjOut {
 };
 
 // Whether the adjoint of n_e samples with ncols columns of per-wave partial sums
-// fits the allocation-free scratch beside one chunk of samples of the passes
-// (in *chunk, if given, the samples of the chunk that is left).
+// fits the allocation-free scratch: alone up to the one-pass kernel's automatic
+// size, above it beside one chunk of samples of the passes (in *chunk, if given,
+// the samples of the chunk that is left), whichever kernel then runs.
 AmiStatus adjoint_scratch_fits(const AmiTerms *t, bool hub, int64_t n_e, int ncols, int64_t *chunk = nullptr) {
     const int B = jit_block(t, hub);
     const int64_t rows = (n_e + B - 1) / B * (B / 64);
-    const int64_t cols = 2 * static_cast<int64_t>(t->tab.G) + 2 * t->n_eps;
     const int64_t left = static_cast<int64_t>(kScratchBytes / sizeof(double)) - rows * ncols;
+    if (!chunk && t->tab.T <= kJitAutoAdjointTerms) {
+        if (left >= 0) return AMI_OK;
+        return fail(AMI_E_ARG, "the partial sums need " + std::to_string(rows * ncols * sizeof(double)) +
+                                   " bytes, more than the " + std::to_string(kScratchBytes) +
+                                   "-byte scratch of the allocation-free entry point: split the samples");
+    }
+    const int64_t cols = 2 * static_cast<int64_t>(t->tab.G) + 2 * t->n_eps;
     const int64_t ld = left > 0 ? left / cols / B * B : 0;
     if (chunk) *chunk = ld;
     if (ld >= B) return AMI_OK;
@@ -722,7 +730,7 @@ AmiStatus launch_adjoint_passes(AmiTerms *t, DeviceTables *dt, bool hub, KArgs &
 // the partial sums in the allocation-free scratch, under the size limit of the
 // passes (the entry point's documented one).
 AmiStatus launch_adjoint_block(AmiTerms *t, DeviceTables *dt, bool hub, KArgs &a, const AdjOut &o, void *fn,
-                               hipStream_t stream, double *fixed_ws) {
+                               hipStream_t stream, double *fixed_ws, bool cplx = false) {
     const int64_t rows = (a.n_e + 63) / 64;
     if (rows > 0x7fffffffLL) return fail(AMI_E_ARG, "n_e too large");
     const int ncols = kAdjScalars + 2 * a.n_f * t->n_ext;
@@ -738,9 +746,11 @@ AmiStatus launch_adjoint_block(AmiTerms *t, DeviceTables *dt, bool hub, KArgs &a
     a.gpartial = ws;
     a.partial = o.out_sum ? ws + static_cast<size_t>(rows) * ncols : nullptr;
     a.nrows = rows;
-    hipError_t e = launch_jit(fn, rows, 64 * jit_block_waves_of(t, hub), stream, a);
+    hipError_t e = launch_jit(fn, rows, 64 * jit_block_waves_of(t, hub, cplx), stream, a);
     if (e == hipSuccess) e = hipGetLastError();
-    g_last_variant = "specialized passes";
+    // named by the size, as the kernels it stands for (one pass or passes)
+    if (cplx) g_last_variant = t->tab.T > kJitAutoComplexAdjointTerms ? "specialized complex passes" : "specialized complex";
+    else g_last_variant = t->tab.T > kJitAutoAdjointTerms ? "specialized passes" : "specialized";
     if (e != hipSuccess) return hip_fail(e, "block adjoint launch");
     hipLaunchKernelGGL(ami_adj_finalize_kernel, dim3(ncols + nval), dim3(kRedThreads), 0, stream, a.gpartial, rows,
                        ncols, 1, o.grad_beta, o.grad_mu, o.grad_t, o.grad_freqs, 2 * a.n_f, o.out_sum);
@@ -1032,6 +1042,29 @@ AmiStatus amiEvaluateComplexAdjoint(AmiTerms *t, const double *energies, int64_t
     DeviceTables *dt = nullptr;
     st = upload(t, &dt);
     if (st != AMI_OK) return st;
+    KArgs ba;
+    std::memset(&ba, 0, sizeof(ba));
+    ba.energies = energies;
+    ba.stride_s = stride_s;
+    ba.stride_i = stride_i;
+    set_common(ba, ext_freqs, n_f, beta, e_reg, n_e);
+    ba.g_out = grad_out;
+    ba.g_sum = grad_sum;
+    ba.grad_e = grad_energies;
+    ba.out = out;
+    AdjOut bo;
+    bo.grad_beta = grad_beta;
+    bo.grad_freqs = grad_freqs;
+    bo.out_sum = out_sum;
+    // AUTO: the block adjoint where the solution splits over the waves of a block
+    if (t->variant == AMI_VARIANT_AUTO && n_e > 0 &&
+        t->tab.T > (n_f == 1 ? kJitAutoComplexBlockTermsOneRow : kJitAutoComplexBlockTerms) &&
+        jit_block_waves_of(t, false, true) > 0) {
+        void *fb = nullptr;
+        st = jit_get(t, false, kJitComplexBlockAdjoint, &fb);
+        if (st == AMI_OK) return launch_adjoint_block(t, dt, false, ba, bo, fb, stream, nullptr, true);
+        clear_error();
+    }
     // above the one-pass complex adjoint's automatic size (unless the handle
     // forces the specialized variant), or under the forced two-pass variant:
     // the adjoint in passes at complex energies
@@ -1048,21 +1081,7 @@ AmiStatus amiEvaluateComplexAdjoint(AmiTerms *t, const double *energies, int64_t
             if (st == AMI_OK) st = fill(grad_freqs, 2 * n_f * t->n_ext, stream);
             return st;
         }
-        KArgs a;
-        std::memset(&a, 0, sizeof(a));
-        a.energies = energies;
-        a.stride_s = stride_s;
-        a.stride_i = stride_i;
-        set_common(a, ext_freqs, n_f, beta, e_reg, n_e);
-        a.g_out = grad_out;
-        a.g_sum = grad_sum;
-        a.grad_e = grad_energies;
-        a.out = out;
-        AdjOut o;
-        o.grad_beta = grad_beta;
-        o.grad_freqs = grad_freqs;
-        o.out_sum = out_sum;
-        return launch_adjoint_passes(t, dt, false, a, o, fs, ff, fl, stream, nullptr, true);
+        return launch_adjoint_passes(t, dt, false, ba, bo, fs, ff, fl, stream, nullptr, true);
     }
     void *fn = nullptr;
     st = jit_get(t, false, kJitComplexAdj, &fn);
@@ -1317,8 +1336,8 @@ AmiStatus amiTermsSpecialize(AmiTerms *t, int32_t momentum) {
         if (!jit_prefers_two_pass(t)) kinds.push_back(kJitSumsPass);
         kinds.push_back(kJitAdjFreq);
         kinds.push_back(kJitAdjLeaf);
-        if (jit_block_waves_of(t, hub) > 0) kinds.push_back(kJitBlockAdjoint);
     }
+    if (jit_prefers_block_adjoint(t) && jit_block_waves_of(t, hub) > 0) kinds.push_back(kJitBlockAdjoint);
     // the complex-energy kernels AUTO uses: forward in one pass up to 1024
     // terms, in two above; the adjoint in one pass up to 512 terms, in passes
     // above
@@ -1329,7 +1348,11 @@ AmiStatus amiTermsSpecialize(AmiTerms *t, int32_t momentum) {
             kinds.push_back(kJitComplexSums);
             kinds.push_back(kJitComplexFreq);
         }
-        if (t->tab.T <= kJitAutoComplexAdjointTerms) {
+        const bool block = jit_block_waves_of(t, false, true) > 0;
+        if (block && t->tab.T > kJitAutoComplexBlockTermsOneRow) kinds.push_back(kJitComplexBlockAdjoint);
+        if (block && t->tab.T > kJitAutoComplexBlockTerms) {
+            // for any number of rows
+        } else if (t->tab.T <= kJitAutoComplexAdjointTerms) {
             kinds.push_back(kJitComplexAdj);
         } else {
             if (small) kinds.push_back(kJitComplexSums);

@@ -162,12 +162,13 @@ AmiStatus code_object(AmiTerms *t, bool hub, int kind) {
     std::string why;
     const bool passes = kind == kJitSumsPass || kind == kJitFreqPass || kind == kJitAdjFreq || kind == kJitAdjLeaf ||
                         kind == kJitComplexSums || kind == kJitComplexFreq || kind == kJitComplexAdjFreq ||
-                        kind == kJitComplexAdjLeaf || kind == kJitBlockAdjoint;
+                        kind == kJitComplexAdjLeaf || kind == kJitBlockAdjoint || kind == kJitComplexBlockAdjoint;
     if (!jit_supported(t, hub, &why, passes)) {
         err = "no specialized kernel: " + why;
         return fail(AMI_E_UNSUPPORTED, err);
     }
-    if (kind == kJitBlockAdjoint && jit_block_waves(t, hub, false) == 0) {
+    if ((kind == kJitBlockAdjoint || kind == kJitComplexBlockAdjoint) &&
+        jit_block_waves(t, hub, kind == kJitComplexBlockAdjoint) == 0) {
         err = "no block adjoint: the solution does not split over the waves of a block";
         return fail(AMI_E_UNSUPPORTED, err);
     }
@@ -244,10 +245,10 @@ AmiStatus code_from_source(const std::string &src, std::vector<char> &code, std:
     return AMI_OK;
 }
 
-int jit_block_waves_of(AmiTerms *t, bool hub) {
+int jit_block_waves_of(AmiTerms *t, bool hub, bool cplx) {
     std::lock_guard<std::mutex> lock(t->jit_mu);
-    int &w = t->block_waves[hub ? 1 : 0];
-    if (w < 0) w = jit_block_waves(t, hub, false);
+    int &w = t->block_waves[cplx ? 2 : hub ? 1 : 0];
+    if (w < 0) w = jit_block_waves(t, hub, cplx);
     return w;
 }
 
@@ -283,7 +284,8 @@ AmiStatus jit_get(AmiTerms *t, bool hub, int kind, void **fn) {
     static const char *const kNames[kJitKinds] = {"ami_jit_fwd",  "ami_jit_adj",   "ami_jit_mc",   "ami_jit_cfwd",
                                                   "ami_jit_sums", "ami_jit_freq",  "ami_jit_adjf", "ami_jit_adjl",
                                                   "ami_jit_cadj", "ami_jit_csums", "ami_jit_cfreq", "ami_jit_cadjf",
-                                                  "ami_jit_cadjl", "ami_jit_badj"};
+                                                  "ami_jit_cadjl", "ami_jit_badj",
+                                                  "ami_jit_bcadj"};
     e = hipModuleGetFunction(&f, mod, kNames[kind]);
     if (e != hipSuccess) {
         (void)hipModuleUnload(mod);

@@ -24,6 +24,22 @@ constexpr int kJitAutoAdjointTerms = 128;
 // complex values per leaf and node (per 10^6-sample step: 264 terms one pass
 // 0.91 ms, passes 1.75 ms; 380: 1.30 / 3.18 ms; 560: 2.21 / 1.91 ms).
 constexpr int kJitAutoComplexAdjointTerms = 512;
+// AUTO takes the block adjoint at complex energies above this many terms (2 10^5
+// samples, one row: 264 terms one pass 201 us, block 105; 560: passes 302, block
+// 134; four rows of 5 10^4: 88 and 52, 169 and 70), and with one frequency row
+// from fewer on (136 terms 84 and 66 us, 76: 76 and 63, 52: 56 and 48, 40: 48 and
+// 47; but 30 and 35, 29 and 33, 21 and 26 at four rows of 5 10^4 samples, where
+// each wave forms its denominators again for every row).
+constexpr int kJitAutoComplexBlockTerms = 200;
+constexpr int kJitAutoComplexBlockTermsOneRow = 50;
+
+// Whether AUTO's adjoint of a solution up to kJitAutoAdjointTerms terms takes the
+// block kernel: the one-pass kernel keeps a leaf and four values per group and
+// denominator, and two per energy, live at once; beyond 100 of the 128 doubles
+// that two waves per SIMD have, it spills (76 terms in 16 groups, 123 values,
+// 2 10^5 samples: 62 us a step, the block kernel 39; 40 terms in 8 groups, 81
+// values: 28 and 30; 52 terms in 4 groups, 68 values: 25 and 33).
+bool jit_prefers_block_adjoint(const AmiTerms *t);
 
 // Whether the adjoint of a solution above kJitAutoAdjointTerms can run in
 // passes (the two-pass form, no Taylor-coefficient leaves).
@@ -34,7 +50,7 @@ bool jit_adjoint_passes_supported(const AmiTerms *t, bool hub, std::string *why)
 // columns than the LDS of a CU holds).  jit_block_waves computes it;
 // jit_block_waves_of keeps it with the handle.
 int jit_block_waves(const AmiTerms *t, bool hub, bool cplx);
-int jit_block_waves_of(AmiTerms *t, bool hub);
+int jit_block_waves_of(AmiTerms *t, bool hub, bool cplx = false);
 
 // Whether the diagram can be specialized for the energy (hub = false) or
 // momentum (hub = true) input; *why says why not.
@@ -62,7 +78,7 @@ int jit_block(const AmiTerms *t, bool hub);
 // passes of the adjoint at complex energies that follow the first of those
 // (kernels & 2048: per frequency, the complex group-sum and denominator
 // cotangents; kernels & 4096: the complex leaf cotangents and the gradients),
-// and the block adjoint (kernels & 8192).
+// and the block adjoint (kernels & 8192; at complex energies, alone, 16384).
 // nested_part: terms per part of the one-pass adjoint's leaf cotangents as a
 // reverse sweep of the nested group sums (0: per-term prefix/suffix products;
 // -1: the AMIGPU_JIT_NESTED_COTANGENTS override, else per-term products).
@@ -109,7 +125,8 @@ int64_t code_meta(const std::vector<char> &code, const char *key);
 // energies (solutions above kJitMaxTerms terms); kJitComplexAdjFreq and
 // kJitComplexAdjLeaf the frequency and leaf passes of the adjoint at complex
 // energies (after kJitComplexSums); kJitBlockAdjoint the adjoint of large
-// solutions whose work the waves of a block split (no workspace).
+// solutions whose work the waves of a block split (no workspace),
+// kJitComplexBlockAdjoint the same at complex energies.
 enum JitKind {
     kJitForward = 0,
     kJitAdjoint = 1,
@@ -124,14 +141,15 @@ enum JitKind {
     kJitComplexFreq = 10,
     kJitComplexAdjFreq = 11,
     kJitComplexAdjLeaf = 12,
-    kJitBlockAdjoint = 13
+    kJitBlockAdjoint = 13,
+    kJitComplexBlockAdjoint = 14
 };
-constexpr int kJitKinds = 14;
+constexpr int kJitKinds = 15;
 
 // Kinds for the energy input only (complex energies).
 inline bool jit_kind_complex(int kind) {
     return kind == kJitComplex || kind == kJitComplexAdj || kind == kJitComplexSums || kind == kJitComplexFreq ||
-           kind == kJitComplexAdjFreq || kind == kJitComplexAdjLeaf;
+           kind == kJitComplexAdjFreq || kind == kJitComplexAdjLeaf || kind == kJitComplexBlockAdjoint;
 }
 
 // The specialized kernel of `kind` for the energy (hub = false) or momentum

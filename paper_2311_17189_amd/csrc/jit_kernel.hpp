@@ -182,3 +182,11 @@ extern "C" __global__ __launch_bounds__(64 * amijit::NW) __attribute__((amdgpu_w
     else amijit::badj_tile<AMI_JIT_HUB, false>(a, blockIdx.x, sm);
 }
 #endif
+
+#if AMI_JIT_KERNELS & 16384
+extern "C" __global__ __launch_bounds__(64 * amijit::NW) __attribute__((amdgpu_waves_per_eu(2))) void ami_jit_bcadj(ami::KArgs a) {
+    __shared__ double sm[64 * amijit::kBlockCols];
+    if (a.n_f == 1) amijit::bcadj_tile<true>(a, blockIdx.x, sm);
+    else amijit::bcadj_tile<false>(a, blockIdx.x, sm);
+}
+#endif

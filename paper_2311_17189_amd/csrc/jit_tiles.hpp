@@ -1214,6 +1214,25 @@ __device__ __forceinline__ void cadj_tile(const KArgs &a, int64_t blk, double *p
 }
 #endif
 
+#if AMI_JIT_KERNELS & (8192 | 16384)
+// sum over the waves of the columns first, first + 1, ... (in wave order)
+__device__ __forceinline__ double blk_wave_total(ami::clds col, int first) {
+    double v = col[64 * first];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v += col[64 * (first + w)];
+    return v;
+}
+
+// rows of W doubles staged at a stride of W + 1, the first n of them to dst
+template <int W>
+__device__ __forceinline__ void blk_store_rows(const double *stage, double *dst, int64_t n) {
+    for (int e = threadIdx.x; e < 64 * W; e += 64 * NW) {
+        const int r = e / W;
+        if (r < n) dst[e] = stage[e + r];
+    }
+}
+#endif
+
 #if AMI_JIT_KERNELS & 8192
 // Block adjoint of large solutions: NW waves share 64 samples (lane i of every
 // wave is sample i), each wave with its own part of the solution, and what the
@@ -1282,14 +1301,6 @@ __device__ __forceinline__ void blk_leaves(const KArgs &a, ami::lds col) {
     }
 }
 
-// sum over the waves of the columns first, first + 1, ... (in wave order)
-__device__ __forceinline__ double blk_wave_total(ami::clds col, int first) {
-    double v = col[64 * first];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) v += col[64 * (first + w)];
-    return v;
-}
-
 // Columns of the last steps, from kBU: NW per energy (and beta) of the energies'
 // cotangents, then dL/dK_x and dL/dK_y per line and NW each for dL/dmu, dL/dt.
 constexpr int kBG = kBU + (NE + 1) * NW, kBM = kBG + 2 * NE;
@@ -1334,15 +1345,6 @@ __device__ __forceinline__ void blk_momentum_grads(int lane, ami::clds col, doub
     line_scatter(gx, gy, gkx, gky);
 #pragma unroll
     for (int c = WV; c < 2 * NI; c += NW) stage[lane * (2 * NI + 1) + c] = (c & 1) ? gky[c / 2] : gkx[c / 2];
-}
-
-// rows of W doubles staged at a stride of W + 1, the first n of them to dst
-template <int W>
-__device__ __forceinline__ void blk_store_rows(const double *stage, double *dst, int64_t n) {
-    for (int e = threadIdx.x; e < 64 * W; e += 64 * NW) {
-        const int r = e / W;
-        if (r < n) dst[e] = stage[e + r];
-    }
 }
 
 // Wave WV of the block.  The waves run copies of this function of their own
@@ -1452,9 +1454,10 @@ __device__ __forceinline__ void badj_wave(const KArgs &a, int64_t tile, double *
 
     double gmu = 0.0, gt = 0.0;
     const int64_t n_rows = a.n_e - s0 < 64 ? a.n_e - s0 : 64;
-    // the staged gradient rows: over the first columns, which nothing reads any
-    // more once the momenta's are formed, or in the momentum input's own columns
-    double *const stage = sm + 64 * (HUB ? kBE : kBG);
+    // the staged gradient rows lie over the first columns (energies, a row's
+    // sums), which nothing reads any more: one column more than a row's length
+    static_assert(kBE == 0 && (HUB ? 2 * NI : NE) + 1 <= kBlockCols && (HUB || NE + 1 <= kBU), "staging area");
+    double *const stage = sm;
     if constexpr (HUB) {
         blk_energy_grads<HUB, WV>(a, sc, lane, col, nullptr, gmu, gt);
         col[64 * (kBM + wv)] = gmu;
@@ -1489,6 +1492,169 @@ __device__ __forceinline__ void badj_tile(const KArgs &a, int64_t tile, double *
     case 5: if constexpr (NW > 4) badj_wave<HUB, 5, ONE>(a, tile, sm); break;
     case 6: if constexpr (NW > 4) badj_wave<HUB, 6, ONE>(a, tile, sm); break;
     case 7: if constexpr (NW > 4) badj_wave<HUB, 7, ONE>(a, tile, sm); break;
+    }
+}
+#endif
+
+#if AMI_JIT_KERNELS & 16384
+// Block adjoint at complex energies: badj_wave's steps with complex energies,
+// leaves, group sums and cotangents (energy input).  Columns from kBU at the
+// end: NW per real and imaginary part of an energy's cotangent and for beta.
+// Gradient step at 2 10^5 samples, one row: 560 terms 302 us in passes, 134 here
+// (71 and 26 at 2 10^4 samples); 264 terms 201 us in one pass, 105 here.
+template <int WV, bool ONE>
+__device__ __forceinline__ void bcadj_wave(const KArgs &a, int64_t tile, double *sm) {
+    const int lane = threadIdx.x & 63;
+    const int64_t s0 = tile * 64, s = s0 + lane;
+    const bool active = s < a.n_e;
+    const int64_t sc = active ? s : a.n_e - 1;
+    const ami::lds col = (ami::lds)sm + lane;
+
+    {
+        const double *row = a.energies + 2 * sc * a.stride_s;
+#pragma unroll
+        for (int i = WV; i < NE; i += NW) {
+            col[64 * (kBE + i)] = row[2 * i * a.stride_i];
+            col[64 * (kBE + NE + i)] = row[2 * i * a.stride_i + 1];
+        }
+    }
+    __syncthreads();
+    {
+        double Er[NE], Ei[NE], xr[L], xi[L];
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {
+            Er[i] = col[64 * (kBE + i)];
+            Ei[i] = col[64 * (kBE + NE + i)];
+        }
+        leaf_args(Er, xr);
+        leaf_args(Ei, xi);
+#pragma unroll
+        for (int l = WV; l < L; l += NW) {
+            double fr, fi, Sr, Si;
+            blk_cleaf(kBose[l], a.beta * (kBose[l] ? xr[l] + a.e_reg : xr[l]), a.beta * xi[l], fr, fi, Sr, Si);
+            col[64 * (kBF + 2 * l)] = fr;
+            col[64 * (kBF + 2 * l + 1)] = fi;
+            if constexpr (kBS >= 0) {
+                col[64 * (kBS + 2 * l)] = Sr;
+                col[64 * (kBS + 2 * l + 1)] = Si;
+            }
+        }
+    }
+    __syncthreads();
+    double ftr[GW], fti[GW], ftbr[GW], ftbi[GW], gEr[NE], gEi[NE];
+#pragma unroll
+    for (int g = 0; g < GW; ++g) ftr[g] = fti[g] = ftbr[g] = ftbi[g] = 0.0;
+#pragma unroll
+    for (int i = 0; i < NE; ++i) gEr[i] = gEi[i] = 0.0;
+    blk_sums<WV>(col + 64 * kBF, col + 64 * kBT, ftr, fti);
+
+    double *gp = a.gpartial + tile;                  // column c at gp[c * nrows]
+    // a row's values and sums from the waves' parts
+    auto finish_row = [&](int f) __attribute__((always_inline)) {
+        const double re = blk_wave_total(col, kBA), im = blk_wave_total(col, kBA + NW);
+        if (active && a.out) {
+            double2 v;
+            v.x = re;
+            v.y = im;
+            reinterpret_cast<double2 *>(a.out)[static_cast<int64_t>(f) * a.n_e + s] = v;
+        }
+        constexpr int NV = 2 * NX + 2, NV4 = (NV + 3) / 4 * 4;
+        double vv[NV4];
+        double *pp[NV4];
+#pragma unroll
+        for (int x = 0; x < NX; ++x) {
+            const double r = blk_wave_total(col, kBA + (2 + 2 * x) * NW);
+            const double i = blk_wave_total(col, kBA + (3 + 2 * x) * NW);
+            vv[2 * x] = active ? r : 0.0;
+            vv[2 * x + 1] = active ? -i : 0.0;
+            pp[2 * x] = gp + (ami::kAdjScalars + 2 * (f * NX + x)) * a.nrows;
+            pp[2 * x + 1] = pp[2 * x] + a.nrows;
+        }
+        vv[2 * NX] = active ? re : 0.0;
+        vv[2 * NX + 1] = active ? im : 0.0;
+        pp[2 * NX] = a.partial ? a.partial + 2 * f * a.nrows + tile : nullptr;
+        pp[2 * NX + 1] = a.partial ? pp[2 * NX] + a.nrows : nullptr;
+#pragma unroll
+        for (int c = NV; c < NV4; ++c) {
+            vv[c] = 0.0;
+            pp[c] = nullptr;
+        }
+#pragma unroll
+        for (int c = 0; c < NV4; c += 4)
+            ami::wave_store4(vv[c], vv[c + 1], vv[c + 2], vv[c + 3], lane, pp[c], pp[c + 1], pp[c + 2], pp[c + 3]);
+    };
+    const int nf = ONE ? 1 : a.n_f;
+    for (int f = 0; f < nf; ++f) {
+        double cr = 0.0, ci = 0.0;
+        if (active) {
+            if (a.g_out) {
+                cr = a.g_out[2 * (static_cast<int64_t>(f) * a.n_e + s)];
+                ci = a.g_out[2 * (static_cast<int64_t>(f) * a.n_e + s) + 1];
+            }
+            if (a.g_sum) {
+                cr += a.g_sum[2 * f];
+                ci += a.g_sum[2 * f + 1];
+            }
+        }
+        double wr[NXA], wi[NXA], gwr[NXA], gwi[NXA], acc_re = 0.0, acc_im = 0.0;
+        load_freq(a, f, wr, wi);
+#pragma unroll
+        for (int x = 0; x < NXA; ++x) gwr[x] = gwi[x] = 0.0;
+        blk_freq<WV, ONE>(col + 64 * kBE, wr, wi, col + 64 * kBT, ftr, fti, cr, ci, ftbr, ftbi, acc_re, acc_im, gEr, gEi,
+                          gwr, gwi);
+        if (f > 0) __syncthreads();                  // the last row's sums have been read
+        col[64 * (kBA + WV)] = acc_re;
+        col[64 * (kBA + NW + WV)] = acc_im;
+#pragma unroll
+        for (int x = 0; x < NX; ++x) {
+            col[64 * (kBA + (2 + 2 * x) * NW + WV)] = gwr[x];
+            col[64 * (kBA + (3 + 2 * x) * NW + WV)] = gwi[x];
+        }
+        if constexpr (!ONE) {
+            __syncthreads();
+            if (WV == f % NW) finish_row(f);
+        }
+    }
+
+    double FBr[L], FBi[L], gbeta = 0.0;
+#pragma unroll
+    for (int l = 0; l < L; ++l) FBr[l] = FBi[l] = 0.0;
+    if constexpr (!ONE) blk_keep<WV>(col + 64 * kBT, ftbr, ftbi);
+    blk_leaf<WV>(col + 64 * kBF, col + 64 * kBT, ftbr, ftbi, FBr, FBi);
+    blk_rounds<WV>(FBr, FBi, a.beta, a.e_reg, col + 64 * kBE, col + 64 * kBU, col + 64 * kBS, gEr, gEi, gbeta);
+    if constexpr (ONE && WV == 0) finish_row(0);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NE; ++i) {
+        col[64 * (kBU + 2 * i * NW + WV)] = gEr[i];
+        col[64 * (kBU + (2 * i + 1) * NW + WV)] = gEi[i];
+    }
+    col[64 * (kBU + 2 * NE * NW + WV)] = gbeta;
+    __syncthreads();
+    static_assert(kBE == 0 && 2 * NE + 1 <= kBU, "staging area");
+    double *const stage = sm;
+#pragma unroll
+    for (int i = WV; i < 2 * NE; i += NW) stage[lane * (2 * NE + 1) + i] = blk_wave_total(col, kBU + i * NW);
+    if constexpr (WV == NW - 1) {
+        const double b = blk_wave_total(col, kBU + 2 * NE * NW);
+        ami::wave_store4(active ? b : 0.0, 0.0, 0.0, 0.0, lane, gp, gp + a.nrows, gp + 2 * a.nrows, nullptr);
+    }
+    __syncthreads();
+    const int64_t n_rows = a.n_e - s0 < 64 ? a.n_e - s0 : 64;
+    if (a.grad_e) blk_store_rows<2 * NE>(stage, a.grad_e + 2 * s0 * NE, n_rows);
+}
+
+template <bool ONE>
+__device__ __forceinline__ void bcadj_tile(const KArgs &a, int64_t tile, double *sm) {
+    switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
+    case 0: bcadj_wave<0, ONE>(a, tile, sm); break;
+    case 1: bcadj_wave<1, ONE>(a, tile, sm); break;
+    case 2: if constexpr (NW > 2) bcadj_wave<2, ONE>(a, tile, sm); break;
+    case 3: if constexpr (NW > 2) bcadj_wave<3, ONE>(a, tile, sm); break;
+    case 4: if constexpr (NW > 4) bcadj_wave<4, ONE>(a, tile, sm); break;
+    case 5: if constexpr (NW > 4) bcadj_wave<5, ONE>(a, tile, sm); break;
+    case 6: if constexpr (NW > 4) bcadj_wave<6, ONE>(a, tile, sm); break;
+    case 7: if constexpr (NW > 4) bcadj_wave<7, ONE>(a, tile, sm); break;
     }
 }
 #endif
