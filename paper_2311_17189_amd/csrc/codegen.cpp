@@ -2376,7 +2376,8 @@ std::string jit_batch_source(const std::vector<const AmiTerms *> &items, const s
                 o << "    case " << label << ":\n      for (int64_t t = tile0; t < tile0 + ntiles; ++t) {\n"
                   << "        asm volatile(\"\" ::: \"memory\");   // each tile loads its own inputs\n        ";
                 if (two_pass[j]) o << ns << "::sums_tile<" << h << ">(a, t);\n";
-                else o << ns << "::fwd_tile<" << h << ", " << (one_row[j] ? "true" : "false") << ">(a, t);\n";
+                else o << ns << "::fwd_tile<" << h << ", " << (one_row[j] ? "true" : "false")
+                       << ">(a, t, 0, a.n_f);\n";
                 o << "      }\n      break;\n";
             } else if (two_pass[j]) {
                 o << "    case " << label << ":\n      for (int64_t t = tile0; t < tile0 + ntiles; ++t)\n"

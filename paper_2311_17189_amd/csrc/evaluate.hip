@@ -478,6 +478,24 @@ hipError_t launch_jit(void *fn, int64_t nblocks, int block, hipStream_t stream, 
                                  static_cast<unsigned>(block), 1, 1, 0, stream, params, nullptr);
 }
 
+// Parts of the frequency rows of a one-pass forward, each a grid of its own over
+// the samples that forms the leaves and group sums again.  A SIMD with one wave
+// issues FP64 at half rate, so as many parts as keep to two waves per SIMD (2048
+// waves) cost no time; more, up to eight per SIMD, pay while a part holds enough
+// rows to make the repeated leaves an eighth of it (instructions estimated from
+// the sizes).  Order 4, 52 terms, 256 rows of 10^5 samples: one part 141 us, six
+// 103 us.
+int forward_row_parts(const AmiTerms *t, bool hub, int64_t n_waves, int64_t n_f) {
+    if (n_f < 4) return 1;
+    const Tables &tb = t->tab;
+    const double once = 30.0 * tb.L + tb.T + (hub ? 34.0 * t->n_g : 0.0);
+    const double per_row = 18.0 * tb.D + 10.0 * tb.G + 20.0;
+    const int64_t free_parts = 2048 / std::max<int64_t>(n_waves, 1);
+    const int64_t full_parts = std::min<int64_t>((8192 + n_waves - 1) / std::max<int64_t>(n_waves, 1),
+                                                 static_cast<int64_t>(n_f * per_row / (8.0 * once)));
+    return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>({std::max(free_parts, full_parts), n_f / 2, 1024})));
+}
+
 // The two-pass forward: the samples in chunks whose group sums and energies
 // fit the chunk workspace; per chunk the sums pass (one lane per sample) and
 // the frequency pass (a block per tile and frequency row), then one column reduction
@@ -485,7 +503,7 @@ hipError_t launch_jit(void *fn, int64_t nblocks, int block, hipStream_t stream, 
 // cplx: the complex-energy passes, whose group sums and energies take two
 // columns each.
 AmiStatus launch_two_pass(AmiTerms *t, DeviceTables *dt, bool hub, KArgs &a, double *out_sum, void *fn_sums,
-                          void *fn_freq, hipStream_t stream, bool cplx = false) {
+                          void *fn_freq, hipStream_t stream, bool cplx = false, RowSums *sums = nullptr) {
     const int B = jit_block(t, hub);
     const int64_t tiles = (a.n_e + B - 1) / B;
     if (tiles > 0x7fffffffLL) return fail(AMI_E_ARG, "n_e too large");
@@ -519,7 +537,8 @@ AmiStatus launch_two_pass(AmiTerms *t, DeviceTables *dt, bool hub, KArgs &a, dou
     if (e == hipSuccess) e = hipGetLastError();
     g_last_variant = cplx ? "specialized complex two-pass" : "specialized two-pass";
     if (e != hipSuccess) return hip_fail(e, "two-pass launch");
-    if (out_sum) {
+    if (sums) *sums = RowSums{a.partial, rows, ncols};
+    else if (out_sum) {
         hipLaunchKernelGGL(ami_colsum_kernel, dim3(ncols), dim3(kRedThreads), 0, stream, a.partial, rows,
                            static_cast<int64_t>(1), rows, out_sum);
         e = hipGetLastError();
@@ -528,7 +547,8 @@ AmiStatus launch_two_pass(AmiTerms *t, DeviceTables *dt, bool hub, KArgs &a, dou
     return AMI_OK;
 }
 
-AmiStatus launch_forward(AmiTerms *t, bool hub, KArgs &a, double *out_sum, hipStream_t stream, int variant = -1) {
+AmiStatus launch_forward(AmiTerms *t, bool hub, KArgs &a, double *out_sum, hipStream_t stream, int variant = -1,
+                         RowSums *sums = nullptr) {
     DeviceTables *dt = nullptr;
     AmiStatus st = upload(t, &dt);
     if (st != AMI_OK) return st;
@@ -539,7 +559,8 @@ AmiStatus launch_forward(AmiTerms *t, bool hub, KArgs &a, double *out_sum, hipSt
     std::string note;
     st = choose_path(t, hub, false, path, &jit_fn, note, &jit_fn2, a.n_f, variant);
     if (st != AMI_OK) return st;
-    if (path == Path::TWO_PASS) return launch_two_pass(t, dt, hub, a, out_sum, jit_fn, jit_fn2, stream);
+    if (path == Path::TWO_PASS)
+        return launch_two_pass(t, dt, hub, a, out_sum, jit_fn, jit_fn2, stream, false, sums);
     LaunchShape ls;
     if (path == Path::SPECIALIZED) {
         ls.block = jit_block(t, hub);
@@ -562,7 +583,7 @@ AmiStatus launch_forward(AmiTerms *t, bool hub, KArgs &a, double *out_sum, hipSt
     if (path == Path::SPECIALIZED) {
         a.partial = partial;
         a.nrows = rows;
-        e = launch_jit(jit_fn, nblocks, ls.block, stream, a);
+        e = launch_jit(jit_fn, nblocks, ls.block, stream, a, forward_row_parts(t, hub, rows, a.n_f));
         g_last_variant = "specialized";
         if (e == hipSuccess) e = hipGetLastError();
     } else if (path == Path::PACKED) {
@@ -580,7 +601,9 @@ AmiStatus launch_forward(AmiTerms *t, bool hub, KArgs &a, double *out_sum, hipSt
     }
     if (path != Path::SPECIALIZED) timer_mark(stream, true);
     if (e != hipSuccess) return hip_fail(e, "forward launch");
-    if (out_sum) {
+    if (sums && path == Path::SPECIALIZED) {
+        *sums = RowSums{partial, rows, 2 * a.n_f};
+    } else if (out_sum) {
         const bool cm = path == Path::SPECIALIZED;
         hipLaunchKernelGGL(ami_colsum_kernel, dim3(2 * a.n_f), dim3(kRedThreads), 0, stream, partial, rows,
                            static_cast<int64_t>(cm ? 1 : 2 * a.n_f), cm ? rows : static_cast<int64_t>(1), out_sum);
@@ -895,8 +918,9 @@ void set_common(KArgs &a, const double *ext_freqs, int64_t n_f, double beta, dou
 
 }  // namespace
 
-AmiStatus launch_forward_as(AmiTerms *t, bool hub, KArgs &a, double *out_sum, hipStream_t stream, int variant) {
-    return launch_forward(t, hub, a, out_sum, stream, variant);
+AmiStatus launch_forward_as(AmiTerms *t, bool hub, KArgs &a, double *out_sum, hipStream_t stream, int variant,
+                            RowSums *sums) {
+    return launch_forward(t, hub, a, out_sum, stream, variant, sums);
 }
 
 bool specialized_forward_ready(AmiTerms *t, bool hub, int n_f) {
@@ -1014,7 +1038,7 @@ AmiStatus amiEvaluateComplex(AmiTerms *t, const double *energies, int64_t n_e, i
         st = workspace(t, dt, stream, static_cast<size_t>(rows) * n_f * 2 * sizeof(double), &a.partial);
         if (st != AMI_OK) return st;
     }
-    hipError_t e = launch_jit(fn, nblocks, block, stream, a);
+    hipError_t e = launch_jit(fn, nblocks, block, stream, a, forward_row_parts(t, false, rows, n_f));
     if (e == hipSuccess) e = hipGetLastError();
     g_last_variant = "specialized complex";
     if (e != hipSuccess) return hip_fail(e, "complex-energy launch");

@@ -36,10 +36,22 @@
 // passes of the forward at complex energies (512, 1024), the frequency and
 // leaf passes of the adjoint at complex energies (2048, 4096), or a sum of
 // them
+// The one-pass forwards run blocks (tile, part of the rows): every part forms
+// the tile's leaves and group sums again, and takes an even number of rows.
+#define AMI_JIT_ROW_PART(f0, f1)                                                    \
+    const int per = ((a.n_f + static_cast<int>(gridDim.y) - 1) / static_cast<int>(gridDim.y) + 1) & ~1; \
+    const int f0 = static_cast<int>(blockIdx.y) * per;                                      \
+    if (f0 >= a.n_f) return;                                                                \
+    const int f1 = f0 + per < a.n_f ? f0 + per : a.n_f;
+
 #if AMI_JIT_KERNELS & 1
 extern "C" __global__ __launch_bounds__(AMI_JIT_BLOCK) void ami_jit_fwd(ami::KArgs a) {
-    if (a.n_f == 1) amijit::fwd_tile<AMI_JIT_HUB, true>(a, blockIdx.x);
-    else amijit::fwd_tile<AMI_JIT_HUB, false>(a, blockIdx.x);
+    if (a.n_f == 1) {
+        amijit::fwd_tile<AMI_JIT_HUB, true>(a, blockIdx.x, 0, 1);
+    } else {
+        AMI_JIT_ROW_PART(f0, f1)
+        amijit::fwd_tile<AMI_JIT_HUB, false>(a, blockIdx.x, f0, f1);
+    }
 }
 #endif
 
@@ -69,7 +81,8 @@ extern "C" __global__ __launch_bounds__(AMI_JIT_BLOCK) void ami_jit_mc(ami::KArg
 
 #if AMI_JIT_KERNELS & 8
 extern "C" __global__ __launch_bounds__(AMI_JIT_BLOCK) void ami_jit_cfwd(ami::KArgs a) {
-    amijit::cfwd_tile(a, blockIdx.x);
+    AMI_JIT_ROW_PART(f0, f1)
+    amijit::cfwd_tile(a, blockIdx.x, f0, f1);
 }
 #endif
 

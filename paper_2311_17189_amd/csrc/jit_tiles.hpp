@@ -201,14 +201,54 @@ __device__ __forceinline__ void reciprocals(const double (&E)[NE], const double 
     }
 }
 
+#if AMI_JIT_KERNELS & (1 | 8)
+// The rows [f0, f1) of one sample, two at a time: row(f, re, im) gives a row's
+// value, which goes to out; the wave sums of two rows leave in one wave_store4
+// (21 instructions for four sums; two wave_store2 take twice that, a sixth of a
+// row of an order-4 diagram).
+template <typename Row>
+__device__ __forceinline__ void forward_rows(const KArgs &a, int64_t s, bool active, int lane, int64_t row, int f0,
+                                             int f1, Row row_value) {
+    auto put = [&](int f, double re, double im) {
+        if (active && a.out) {
+            double2 v;
+            v.x = re;
+            v.y = im;
+            reinterpret_cast<double2 *>(a.out)[static_cast<int64_t>(f) * a.n_e + s] = v;
+        }
+    };
+    int f = f0;
+    for (; f + 1 < f1; f += 2) {
+        double re0, im0, re1, im1;
+        row_value(f, re0, im0);
+        put(f, re0, im0);
+        row_value(f + 1, re1, im1);
+        put(f + 1, re1, im1);
+        if (a.partial) {
+            double *p = a.partial + 2 * f * a.nrows + row;
+            ami::wave_store4(active ? re0 : 0.0, active ? im0 : 0.0, active ? re1 : 0.0, active ? im1 : 0.0, lane, p,
+                             p + a.nrows, p + 2 * a.nrows, p + 3 * a.nrows);
+        }
+    }
+    if (f < f1) {
+        double re, im;
+        row_value(f, re, im);
+        put(f, re, im);
+        if (a.partial)
+            ami::wave_store2(active ? re : 0.0, active ? im : 0.0, lane, a.partial + 2 * f * a.nrows + row, a.nrows);
+    }
+}
+#endif
+
 #if AMI_JIT_KERNELS & 1
 // Partial sums are per wave: row r = tile * (B / 64) + wave of the partial
 // arrays (column c at [c * nrows + r]), each total written by the one lane
 // of the wave that holds it (wave_store2, wave_store4).
 // NF1: one frequency row (n_f = 1 known at compile time, so the tile is
-// straight-line code the compiler schedules as a whole).
+// straight-line code the compiler schedules as a whole); else the rows
+// [f0, f1), f0 even.
 template <bool HUB, bool NF1>
-__device__ __forceinline__ void fwd_tile(const KArgs &a, int64_t tile) {
+__device__ __forceinline__ void fwd_tile(const KArgs &a, int64_t tile, int f0, int f1) {
     const int tid = threadIdx.x, B = blockDim.x, lane = tid & 63;
     const int64_t row = tile * (B >> 6) + (tid >> 6);
     const int64_t s = tile * B + tid;
@@ -228,23 +268,13 @@ __device__ __forceinline__ void fwd_tile(const KArgs &a, int64_t tile) {
     double FT[G];
     group_sums(F, FT);
 
-    const int nf = NF1 ? 1 : a.n_f;
-    for (int f = 0; f < nf; ++f) {
-        double wr[NXA], wi[NXA], xr[D], xi[D];
-        load_freq(a, f, wr, wi);
-        reciprocals(E, wr, wi, xr, xi);
-        double acc_re, acc_im;
-        groups_combine(xr, xi, FT, acc_re, acc_im);
-        if (active && a.out) {
-            double2 v;
-            v.x = acc_re;
-            v.y = acc_im;
-            reinterpret_cast<double2 *>(a.out)[static_cast<int64_t>(f) * a.n_e + s] = v;
-        }
-        if (a.partial)
-            ami::wave_store2(active ? acc_re : 0.0, active ? acc_im : 0.0, lane, a.partial + 2 * f * a.nrows + row,
-                             a.nrows);
-    }
+    forward_rows(a, s, active, lane, row, NF1 ? 0 : f0, NF1 ? 1 : f1,
+                 [&](int f, double &re, double &im) __attribute__((always_inline)) {
+                     double wr[NXA], wi[NXA], xr[D], xi[D];
+                     load_freq(a, f, wr, wi);
+                     reciprocals(E, wr, wi, xr, xi);
+                     groups_combine(xr, xi, FT, re, im);
+                 });
 }
 
 #endif
@@ -755,7 +785,7 @@ __device__ __forceinline__ void adjl_tile(const KArgs &a, int64_t tile, double *
 // the denominators are linear in E, so leaf_args and den_args serve the real
 // and the imaginary parts alike; the leaves are complex (leaf_complex) and so
 // are the group sums FT_g, each multiplied by R_g in complex arithmetic.
-__device__ __forceinline__ void cfwd_tile(const KArgs &a, int64_t tile) {
+__device__ __forceinline__ void cfwd_tile(const KArgs &a, int64_t tile, int f0, int f1) {
     const int tid = threadIdx.x, B = blockDim.x, lane = tid & 63;
     const int64_t row = tile * (B >> 6) + (tid >> 6);
     const int64_t s = tile * B + tid;
@@ -784,34 +814,26 @@ __device__ __forceinline__ void cfwd_tile(const KArgs &a, int64_t tile) {
         den_args(Ei, zr, zi, dEi, unused);          // e_k . Im E
     }
 
-    for (int f = 0; f < a.n_f; ++f) {
+    forward_rows(a, s, active, lane, row, f0, f1, [&](int f, double &re, double &im) __attribute__((always_inline)) {
         double wr[NXA], wi[NXA], dr[D], di[D], xr[D], xi[D], Rr[G], Ri[G];
         load_freq(a, f, wr, wi);
         den_args(Er, wr, wi, dr, di);
 #pragma unroll
         for (int k = 0; k < D; ++k) {
-            const double im = di[k] + dEi[k];
-            const double inv = ami::rcp_nr(fma(dr[k], dr[k], im * im));
+            const double im_k = di[k] + dEi[k];
+            const double inv = ami::rcp_nr(fma(dr[k], dr[k], im_k * im_k));
             xr[k] = dr[k] * inv;
-            xi[k] = -im * inv;
+            xi[k] = -im_k * inv;
         }
         group_products(xr, xi, Rr, Ri);
-        double acc_re = 0.0, acc_im = 0.0;
+        re = 0.0;
+        im = 0.0;
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            acc_re = fma(FTr[g], Rr[g], fma(-FTi[g], Ri[g], acc_re));
-            acc_im = fma(FTr[g], Ri[g], fma(FTi[g], Rr[g], acc_im));
+            re = fma(FTr[g], Rr[g], fma(-FTi[g], Ri[g], re));
+            im = fma(FTr[g], Ri[g], fma(FTi[g], Rr[g], im));
         }
-        if (active && a.out) {
-            double2 v;
-            v.x = acc_re;
-            v.y = acc_im;
-            reinterpret_cast<double2 *>(a.out)[static_cast<int64_t>(f) * a.n_e + s] = v;
-        }
-        if (a.partial)
-            ami::wave_store2(active ? acc_re : 0.0, active ? acc_im : 0.0, lane, a.partial + 2 * f * a.nrows + row,
-                             a.nrows);
-    }
+    });
 }
 #endif
 

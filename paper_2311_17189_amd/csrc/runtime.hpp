@@ -58,9 +58,19 @@ AmiStatus pick_shape(int slots, LaunchShape &ls);
 PackedTabs packed_tabs(const AmiTerms *t, const DeviceTables *dt);
 int fwd_slots(const Tables &tb);
 
+// The per-wave partial sums of a forward whose row sums the caller reduces:
+// column c (of ncols) holds `rows` values at partial + c * rows.
+struct RowSums {
+    const double *partial = nullptr;
+    int64_t rows = 0;
+    int ncols = 0;
+};
+
 // The forward of one handle as an evaluate call with the given variant
-// (AMI_VARIANT_*) would launch it on `stream`, row sums included.
-AmiStatus launch_forward_as(AmiTerms *t, bool hub, KArgs &a, double *out_sum, hipStream_t stream, int variant);
+// (AMI_VARIANT_*) would launch it on `stream`, row sums included; with `sums`
+// the specialized kernels' row sums are left to the caller.
+AmiStatus launch_forward_as(AmiTerms *t, bool hub, KArgs &a, double *out_sum, hipStream_t stream, int variant,
+                            RowSums *sums = nullptr);
 // Whether AUTO would run the specialized (one- or two-pass) forward of t for
 // n_f frequency rows; compiles and loads its kernels on the current device.
 bool specialized_forward_ready(AmiTerms *t, bool hub, int n_f);
