@@ -121,8 +121,8 @@ struct AmiTerms {
     // complex energies, 4 and 5 the two passes of the two-pass forward) -- and
     // the modules loaded from them, one per device
     std::mutex jit_mu;
-    std::vector<char> jit_code[30];           // [2 inputs][kJitKinds]
-    std::string jit_error[30];                // why a compilation failed (not retried)
+    std::vector<char> jit_code[32];           // [2 inputs][kJitKinds]
+    std::string jit_error[32];                // why a compilation failed (not retried)
     int block_waves[3] = {-1, -1, -1};        // waves per block of the block adjoints: energies, momenta, complex energies (-1: not computed)
     struct JitModule {
         int device = -1, kind = 0;

@@ -466,27 +466,12 @@ constexpr int kBlockMaxColumns = 316;
 // Groups whose sums and cotangents a wave holds in registers at most.
 constexpr int kBlockRegisterGroups = 12;
 
-BlockPlan block_plan(const AmiTerms *t, bool hub, bool cplx, int waves) {
-    const Tables &tb = t->tab;
-    const int G = tb.G, L = tb.L, ni = t->n_int, ne = t->n_eps, nx = t->n_ext;
-    const int cw = cplx ? 2 : 1;          // columns of a value
-    BlockPlan p;
-    if (waves < 2 || G < waves) return p;
-    std::vector<double> cost(static_cast<size_t>(G));
+// Consecutive ranges of groups for `waves` waves (first[w] .. first[w + 1]) with
+// the smallest largest cost.
+bool split_groups(const std::vector<double> &cost, int waves, std::vector<int> &out) {
+    const int G = static_cast<int>(cost.size());
     double total = 0.0;
-    for (int g = 0; g < G; ++g) {
-        std::vector<HornerTerm> ts;
-        for (int ti = tb.group_start[g]; ti < tb.group_start[g + 1]; ++ti) {
-            HornerTerm h{tb.term_sign[ti], {}};
-            for (int j = 0; j < ni; ++j) h.leaves.push_back(tb.term_leaf[static_cast<size_t>(ti) * ni + j]);
-            ts.push_back(std::move(h));
-        }
-        std::vector<HNode> nodes;
-        horner_build(std::move(ts), nodes);
-        const int dens = tb.group_den_start[g + 1] - tb.group_den_start[g];
-        cost[g] = 3.6 * (cplx ? 3.5 : 1.0) * static_cast<double>(nodes.size()) + 3.0 * dens + 8.0;
-        total += cost[g];
-    }
+    for (double c : cost) total += c;
     // the smallest bound under which consecutive ranges fit `waves` waves
     auto ranges = [&](double bound, std::vector<int> &first) {
         first.assign(1, 0);
@@ -511,7 +496,31 @@ BlockPlan block_plan(const AmiTerms *t, bool hub, bool cplx, int waves) {
         if (ranges(mid, first)) hi = mid;
         else lo = mid;
     }
-    if (!ranges(hi, p.first)) return p;
+    return ranges(hi, out);
+}
+
+BlockPlan block_plan(const AmiTerms *t, bool hub, bool cplx, int waves) {
+    const Tables &tb = t->tab;
+    const int G = tb.G, L = tb.L, ni = t->n_int, ne = t->n_eps, nx = t->n_ext;
+    const int cw = cplx ? 2 : 1;          // columns of a value
+    BlockPlan p;
+    if (waves < 2 || G < waves) return p;
+    std::vector<double> cost(static_cast<size_t>(G));
+    double total = 0.0;
+    for (int g = 0; g < G; ++g) {
+        std::vector<HornerTerm> ts;
+        for (int ti = tb.group_start[g]; ti < tb.group_start[g + 1]; ++ti) {
+            HornerTerm h{tb.term_sign[ti], {}};
+            for (int j = 0; j < ni; ++j) h.leaves.push_back(tb.term_leaf[static_cast<size_t>(ti) * ni + j]);
+            ts.push_back(std::move(h));
+        }
+        std::vector<HNode> nodes;
+        horner_build(std::move(ts), nodes);
+        const int dens = tb.group_den_start[g + 1] - tb.group_den_start[g];
+        cost[g] = 3.6 * (cplx ? 3.5 : 1.0) * static_cast<double>(nodes.size()) + 3.0 * dens + 8.0;
+        total += cost[g];
+    }
+    if (!split_groups(cost, waves, p.first)) return p;
     double most = 0.0;
     for (int w = 0; w < waves; ++w) {
         double c = 0.0;
@@ -576,6 +585,17 @@ BlockPlan block_plan(const AmiTerms *t, bool hub, bool cplx, int waves) {
 }
 
 }  // namespace
+
+// Waves per block of the block forward: four, two blocks per CU, where energies,
+// leaves and group sums fit half the LDS, else eight in all of it.
+int jit_block_forward_waves(const AmiTerms *t) {
+    for (int o : t->tab.leaf_order)
+        if (o > 0) return 0;              // Taylor-coefficient leaves: the two passes over a workspace
+    if (t->tab.T > kJitTwoPassMaxTerms) return 0;
+    const int columns = t->n_eps + t->tab.L + t->tab.G;
+    const int waves = columns <= kBlockHalfColumns ? 4 : columns <= kBlockMaxColumns ? 8 : 0;
+    return t->tab.G >= 2 * waves ? waves : 0;
+}
 
 // Waves per block of the block adjoint (AMIGPU_JIT_BLOCK_WAVES overrides): as
 // few as leave each wave a part that fits its registers, since every wave more
@@ -1793,6 +1813,63 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
             o << "  __syncthreads();\n  blk_put" << r << "<WV>(FBr, FBi, sR);\n  __syncthreads();\n  blk_take" << r
               << "<WV>(beta, e_reg, sE, sR, sS, gEr, gEi, gbeta);\n";
         o << "}\n";
+    }
+
+    if (kernels & 32768) {
+        // The block forward of large solutions: as the block adjoint, the
+        // leaves' columns shared by the block's waves, each wave the sums of its
+        // own groups into theirs; then every wave takes whole frequency rows.
+        const int W = jit_block_forward_waves(t);
+        std::vector<double> cost(static_cast<size_t>(G));
+        for (int g = 0; g < G; ++g) {
+            std::vector<HNode> nodes;
+            horner_build(terms_of(tb.group_start[g], tb.group_start[g + 1]), nodes);
+            cost[g] = static_cast<double>(nodes.size()) + 4.0;
+        }
+        bp = BlockPlan();
+        bp.waves = W;
+        (void)split_groups(cost, W, bp.first);
+        o << "constexpr int NW = " << W << ", kBlockCols = NE + L + G;\n";
+        auto fname = [](int l) { return "f" + std::to_string(l); };
+        wave_fn("blk_sums", "ami::clds sF, ami::lds sT", false, [&](int w) {
+            for (int g = bp.first[w]; g < bp.first[w + 1]; ++g) {
+                if (g > bp.first[w]) o << "  AMI_SCHED_FENCE();\n";
+                o << "  { ami::clds p = sF; AMI_OPAQUE(p);\n   ";
+                for (int l : leaves_of(tb.group_start[g], tb.group_start[g + 1]))
+                    o << " const double f" << l << " = p[" << 64 * l << "];";
+                o << "\n";
+                std::vector<HNode> nodes;
+                const HRef v = horner_build(terms_of(tb.group_start[g], tb.group_start[g + 1]), nodes);
+                horner_emit(nodes, fname, o);
+                o << "    sT[" << 64 * g << "] = " << href_expr(v, fname) << "; }\n";
+            }
+        });
+        o << "__device__ __forceinline__ void blk_row(ami::clds sT, const double (&xr)[D], const double (&xi)[D], double "
+             "&acc_re, double &acc_im) {\n";
+        std::vector<HornerTerm> ts;
+        for (int g = 0; g < G; ++g) {
+            HornerTerm h{1.0, {}};
+            for (int j = gbegin(g); j < gend(g); ++j) h.leaves.push_back(tb.group_den_list[j]);
+            h.leaves.push_back(D + g);
+            ts.push_back(std::move(h));
+        }
+        auto leaf = [&](int k) {
+            CVal v;
+            if (k < D) {
+                v.kind = CVal::CPLX;
+                v.re = "xr[" + std::to_string(k) + "]";
+                v.im = "xi[" + std::to_string(k) + "]";
+            } else {
+                v.kind = CVal::REAL;
+                v.re = "sT[" + std::to_string(64 * (k - D)) + "]";
+            }
+            return v;
+        };
+        int temps = 0;
+        CMemo memo;
+        const CVal v = horner_c(ts, leaf, o, temps, memo);
+        o << "    acc_re = " << (v.kind == CVal::ZERO ? "0.0" : v.kind == CVal::CONST ? num(v.c) : v.re)
+          << ";\n    acc_im = " << (v.kind == CVal::CPLX ? v.im : "0.0") << ";\n}\n";
     }
 
     // The adjoint at complex energies in passes (after the complex two-pass

@@ -331,7 +331,7 @@ bool timer_pair(hipEvent_t &start, hipEvent_t &stop) {
     return true;
 }
 
-enum class Path { TABLES, PACKED, SPECIALIZED, TWO_PASS, ADJ_PASSES, ADJ_BLOCK };
+enum class Path { TABLES, PACKED, SPECIALIZED, TWO_PASS, ADJ_PASSES, ADJ_BLOCK, FWD_BLOCK };
 
 // Workspace of one chunk of the two-pass forward and of the adjoint in passes
 // (group sums, energies and their cotangents): 1 GiB unless
@@ -347,6 +347,8 @@ constexpr int kTwoPassMaxFreqs = 65535;
 // With no_load the specialized kernels must already be loaded on the device
 // (jit_loaded): nothing is compiled, loaded or allocated, and a kernel that
 // the call would use but that is not loaded yet is an error, not a fallback.
+// The forward of a solution too large for one pass takes the block kernel under
+// AUTO (Path::FWD_BLOCK), else two kernels over a workspace (Path::TWO_PASS).
 // The adjoint of a large solution takes the block kernel under AUTO where the
 // solution splits over the waves of a block (Path::ADJ_BLOCK), else three
 // kernels over a workspace (Path::ADJ_PASSES): jit_fn (sums pass), jit_fn2
@@ -393,6 +395,14 @@ AmiStatus choose_path(AmiTerms *t, bool hub, bool adjoint, Path &p, void **jit_f
         }
         if (v != AMI_VARIANT_AUTO || (no_load && st != AMI_E_UNSUPPORTED)) return st;
         note = std::string(" (not in passes: ") + amiLastError() + ")";
+        clear_error();
+    }
+    if (two && v == AMI_VARIANT_AUTO && jit_block_forward_waves(t) > 0) {
+        const AmiStatus st = get(kJitBlockForward, jit_fn);
+        if (st == AMI_OK) {
+            p = Path::FWD_BLOCK;
+            return AMI_OK;
+        }
         clear_error();
     }
     if (two) {
@@ -478,13 +488,26 @@ hipError_t launch_jit(void *fn, int64_t nblocks, int block, hipStream_t stream, 
                                  static_cast<unsigned>(block), 1, 1, 0, stream, params, nullptr);
 }
 
+// Launches of a block kernel (`waves` waves share 64 samples) over all `tiles`:
+// more than one where its threads, up to eight per sample, pass the 2^32 of a
+// grid.
+hipError_t launch_block(void *fn, int64_t tiles, int waves, hipStream_t stream, KArgs &a, int gy = 1) {
+    const int64_t most = 0xffffffffLL / (64 * waves);
+    hipError_t e = hipSuccess;
+    for (int64_t t0 = 0; t0 < tiles && e == hipSuccess; t0 += most) {
+        a.s0 = 64 * t0;
+        e = launch_jit(fn, std::min(most, tiles - t0), 64 * waves, stream, a, gy);
+    }
+    return e;
+}
+
 // Parts of the frequency rows of a one-pass forward, each a grid of its own over
 // the samples that forms the leaves and group sums again.  A SIMD with one wave
 // issues FP64 at half rate, so as many parts as keep to two waves per SIMD (2048
 // waves) cost no time; more, up to eight per SIMD, pay while a part holds enough
 // rows to make the repeated leaves an eighth of it (instructions estimated from
-// the sizes).  Order 4, 52 terms, 256 rows of 10^5 samples: one part 141 us, six
-// 103 us.
+// the sizes).  Order 4, 52 terms, 256 rows: 10^5 samples 142 us in one part, 121
+// in six; 10^4 samples 107 and 24.
 int forward_row_parts(const AmiTerms *t, bool hub, int64_t n_waves, int64_t n_f) {
     if (n_f < 4) return 1;
     const Tables &tb = t->tab;
@@ -494,6 +517,15 @@ int forward_row_parts(const AmiTerms *t, bool hub, int64_t n_waves, int64_t n_f)
     const int64_t full_parts = std::min<int64_t>((8192 + n_waves - 1) / std::max<int64_t>(n_waves, 1),
                                                  static_cast<int64_t>(n_f * per_row / (8.0 * once)));
     return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>({std::max(free_parts, full_parts), n_f / 2, 1024})));
+}
+
+// Row parts of the block forward: as many as fill the chip's 512 resident blocks
+// of four waves (256 of eight), a row per wave at least.  Beyond that the leaves
+// and sums formed again cost more than they hide.  560 terms, 256 rows of 4000
+// samples: 40 us in two passes, 29 here; 2804 terms, 200 samples: 41 and 15.
+int block_row_parts(int waves, int64_t tiles, int64_t n_f) {
+    const int64_t fill = (2048 / waves) / std::max<int64_t>(tiles, 1);
+    return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(fill, n_f / waves)));
 }
 
 // The two-pass forward: the samples in chunks whose group sums and energies
@@ -561,8 +593,12 @@ AmiStatus launch_forward(AmiTerms *t, bool hub, KArgs &a, double *out_sum, hipSt
     if (st != AMI_OK) return st;
     if (path == Path::TWO_PASS)
         return launch_two_pass(t, dt, hub, a, out_sum, jit_fn, jit_fn2, stream, false, sums);
+    const bool block_fwd = path == Path::FWD_BLOCK;   // one row of partial sums per 64 samples
+    if (block_fwd) path = Path::SPECIALIZED;
     LaunchShape ls;
-    if (path == Path::SPECIALIZED) {
+    if (block_fwd) {
+        ls.block = 64;
+    } else if (path == Path::SPECIALIZED) {
         ls.block = jit_block(t, hub);
     } else {
         st = pick_shape(fwd_slots(tb), ls);
@@ -583,8 +619,11 @@ AmiStatus launch_forward(AmiTerms *t, bool hub, KArgs &a, double *out_sum, hipSt
     if (path == Path::SPECIALIZED) {
         a.partial = partial;
         a.nrows = rows;
-        e = launch_jit(jit_fn, nblocks, ls.block, stream, a, forward_row_parts(t, hub, rows, a.n_f));
-        g_last_variant = "specialized";
+        const int waves = block_fwd ? jit_block_forward_waves(t) : 0;
+        if (block_fwd) e = launch_block(jit_fn, nblocks, waves, stream, a, block_row_parts(waves, nblocks, a.n_f));
+        else e = launch_jit(jit_fn, nblocks, ls.block, stream, a, forward_row_parts(t, hub, rows, a.n_f));
+        // the block forward is named as the two passes it stands for
+        g_last_variant = block_fwd ? "specialized two-pass" : "specialized";
         if (e == hipSuccess) e = hipGetLastError();
     } else if (path == Path::PACKED) {
         a.tb = packed_tabs(t, dt);
@@ -769,7 +808,7 @@ AmiStatus launch_adjoint_block(AmiTerms *t, DeviceTables *dt, bool hub, KArgs &a
     a.gpartial = ws;
     a.partial = o.out_sum ? ws + static_cast<size_t>(rows) * ncols : nullptr;
     a.nrows = rows;
-    hipError_t e = launch_jit(fn, rows, 64 * jit_block_waves_of(t, hub, cplx), stream, a);
+    hipError_t e = launch_block(fn, rows, jit_block_waves_of(t, hub, cplx), stream, a);
     if (e == hipSuccess) e = hipGetLastError();
     // named by the size, as the kernels it stands for (one pass or passes)
     if (cplx) g_last_variant = t->tab.T > kJitAutoComplexAdjointTerms ? "specialized complex passes" : "specialized complex";
@@ -929,7 +968,7 @@ bool specialized_forward_ready(AmiTerms *t, bool hub, int n_f) {
     std::string note;
     const AmiStatus st = choose_path(t, hub, false, p, &f1, note, &f2, n_f, AMI_VARIANT_AUTO);
     clear_error();
-    return st == AMI_OK && (p == Path::SPECIALIZED || p == Path::TWO_PASS);
+    return st == AMI_OK && (p == Path::SPECIALIZED || p == Path::TWO_PASS || p == Path::FWD_BLOCK);
 }
 
 void set_inputs(KArgs &a, const AmiTerms *t, const double *k, int64_t stride_k, const double *q, double hop_t,
@@ -1352,6 +1391,7 @@ AmiStatus amiTermsSpecialize(AmiTerms *t, int32_t momentum) {
     if (jit_prefers_two_pass(t)) {
         kinds.push_back(kJitSumsPass);
         kinds.push_back(kJitFreqPass);
+        if (jit_block_forward_waves(t) > 0) kinds.push_back(kJitBlockForward);
     } else {
         kinds.push_back(kJitForward);
     }

@@ -162,7 +162,8 @@ AmiStatus code_object(AmiTerms *t, bool hub, int kind) {
     std::string why;
     const bool passes = kind == kJitSumsPass || kind == kJitFreqPass || kind == kJitAdjFreq || kind == kJitAdjLeaf ||
                         kind == kJitComplexSums || kind == kJitComplexFreq || kind == kJitComplexAdjFreq ||
-                        kind == kJitComplexAdjLeaf || kind == kJitBlockAdjoint || kind == kJitComplexBlockAdjoint;
+                        kind == kJitComplexAdjLeaf || kind == kJitBlockAdjoint ||
+                        kind == kJitComplexBlockAdjoint || kind == kJitBlockForward;
     if (!jit_supported(t, hub, &why, passes)) {
         err = "no specialized kernel: " + why;
         return fail(AMI_E_UNSUPPORTED, err);
@@ -170,6 +171,10 @@ AmiStatus code_object(AmiTerms *t, bool hub, int kind) {
     if ((kind == kJitBlockAdjoint || kind == kJitComplexBlockAdjoint) &&
         jit_block_waves(t, hub, kind == kJitComplexBlockAdjoint) == 0) {
         err = "no block adjoint: the solution does not split over the waves of a block";
+        return fail(AMI_E_UNSUPPORTED, err);
+    }
+    if (kind == kJitBlockForward && jit_block_forward_waves(t) == 0) {
+        err = "no block forward: Taylor leaves, or the columns of a sample exceed the LDS";
         return fail(AMI_E_UNSUPPORTED, err);
     }
     if (jit_kind_complex(kind))
@@ -284,8 +289,7 @@ AmiStatus jit_get(AmiTerms *t, bool hub, int kind, void **fn) {
     static const char *const kNames[kJitKinds] = {"ami_jit_fwd",  "ami_jit_adj",   "ami_jit_mc",   "ami_jit_cfwd",
                                                   "ami_jit_sums", "ami_jit_freq",  "ami_jit_adjf", "ami_jit_adjl",
                                                   "ami_jit_cadj", "ami_jit_csums", "ami_jit_cfreq", "ami_jit_cadjf",
-                                                  "ami_jit_cadjl", "ami_jit_badj",
-                                                  "ami_jit_bcadj"};
+                                                  "ami_jit_cadjl", "ami_jit_badj", "ami_jit_bcadj", "ami_jit_bfwd"};
     e = hipModuleGetFunction(&f, mod, kNames[kind]);
     if (e != hipSuccess) {
         (void)hipModuleUnload(mod);

@@ -51,6 +51,7 @@ bool jit_adjoint_passes_supported(const AmiTerms *t, bool hub, std::string *why)
 // jit_block_waves_of keeps it with the handle.
 int jit_block_waves(const AmiTerms *t, bool hub, bool cplx);
 int jit_block_waves_of(AmiTerms *t, bool hub, bool cplx = false);
+int jit_block_forward_waves(const AmiTerms *t);   // of the block forward, 0: none
 
 // Whether the diagram can be specialized for the energy (hub = false) or
 // momentum (hub = true) input; *why says why not.
@@ -78,7 +79,8 @@ int jit_block(const AmiTerms *t, bool hub);
 // passes of the adjoint at complex energies that follow the first of those
 // (kernels & 2048: per frequency, the complex group-sum and denominator
 // cotangents; kernels & 4096: the complex leaf cotangents and the gradients),
-// and the block adjoint (kernels & 8192; at complex energies, alone, 16384).
+// and the block adjoint (kernels & 8192; at complex energies 16384) or the block
+// forward (32768), each alone.
 // nested_part: terms per part of the one-pass adjoint's leaf cotangents as a
 // reverse sweep of the nested group sums (0: per-term prefix/suffix products;
 // -1: the AMIGPU_JIT_NESTED_COTANGENTS override, else per-term products).
@@ -126,7 +128,8 @@ int64_t code_meta(const std::vector<char> &code, const char *key);
 // kJitComplexAdjLeaf the frequency and leaf passes of the adjoint at complex
 // energies (after kJitComplexSums); kJitBlockAdjoint the adjoint of large
 // solutions whose work the waves of a block split (no workspace),
-// kJitComplexBlockAdjoint the same at complex energies.
+// kJitComplexBlockAdjoint the same at complex energies, kJitBlockForward the
+// forward of large solutions that way.
 enum JitKind {
     kJitForward = 0,
     kJitAdjoint = 1,
@@ -142,9 +145,10 @@ enum JitKind {
     kJitComplexAdjFreq = 11,
     kJitComplexAdjLeaf = 12,
     kJitBlockAdjoint = 13,
-    kJitComplexBlockAdjoint = 14
+    kJitComplexBlockAdjoint = 14,
+    kJitBlockForward = 15
 };
-constexpr int kJitKinds = 15;
+constexpr int kJitKinds = 16;
 
 // Kinds for the energy input only (complex energies).
 inline bool jit_kind_complex(int kind) {

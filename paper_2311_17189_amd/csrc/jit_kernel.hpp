@@ -36,7 +36,7 @@
 // passes of the forward at complex energies (512, 1024), the frequency and
 // leaf passes of the adjoint at complex energies (2048, 4096), or a sum of
 // them
-// The one-pass forwards run blocks (tile, part of the rows): every part forms
+// The one-pass and block forwards run blocks (tile, part of the rows): every part forms
 // the tile's leaves and group sums again, and takes an even number of rows.
 #define AMI_JIT_ROW_PART(f0, f1)                                                    \
     const int per = ((a.n_f + static_cast<int>(gridDim.y) - 1) / static_cast<int>(gridDim.y) + 1) & ~1; \
@@ -191,15 +191,26 @@ extern "C" __global__ __launch_bounds__(AMI_JIT_BLOCK) void ami_jit_cadjl(ami::K
 // waves, or one of eight, on a CU
 extern "C" __global__ __launch_bounds__(64 * amijit::NW) __attribute__((amdgpu_waves_per_eu(2))) void ami_jit_badj(ami::KArgs a) {
     __shared__ double sm[64 * amijit::kBlockCols];
-    if (a.n_f == 1) amijit::badj_tile<AMI_JIT_HUB, true>(a, blockIdx.x, sm);
-    else amijit::badj_tile<AMI_JIT_HUB, false>(a, blockIdx.x, sm);
+    const int64_t tile = (a.s0 >> 6) + blockIdx.x;      // s0: the launch's first sample
+    if (a.n_f == 1) amijit::badj_tile<AMI_JIT_HUB, true>(a, tile, sm);
+    else amijit::badj_tile<AMI_JIT_HUB, false>(a, tile, sm);
 }
 #endif
 
 #if AMI_JIT_KERNELS & 16384
 extern "C" __global__ __launch_bounds__(64 * amijit::NW) __attribute__((amdgpu_waves_per_eu(2))) void ami_jit_bcadj(ami::KArgs a) {
     __shared__ double sm[64 * amijit::kBlockCols];
-    if (a.n_f == 1) amijit::bcadj_tile<true>(a, blockIdx.x, sm);
-    else amijit::bcadj_tile<false>(a, blockIdx.x, sm);
+    const int64_t tile = (a.s0 >> 6) + blockIdx.x;      // s0: the launch's first sample
+    if (a.n_f == 1) amijit::bcadj_tile<true>(a, tile, sm);
+    else amijit::bcadj_tile<false>(a, tile, sm);
+}
+#endif
+
+#if AMI_JIT_KERNELS & 32768
+extern "C" __global__ __launch_bounds__(64 * amijit::NW) __attribute__((amdgpu_waves_per_eu(2))) void ami_jit_bfwd(ami::KArgs a) {
+    __shared__ double sm[64 * amijit::kBlockCols];
+    const int64_t tile = (a.s0 >> 6) + blockIdx.x;      // s0: the launch's first sample
+    AMI_JIT_ROW_PART(f0, f1)
+    amijit::bfwd_tile<AMI_JIT_HUB>(a, tile, f0, f1, sm);
 }
 #endif

@@ -1236,6 +1236,20 @@ __device__ __forceinline__ void cadj_tile(const KArgs &a, int64_t blk, double *p
 }
 #endif
 
+#if AMI_JIT_KERNELS & (8192 | 32768)
+// The line momenta of a sample (a wave keeps those it uses).
+__device__ __forceinline__ void blk_lines(const KArgs &a, int64_t sc, double (&Kx)[NGA], double (&Ky)[NGA]) {
+    double in[NIN], kx[NIA], ky[NIA];
+    load_inputs<true>(a, sc, in);
+#pragma unroll
+    for (int l = 0; l < NI; ++l) {
+        kx[l] = ami::reduce_2pi(in[2 * l]);
+        ky[l] = ami::reduce_2pi(in[2 * l + 1]);
+    }
+    lines(kx, ky, a.q, Kx, Ky);
+}
+#endif
+
 #if AMI_JIT_KERNELS & (8192 | 16384)
 // sum over the waves of the columns first, first + 1, ... (in wave order)
 __device__ __forceinline__ double blk_wave_total(ami::clds col, int first) {
@@ -1275,18 +1289,6 @@ __device__ __forceinline__ void blk_store_rows(const double *stage, double *dst,
 // 113 -> 77 us, 264 terms 78 -> 64, 136 terms 57 -> 42 at 2 10^5.  What is left
 // of it is issue (2.1 10^4 VALU instructions per block, 115 us of the 190) and
 // the barriers of unequal waves.
-// The line momenta of a sample (a wave keeps those it uses).
-__device__ __forceinline__ void blk_lines(const KArgs &a, int64_t sc, double (&Kx)[NGA], double (&Ky)[NGA]) {
-    double in[NIN], kx[NIA], ky[NIA];
-    load_inputs<true>(a, sc, in);
-#pragma unroll
-    for (int l = 0; l < NI; ++l) {
-        kx[l] = ami::reduce_2pi(in[2 * l]);
-        ky[l] = ami::reduce_2pi(in[2 * l + 1]);
-    }
-    lines(kx, ky, a.q, Kx, Ky);
-}
-
 // The wave's energies to their columns.
 template <bool HUB, int WV>
 __device__ __forceinline__ void blk_energies(const KArgs &a, int64_t sc, ami::lds col) {
@@ -1677,6 +1679,86 @@ __device__ __forceinline__ void bcadj_tile(const KArgs &a, int64_t tile, double 
     case 5: if constexpr (NW > 4) bcadj_wave<5, ONE>(a, tile, sm); break;
     case 6: if constexpr (NW > 4) bcadj_wave<6, ONE>(a, tile, sm); break;
     case 7: if constexpr (NW > 4) bcadj_wave<7, ONE>(a, tile, sm); break;
+    }
+}
+#endif
+
+#if AMI_JIT_KERNELS & 32768
+// Block forward of large solutions: NW waves share 64 samples.  Wave j mod NW
+// forms line j's energy and leaf j, each wave its own groups' sums, all in LDS
+// columns (column c of lane i at [64 c + i]: NE energies, L leaves, G group
+// sums); then each wave takes every NW-th of the frequency rows [f0, f1) whole,
+// reading the group sums where the nesting needs them.  The two kernels over a
+// workspace that it replaces moved every group sum through L2 once per row
+// (order 6, 2804 terms, 16 rows of 2 10^5 samples: 2.4 GB, at which the
+// frequency pass ran at half its issue rate).  Now issue bounds it, and LDS
+// reads in the sums of one row.  2 10^5 momenta: 2804 terms 211 -> 156 us (one
+// row 82 -> 77), 560 terms 114 -> 82 (38 -> 31); solutions whose one-pass forward
+// fits the registers stay there (264 terms: 48 against 54 us, one row 17 against
+// 22).  The values are the same bit for bit.
+template <bool HUB, int WV>
+__device__ __forceinline__ void bfwd_sums(const KArgs &a, int64_t sc, ami::lds col) {
+    if constexpr (HUB) {
+        double Kx[NGA], Ky[NGA];
+        blk_lines(a, sc, Kx, Ky);
+#pragma unroll
+        for (int j = WV; j < NG; j += NW) col[64 * j] = fma(2.0 * a.hop_t, ami::cos_red(Kx[j]) + ami::cos_red(Ky[j]), a.mu);
+    } else {
+        const double *row = a.energies + sc * a.stride_s;
+#pragma unroll
+        for (int i = WV; i < NE; i += NW) col[64 * i] = row[i * a.stride_i];
+    }
+    __syncthreads();
+    double E[NE], x[L];
+#pragma unroll
+    for (int i = 0; i < NE; ++i) E[i] = col[64 * i];
+    leaf_args(E, x);
+#pragma unroll
+    for (int l = WV; l < L; l += NW) {
+        double f, fm;
+        ami::leaf_pair(kBose[l], a.beta * (kBose[l] ? x[l] + a.e_reg : x[l]), f, fm);
+        col[64 * (NE + l)] = f;
+    }
+    __syncthreads();
+    blk_sums<WV>(col + 64 * NE, col + 64 * (NE + L));
+}
+
+template <bool HUB>
+__device__ __forceinline__ void bfwd_tile(const KArgs &a, int64_t tile, int f0, int f1, double *sm) {
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t s = tile * 64 + lane;
+    const bool active = s < a.n_e;
+    const int64_t sc = active ? s : a.n_e - 1;
+    const ami::lds col = (ami::lds)sm + lane;
+    switch (wv) {                       // the waves' own copies pass the same barriers
+    case 0: bfwd_sums<HUB, 0>(a, sc, col); break;
+    case 1: bfwd_sums<HUB, 1>(a, sc, col); break;
+    case 2: bfwd_sums<HUB, 2>(a, sc, col); break;
+    case 3: bfwd_sums<HUB, 3>(a, sc, col); break;
+    case 4: if constexpr (NW > 4) bfwd_sums<HUB, 4>(a, sc, col); break;
+    case 5: if constexpr (NW > 4) bfwd_sums<HUB, 5>(a, sc, col); break;
+    case 6: if constexpr (NW > 4) bfwd_sums<HUB, 6>(a, sc, col); break;
+    case 7: if constexpr (NW > 4) bfwd_sums<HUB, 7>(a, sc, col); break;
+    }
+    __syncthreads();
+    double E[NE];
+#pragma unroll
+    for (int i = 0; i < NE; ++i) E[i] = col[64 * i];
+    for (int f = f0 + wv; f < f1; f += NW) {
+        double wr[NXA], wi[NXA], xr[D], xi[D], re, im;
+        load_freq(a, f, wr, wi);
+        reciprocals(E, wr, wi, xr, xi);
+        ami::clds sT = col + 64 * (NE + L);
+        AMI_OPAQUE(sT);                 // read in every row, not held through them
+        blk_row(sT, xr, xi, re, im);
+        if (active && a.out) {
+            double2 v;
+            v.x = re;
+            v.y = im;
+            reinterpret_cast<double2 *>(a.out)[static_cast<int64_t>(f) * a.n_e + s] = v;
+        }
+        if (a.partial)
+            ami::wave_store2(active ? re : 0.0, active ? im : 0.0, lane, a.partial + 2 * f * a.nrows + tile, a.nrows);
     }
 }
 #endif
