@@ -68,6 +68,7 @@ struct DeviceTables {
         void *stream = nullptr;
         void *ptr = nullptr;
         size_t bytes = 0;
+        unsigned *ticket = nullptr;     // of calls whose last block adds the partial sums (zero between launches)
     };
     std::vector<Workspace> ws;
     std::vector<void *> retired;

@@ -473,6 +473,75 @@ AmiStatus workspace(AmiTerms *t, DeviceTables *dt, hipStream_t stream, size_t by
     return AMI_OK;
 }
 
+// Where the totals of a call's partial sums go (finish_small): a's gradient
+// columns, then the row sums of the values.
+struct AdjOut {
+    double *grad_beta = nullptr, *grad_mu = nullptr, *grad_t = nullptr, *grad_freqs = nullptr;
+    double *out_sum = nullptr;   // forward row sums computed on the way (optional)
+};
+
+// Has the kernel's last block add the partial sums (a.nrows rows of ncols columns
+// of gradients and nval of values) instead of a second launch, where that is
+// cheaper: the launch takes 3 us of the host, the last block's work some 30 ns
+// of the GPU per block (each releases its rows) and 1 us per 16 loads of 64 rows
+// by a wave.  The limits keep that below the launch it replaces, so that a caller
+// who waits for every call loses nothing either; a kernel whose blocks run long
+// takes fewer.  At most 1024 rows, the reduction kernel's one pass.  Per call,
+// with two launches and with one: forwards of momenta 14.4 and 11.3 us, adjoints
+// 21.5 and 18.5 (waited for: 23.7 and 23.7, 31.5 and 31); past the limits, waited
+// for: 32 and 35 (order 2 adjoint, 130 blocks), and 22 and 28 (2804 terms, 3 rows,
+// 500 blocks).
+// Needs the stream's workspace (call workspace() first).  Not under capture,
+// whose replays may run on other streams beside this one's calls, nor on the
+// per-thread default stream, one handle of many streams: both would share the
+// counter.
+struct FinishLimits {
+    int64_t blocks, loads;
+};
+constexpr FinishLimits kFinishOnePass{64, 16}, kFinishBlockForward{64, 16}, kFinishBlockAdjoint{32, 4};
+constexpr FinishLimits kFinishComplex{32, 8}, kFinishComplexAdjoint{32, 4};
+bool finish_small(AmiTerms *t, DeviceTables *dt, hipStream_t stream, KArgs &a, const FinishLimits &lim, int64_t blocks,
+                  int waves, int ncols, int nval, const AdjOut &o) {
+    const int64_t chunks = (a.nrows + 63) / 64;
+    if (chunks > 16 || blocks > lim.blocks || (ncols + nval + waves - 1) / waves * chunks > lim.loads) return false;
+    if (stream == hipStreamPerThread) return false;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (cap != hipStreamCaptureStatusNone) return false;
+    {
+        std::lock_guard<std::mutex> lk(t->dev_mu);
+        DeviceTables::Workspace *w = nullptr;
+        for (auto &x : dt->ws)
+            if (x.stream == static_cast<void *>(stream)) w = &x;
+        if (!w) return false;
+        if (!w->ticket) {
+            void *p = nullptr;
+            if (hipMalloc(&p, 256) != hipSuccess) {
+                (void)hipGetLastError();
+                return false;
+            }
+            dt->retired.push_back(p);     // freed with the handle
+            if (fill(static_cast<double *>(p), 32, stream) != AMI_OK) {
+                clear_error();
+                return false;
+            }
+            w->ticket = static_cast<unsigned *>(p);
+        }
+        a.fin_ticket = w->ticket;
+    }
+    a.fin_cols = ncols + nval;
+    a.fin_grad = ncols;
+    a.fin_beta = o.grad_beta;
+    a.fin_mu = o.grad_mu;
+    a.fin_t = o.grad_t;
+    a.fin_w = o.grad_freqs;
+    a.fin_sum = o.out_sum;
+    return true;
+}
+
 // Launch of a specialized kernel on a grid of nblocks x gy blocks (timed by
 // the kernel timer when it runs).
 hipError_t launch_jit(void *fn, int64_t nblocks, int block, hipStream_t stream, KArgs &a, int gy = 1) {
@@ -501,6 +570,14 @@ hipError_t launch_block(void *fn, int64_t tiles, int waves, hipStream_t stream, 
     return e;
 }
 
+// The parts of at most `parts` that hold a row: each takes an even number of
+// them (AMI_JIT_ROW_PART).
+int nonempty_parts(int64_t n_f, int64_t parts) {
+    if (parts <= 1) return 1;
+    const int64_t per = ((n_f + parts - 1) / parts + 1) & ~int64_t(1);
+    return static_cast<int>((n_f + per - 1) / per);
+}
+
 // Parts of the frequency rows of a one-pass forward, each a grid of its own over
 // the samples that forms the leaves and group sums again.  A SIMD with one wave
 // issues FP64 at half rate, so as many parts as keep to two waves per SIMD (2048
@@ -516,7 +593,7 @@ int forward_row_parts(const AmiTerms *t, bool hub, int64_t n_waves, int64_t n_f)
     const int64_t free_parts = 2048 / std::max<int64_t>(n_waves, 1);
     const int64_t full_parts = std::min<int64_t>((8192 + n_waves - 1) / std::max<int64_t>(n_waves, 1),
                                                  static_cast<int64_t>(n_f * per_row / (8.0 * once)));
-    return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>({std::max(free_parts, full_parts), n_f / 2, 1024})));
+    return nonempty_parts(n_f, std::min<int64_t>({std::max(free_parts, full_parts), n_f / 2, 1024}));
 }
 
 // Row parts of the block forward: as many as fill the chip's 512 resident blocks
@@ -525,7 +602,7 @@ int forward_row_parts(const AmiTerms *t, bool hub, int64_t n_waves, int64_t n_f)
 // samples: 40 us in two passes, 29 here; 2804 terms, 200 samples: 41 and 15.
 int block_row_parts(int waves, int64_t tiles, int64_t n_f) {
     const int64_t fill = (2048 / waves) / std::max<int64_t>(tiles, 1);
-    return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(fill, n_f / waves)));
+    return nonempty_parts(n_f, std::min<int64_t>(fill, n_f / waves));
 }
 
 // The two-pass forward: the samples in chunks whose group sums and energies
@@ -619,9 +696,17 @@ AmiStatus launch_forward(AmiTerms *t, bool hub, KArgs &a, double *out_sum, hipSt
     if (path == Path::SPECIALIZED) {
         a.partial = partial;
         a.nrows = rows;
-        const int waves = block_fwd ? jit_block_forward_waves(t) : 0;
-        if (block_fwd) e = launch_block(jit_fn, nblocks, waves, stream, a, block_row_parts(waves, nblocks, a.n_f));
-        else e = launch_jit(jit_fn, nblocks, ls.block, stream, a, forward_row_parts(t, hub, rows, a.n_f));
+        const int waves = block_fwd ? jit_block_forward_waves(t) : ls.block / 64;
+        const int parts = block_fwd ? block_row_parts(waves, nblocks, a.n_f) : forward_row_parts(t, hub, rows, a.n_f);
+        if (out_sum && !sums) {
+            AdjOut o;
+            o.out_sum = out_sum;
+            if (finish_small(t, dt, stream, a, block_fwd ? kFinishBlockForward : kFinishOnePass, nblocks * parts, waves, 0,
+                             2 * a.n_f, o))
+                out_sum = nullptr;
+        }
+        if (block_fwd) e = launch_block(jit_fn, nblocks, waves, stream, a, parts);
+        else e = launch_jit(jit_fn, nblocks, ls.block, stream, a, parts);
         // the block forward is named as the two passes it stands for
         g_last_variant = block_fwd ? "specialized two-pass" : "specialized";
         if (e == hipSuccess) e = hipGetLastError();
@@ -697,11 +782,6 @@ AmiStatus find_uploaded(AmiTerms *t, DeviceTables **out) {
         }
     return fail(AMI_E_ARG, "the tables are not on this device: call amiTermsUpload first");
 }
-
-struct AdjOut {
-    double *grad_beta = nullptr, *grad_mu = nullptr, *grad_t = nullptr, *grad_freqs = nullptr;
-    double *out_sum = nullptr;   // forward row sums computed on the way (optional)
-};
 
 // Whether the adjoint of n_e samples with ncols columns of per-wave partial sums
 // fits the allocation-free scratch: alone up to the one-pass kernel's automatic
@@ -808,12 +888,15 @@ AmiStatus launch_adjoint_block(AmiTerms *t, DeviceTables *dt, bool hub, KArgs &a
     a.gpartial = ws;
     a.partial = o.out_sum ? ws + static_cast<size_t>(rows) * ncols : nullptr;
     a.nrows = rows;
-    hipError_t e = launch_block(fn, rows, jit_block_waves_of(t, hub, cplx), stream, a);
+    const int waves = jit_block_waves_of(t, hub, cplx);
+    const bool fin = !fixed_ws && finish_small(t, dt, stream, a, kFinishBlockAdjoint, rows, waves, ncols, nval, o);
+    hipError_t e = launch_block(fn, rows, waves, stream, a);
     if (e == hipSuccess) e = hipGetLastError();
     // named by the size, as the kernels it stands for (one pass or passes)
     if (cplx) g_last_variant = t->tab.T > kJitAutoComplexAdjointTerms ? "specialized complex passes" : "specialized complex";
     else g_last_variant = t->tab.T > kJitAutoAdjointTerms ? "specialized passes" : "specialized";
     if (e != hipSuccess) return hip_fail(e, "block adjoint launch");
+    if (fin) return AMI_OK;
     hipLaunchKernelGGL(ami_adj_finalize_kernel, dim3(ncols + nval), dim3(kRedThreads), 0, stream, a.gpartial, rows,
                        ncols, 1, o.grad_beta, o.grad_mu, o.grad_t, o.grad_freqs, 2 * a.n_f, o.out_sum);
     e = hipGetLastError();
@@ -874,11 +957,14 @@ AmiStatus launch_adjoint(AmiTerms *t, bool hub, KArgs &a, const AdjOut &o, hipSt
         if (st != AMI_OK) return st;
     }
     hipError_t e;
+    bool fin = false;
     a.gpartial = partial;
     a.partial = o.out_sum ? partial + n_grad : nullptr;
     const dim3 grid(static_cast<unsigned>(nblocks)), block(ls.block);
     if (path == Path::SPECIALIZED) {
         a.nrows = rows;
+        fin = !fixed_ws && finish_small(t, dt, stream, a, kFinishOnePass, nblocks, ls.block / 64, ncols,
+                                       o.out_sum ? 2 * a.n_f : 0, o);
         e = launch_jit(jit_fn, nblocks, ls.block, stream, a);
         g_last_variant = "specialized";
         if (e == hipSuccess) e = hipGetLastError();
@@ -893,6 +979,7 @@ AmiStatus launch_adjoint(AmiTerms *t, bool hub, KArgs &a, const AdjOut &o, hipSt
         timer_mark(stream, true);
     }
     if (e != hipSuccess) return hip_fail(e, "adjoint launch");
+    if (fin) return AMI_OK;
     // one launch for every reduction: gradient columns, then the value row sums
     const int n_red = ncols + (o.out_sum ? 2 * a.n_f : 0);
     hipLaunchKernelGGL(ami_adj_finalize_kernel, dim3(n_red), dim3(kRedThreads), 0, stream, partial, rows, ncols,
@@ -1077,11 +1164,16 @@ AmiStatus amiEvaluateComplex(AmiTerms *t, const double *energies, int64_t n_e, i
         st = workspace(t, dt, stream, static_cast<size_t>(rows) * n_f * 2 * sizeof(double), &a.partial);
         if (st != AMI_OK) return st;
     }
-    hipError_t e = launch_jit(fn, nblocks, block, stream, a, forward_row_parts(t, false, rows, n_f));
+    const int parts = forward_row_parts(t, false, rows, n_f);
+    AdjOut o;
+    o.out_sum = out_sum;
+    const bool fin = out_sum && finish_small(t, dt, stream, a, kFinishComplex, nblocks * parts, block / 64, 0,
+                                             static_cast<int>(2 * n_f), o);
+    hipError_t e = launch_jit(fn, nblocks, block, stream, a, parts);
     if (e == hipSuccess) e = hipGetLastError();
     g_last_variant = "specialized complex";
     if (e != hipSuccess) return hip_fail(e, "complex-energy launch");
-    if (out_sum) {
+    if (out_sum && !fin) {
         hipLaunchKernelGGL(ami_colsum_kernel, dim3(static_cast<unsigned>(2 * n_f)), dim3(kRedThreads), 0, stream,
                            a.partial, rows, static_cast<int64_t>(1), rows, out_sum);
         e = hipGetLastError();
@@ -1179,11 +1271,14 @@ AmiStatus amiEvaluateComplexAdjoint(AmiTerms *t, const double *energies, int64_t
     a.nrows = rows;
     a.gpartial = partial;
     a.partial = out_sum ? partial + n_grad : nullptr;
+    const int nval = out_sum ? 2 * static_cast<int>(n_f) : 0;
+    const bool fin = finish_small(t, dt, stream, a, kFinishComplexAdjoint, nblocks, block / 64, ncols, nval, bo);
     hipError_t e = launch_jit(fn, nblocks, block, stream, a);
     if (e == hipSuccess) e = hipGetLastError();
     g_last_variant = "specialized complex";
     if (e != hipSuccess) return hip_fail(e, "complex-energy adjoint launch");
-    const int n_red = ncols + (out_sum ? 2 * static_cast<int>(n_f) : 0);
+    if (fin) return AMI_OK;
+    const int n_red = ncols + nval;
     hipLaunchKernelGGL(ami_adj_finalize_kernel, dim3(n_red), dim3(kRedThreads), 0, stream, partial, rows, ncols, 1,
                        grad_beta, static_cast<double *>(nullptr), static_cast<double *>(nullptr), grad_freqs,
                        2 * static_cast<int>(n_f), out_sum);

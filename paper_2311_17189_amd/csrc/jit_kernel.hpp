@@ -36,22 +36,87 @@
 // passes of the forward at complex energies (512, 1024), the frequency and
 // leaf passes of the adjoint at complex energies (2048, 4096), or a sum of
 // them
-// The one-pass and block forwards run blocks (tile, part of the rows): every part forms
-// the tile's leaves and group sums again, and takes an even number of rows.
+
+// Small calls (a.fin_cols > 0): the last block to arrive adds the partial sums of
+// all blocks, in the order of the reduction kernel that large calls launch (64
+// rows at a time, then those totals in row order: the same bits).  NW waves per
+// block, each with its columns, 16 loads in flight.  lds: a word of the kernel's
+// LDS.  The second launch this saves bounds such calls on
+// the host: order 2, 300 samples 14.4 -> 11.3 us, the adjoint of 10^4 21.5 -> 18.5.
+// Every wave's rows are in L2 before the barrier, and released to the device before
+// the block is counted; the block that completes the count resets it for the
+// next launch on the stream.
+template <int NW>
+__device__ __forceinline__ void finish_sums(const ami::KArgs &a, void *lds) {
+    if (a.fin_cols == 0) return;
+    volatile unsigned &last = *static_cast<volatile unsigned *>(lds);
+    const unsigned blocks = gridDim.x * gridDim.y;
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned before = 0;
+        if (blocks > 1) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            before = __hip_atomic_fetch_add(a.fin_ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        last = before == blocks - 1;
+        if (last && blocks > 1) __hip_atomic_store(a.fin_ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (!last) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const double *cols = a.gpartial ? a.gpartial : a.partial;
+    const int rows = static_cast<int>(a.nrows), chunks = (rows + 63) >> 6;
+    const int todo = a.fin_cols > wave ? (a.fin_cols - wave + NW - 1) / NW * chunks : 0;
+    int lc = wave, lk = 0, c = wave, k = 0;     // column and chunk of the next load and of the next addend
+    double total = 0.0;
+    for (int p = 0; p < todo; p += 16) {
+        double v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const int row = 64 * lk + lane;
+            v[u] = p + u < todo && row < rows ? cols[lc * rows + row] : 0.0;
+            if (++lk == chunks) {
+                lk = 0;
+                lc += NW;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            if (p + u >= todo) break;
+            total += ami::wave_sum(0.0 + v[u]);
+            if (++k < chunks) continue;
+            double *dst = nullptr;
+            if (c >= a.fin_grad) dst = a.fin_sum + (c - a.fin_grad);
+            else if (c >= ami::kAdjScalars) dst = a.fin_w ? a.fin_w + (c - ami::kAdjScalars) : nullptr;
+            else if (c < 3) dst = c == 0 ? a.fin_beta : c == 1 ? a.fin_mu : a.fin_t;
+            if (lane == 0 && dst) *dst = total;
+            total = 0.0;
+            k = 0;
+            c += NW;
+        }
+    }
+}
+
+// The one-pass and block forwards run blocks (tile, part of the rows): every part
+// forms the tile's leaves and group sums again, and takes an even number of
+// rows; the host launches no empty part.
 #define AMI_JIT_ROW_PART(f0, f1)                                                    \
     const int per = ((a.n_f + static_cast<int>(gridDim.y) - 1) / static_cast<int>(gridDim.y) + 1) & ~1; \
     const int f0 = static_cast<int>(blockIdx.y) * per;                                      \
-    if (f0 >= a.n_f) return;                                                                \
     const int f1 = f0 + per < a.n_f ? f0 + per : a.n_f;
 
 #if AMI_JIT_KERNELS & 1
 extern "C" __global__ __launch_bounds__(AMI_JIT_BLOCK) void ami_jit_fwd(ami::KArgs a) {
+    __shared__ unsigned word;
     if (a.n_f == 1) {
         amijit::fwd_tile<AMI_JIT_HUB, true>(a, blockIdx.x, 0, 1);
     } else {
         AMI_JIT_ROW_PART(f0, f1)
         amijit::fwd_tile<AMI_JIT_HUB, false>(a, blockIdx.x, f0, f1);
     }
+    finish_sums<AMI_JIT_BLOCK / 64>(a, &word);
 }
 #endif
 
@@ -70,6 +135,7 @@ extern "C" __global__ __launch_bounds__(AMI_JIT_BLOCK) AMI_JIT_ADJ_ATTR void ami
     amijit::load_inputs<AMI_JIT_HUB>(a, s < a.n_e ? s : a.n_e - 1, in);
     if (a.n_f == 1) amijit::adj_tile<AMI_JIT_HUB, true>(a, blockIdx.x, park, in);
     else amijit::adj_tile<AMI_JIT_HUB, false>(a, blockIdx.x, park, in);
+    finish_sums<AMI_JIT_BLOCK / 64>(a, park);
 }
 #endif
 
@@ -81,8 +147,10 @@ extern "C" __global__ __launch_bounds__(AMI_JIT_BLOCK) void ami_jit_mc(ami::KArg
 
 #if AMI_JIT_KERNELS & 8
 extern "C" __global__ __launch_bounds__(AMI_JIT_BLOCK) void ami_jit_cfwd(ami::KArgs a) {
+    __shared__ unsigned word;
     AMI_JIT_ROW_PART(f0, f1)
     amijit::cfwd_tile(a, blockIdx.x, f0, f1);
+    finish_sums<AMI_JIT_BLOCK / 64>(a, &word);
 }
 #endif
 
@@ -93,6 +161,7 @@ __attribute__((amdgpu_waves_per_eu(AMI_JIT_CADJ_WAVES)))
 extern "C" __global__ __launch_bounds__(AMI_JIT_BLOCK) void ami_jit_cadj(ami::KArgs a) {
     __shared__ double park[amijit::kParkS ? 2 * amijit::L * AMI_JIT_BLOCK : 1];
     amijit::cadj_tile(a, blockIdx.x, park);
+    finish_sums<AMI_JIT_BLOCK / 64>(a, park);
 }
 #endif
 
@@ -194,6 +263,7 @@ extern "C" __global__ __launch_bounds__(64 * amijit::NW) __attribute__((amdgpu_w
     const int64_t tile = (a.s0 >> 6) + blockIdx.x;      // s0: the launch's first sample
     if (a.n_f == 1) amijit::badj_tile<AMI_JIT_HUB, true>(a, tile, sm);
     else amijit::badj_tile<AMI_JIT_HUB, false>(a, tile, sm);
+    finish_sums<amijit::NW>(a, sm);
 }
 #endif
 
@@ -203,6 +273,7 @@ extern "C" __global__ __launch_bounds__(64 * amijit::NW) __attribute__((amdgpu_w
     const int64_t tile = (a.s0 >> 6) + blockIdx.x;      // s0: the launch's first sample
     if (a.n_f == 1) amijit::bcadj_tile<true>(a, tile, sm);
     else amijit::bcadj_tile<false>(a, tile, sm);
+    finish_sums<amijit::NW>(a, sm);
 }
 #endif
 
@@ -212,5 +283,6 @@ extern "C" __global__ __launch_bounds__(64 * amijit::NW) __attribute__((amdgpu_w
     const int64_t tile = (a.s0 >> 6) + blockIdx.x;      // s0: the launch's first sample
     AMI_JIT_ROW_PART(f0, f1)
     amijit::bfwd_tile<AMI_JIT_HUB>(a, tile, f0, f1, sm);
+    finish_sums<amijit::NW>(a, sm);
 }
 #endif

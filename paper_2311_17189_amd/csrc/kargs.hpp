@@ -49,6 +49,12 @@ struct KArgs {
     // the counter-based generator (seed), the second accumulates per frequency
     // row sum Re I, sum Im I, sum (Re I)^2, sum (Im I)^2 (columns 4 f .. 4 f + 3)
     int mc;
+    // small calls: the kernel's last block adds the partial sums itself
+    // (finish_sums; fin_cols columns, null or 0: a reduction kernel follows):
+    // a counter that is zero between launches, and the totals' destinations
+    unsigned *fin_ticket;
+    int fin_cols, fin_grad;     // columns, of which the gradients' first
+    double *fin_beta, *fin_mu, *fin_t, *fin_w, *fin_sum;
 };
 
 // Frequency rows one Monte-Carlo launch accumulates (the caller splits longer lists).
