@@ -261,7 +261,9 @@ AmiStatus amiEvaluateComplex(AmiTerms *terms,
  * amiEvaluateComplex; out / out_sum (device, or NULL) receive the forward
  * values on the way.  The sums over samples are reduced in a fixed order.
  * Served by the specialized kernels (compiled on first use): one pass up to
- * 512 terms (up to 1024 under AMI_VARIANT_SPECIALIZED); above, or under
+ * 200 terms (50 with one frequency row; up to 1024 under
+ * AMI_VARIANT_SPECIALIZED); above, a kernel whose waves split the solution,
+ * or, where the solution does not split (one pass up to 512 terms) and under
  * AMI_VARIANT_TWO_PASS, passes over the chunked workspace of the two-pass
  * variant (complex group sums and energies stored; per frequency row the
  * values and the complex cotangents of group sums and denominators; then the
@@ -293,13 +295,14 @@ AmiStatus amiEvaluateComplexAdjoint(AmiTerms *terms,
  * T_j(x) = beta^j f^(j)(beta x) / j!, has dT_j/dx = (j + 1) T_(j+1) and
  * dT_j/dbeta = (j T_j + x dT_j/dx) / beta.  Other arguments as amiEvaluate.
  * The sums over samples are reduced in a fixed order.  Served by the
- * specialized kernels (in one pass up to 128 terms, in passes up to 4096; see
- * the variants below; poles of higher order only there) or by the packed ones
+ * specialized kernels (in one pass up to 128 terms, above in blocks whose waves
+ * split the solution or in passes, up to 4096; see the variants below; poles
+ * of higher order only there) or by the packed ones
  * (every energy coefficient +-1, at most 255 distinct leaves and
  * denominators, at most 8 of each per term, no leaf twice in one term):
  * AMI_E_UNSUPPORTED when none applies.
  * out / out_sum (device, or NULL): the forward values, as amiEvaluate would
- * return them (up to rounding when the adjoint runs in passes), computed on
+ * return them (up to rounding when the adjoint does not run in one pass), computed on
  * the way -- a value-and-gradient pass when the cotangents do not depend on
  * the values (e.g. grad_sum for a Monte-Carlo estimate).
  */
@@ -396,11 +399,15 @@ AmiStatus amiIntegrateHubbard(AmiTerms *terms, int64_t n_samples, uint64_t seed,
  *   AMI_VARIANT_AUTO         (default) specialized when the solution has at
  *                            most 1024 flat terms (4096 in passes) and at
  *                            most 16 energies and its kernels compile -- the
- *                            forward in two passes (below) when the solution
- *                            has more than 1024 terms (up to 4096) or when its
- *                            groups and denominators would not fit the one-pass
- *                            kernel's registers (2 G + 4 D > 128), the adjoint
- *                            in passes (below) above 128 terms -- else
+ *                            forward in blocks whose waves split the solution
+ *                            of 64 samples when it has more than 1024 terms
+ *                            (up to 4096) or when its groups and denominators
+ *                            would not fit the one-pass kernel's registers
+ *                            (2 G + 4 D > 128), the adjoint in such blocks
+ *                            above 128 terms or where the one-pass kernel
+ *                            spills; both in passes (below) where a solution
+ *                            does not split or has poles of higher order --
+ *                            else
  *                            packed when the solution
  *                            has the packed form (+-1 coefficients, at most 255
  *                            leaves/denominators, 8 per term), else tables
@@ -466,8 +473,8 @@ AmiStatus amiSetTwoPassChunkBytes(int64_t bytes);
  * out of later evaluate calls.  Host-blocking.  AMI_E_UNSUPPORTED when the
  * solution is outside the specialized form, AMI_E_HIP when compiling or loading
  * fails (amiLastError holds the compiler log).  The kernels are the forward
- * (its two passes where AUTO takes them), the adjoint AUTO uses (one pass up
- * to 128 terms, its passes above), and for solutions of at most 1024 terms
+ * (its two passes and its block kernel where AUTO takes those), the adjoint
+ * AUTO uses (one pass, block kernel or passes), and for solutions of at most 1024 terms
  * the complex-energy forward and the kernels of its adjoint that AUTO uses
  * (amiEvaluateComplex, amiEvaluateComplexAdjoint) for the energy input, above
  * that the two passes of the complex-energy forward; all are compiled before a

@@ -118,13 +118,13 @@ struct AmiTerms {
     std::mutex dev_mu;
     std::vector<ami::DeviceTables> dev;      // uploaded copies
     // run-time specialized kernels: code objects per (input, kernel) -- index
-    // 6 * momentum + kernel (0 forward, 1 adjoint, 2 Monte-Carlo, 3 forward at
-    // complex energies, 4 and 5 the two passes of the two-pass forward) -- and
-    // the modules loaded from them, one per device
+    // kJitKinds * momentum + JitKind -- and the modules loaded from them, one per
+    // device
     std::mutex jit_mu;
     std::vector<char> jit_code[32];           // [2 inputs][kJitKinds]
     std::string jit_error[32];                // why a compilation failed (not retried)
-    int block_waves[3] = {-1, -1, -1};        // waves per block of the block adjoints: energies, momenta, complex energies (-1: not computed)
+    // waves per block of the block adjoints: energies, momenta, complex energies (-1: not computed)
+    int block_waves[3] = {-1, -1, -1};
     struct JitModule {
         int device = -1, kind = 0;
         void *module = nullptr, *fn = nullptr;

@@ -198,16 +198,15 @@ __global__ __launch_bounds__(kRedThreads) void ami_batch_colsum_kernel(const Col
 }
 
 // The items on their specialized kernels: each item's forward (as an AUTO
-// evaluate call launches it) recorded from up to four
-// streams -- items assigned largest first to the least loaded stream, so
-// small diagrams run side by side -- and, after they have joined, one launch
-// for the row sums of all of them, into a graph added to the batch graph as a
-// child node beside the persistent kernels.  (A graph node costs 7-8 us of
-// submission and more: eight diagrams of orders 2 to 5, 16 rows of 5 10^4 samples
-// each, took 130 us with a row-sum node each, 99 us with one.)  One eager run first sizes the
-// items' per-stream workspaces and loads their kernels, so the recorded
-// launches allocate nothing; the streams stay with the batch (its items'
-// workspaces are keyed by them).
+// evaluate call launches it) recorded from up to four streams -- items assigned
+// largest first to the least loaded stream, so small diagrams run side by side
+// -- and, after they have joined, one launch for the row sums of all of them,
+// into a graph added to the batch graph as a child node beside the persistent
+// kernels.  (A graph node costs 7-8 us of submission and more: eight diagrams of
+// orders 2 to 5, 16 rows of 5 10^4 samples each, took 130 us with a row-sum node
+// each, 99 us with one.)  One eager run first sizes the items' per-stream
+// workspaces and loads their kernels, so the recorded launches allocate nothing;
+// the streams stay with the batch (its items' workspaces are keyed by them).
 AmiStatus capture_specialized(AmiBatch *b, const AmiBatchItem *items, const std::vector<char> &spec, bool hub) {
     std::vector<int> ids;
     for (size_t i = 0; i < spec.size(); ++i)

@@ -701,9 +701,8 @@ AmiStatus launch_forward(AmiTerms *t, bool hub, KArgs &a, double *out_sum, hipSt
         if (out_sum && !sums) {
             AdjOut o;
             o.out_sum = out_sum;
-            if (finish_small(t, dt, stream, a, block_fwd ? kFinishBlockForward : kFinishOnePass, nblocks * parts, waves, 0,
-                             2 * a.n_f, o))
-                out_sum = nullptr;
+            const FinishLimits &lim = block_fwd ? kFinishBlockForward : kFinishOnePass;
+            if (finish_small(t, dt, stream, a, lim, nblocks * parts, waves, 0, 2 * a.n_f, o)) out_sum = nullptr;
         }
         if (block_fwd) e = launch_block(jit_fn, nblocks, waves, stream, a, parts);
         else e = launch_jit(jit_fn, nblocks, ls.block, stream, a, parts);

@@ -35,7 +35,8 @@
 // large solutions (64, 128), the adjoint at complex energies (256), the two
 // passes of the forward at complex energies (512, 1024), the frequency and
 // leaf passes of the adjoint at complex energies (2048, 4096), or a sum of
-// them
+// them, or, alone, the block adjoint (8192; at complex energies 16384) or the
+// block forward (32768)
 
 // Small calls (a.fin_cols > 0): the last block to arrive adds the partial sums of
 // all blocks, in the order of the reduction kernel that large calls launch (64

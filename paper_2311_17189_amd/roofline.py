@@ -11,14 +11,14 @@ sequence the kernels execute on gfx950, read from the AMD assembly of small
 kernels compiled here (FMA 2; add, mul, min/max, ldexp, rndne, rcp 1;
 compares and conversions 0):
 
-    sin and cos of one argument (both, reduced)      44
-    cos alone (reduced by pi)                        29
-    reduction of a momentum component mod 2 pi        8
-    e^z and e^z - 1 of one argument (both)           37
-    reciprocal (estimate + two Newton steps)          9
-    leaf f(y) with its mirror f(-y), Fermi / Bose    47 / 49
-    leaf derivative f'(y)                            48
-    leaf at a complex argument, Fermi / Bose        112 / 135
+    sin and cos of one argument (both, reduced)      35
+    cos alone (reduced by pi)                        24
+    reduction of a momentum component mod 2 pi        6
+    e^z and e^z - 1 of one argument (both)           34
+    reciprocal (estimate + one third-order step)      7
+    leaf f(y) with its mirror f(-y), Fermi / Bose    42 / 45
+    leaf derivative f'(y)                            43
+    leaf at a complex argument, Fermi / Bose         89 / 95
 
 Two models: ``forward_flops``/``adjoint_flops`` for the table-driven (packed)
 kernels and ``specialized_forward_flops``/``specialized_adjoint_flops`` for the
@@ -34,16 +34,16 @@ from dataclasses import dataclass
 
 import numpy as np
 
-C_SINCOS = 44
-C_COS = 29
-C_RED2PI = 8
-C_EXP = 37
-C_RCP = 9
-C_LEAF_FERMI = 47
-C_LEAF_BOSE = 49
-C_LEAF_DERIV = 48
-C_LEAF_C_FERMI = 112    # leaf at a complex argument (leaf_complex), Fermi / Bose-type
-C_LEAF_C_BOSE = 135
+C_SINCOS = 35
+C_COS = 24
+C_RED2PI = 6
+C_EXP = 34
+C_RCP = 7
+C_LEAF_FERMI = 42
+C_LEAF_BOSE = 45
+C_LEAF_DERIV = 43
+C_LEAF_C_FERMI = 89    # leaf at a complex argument (leaf_complex), Fermi / Bose-type
+C_LEAF_C_BOSE = 95
 
 PEAK_FP64_VECTOR = 78.6e12     # 256 CUs x 2.4 GHz x 128 FP64 FLOP/clk
 PEAK_HBM = 8.0e12              # bytes/s
