@@ -197,14 +197,27 @@ __global__ __launch_bounds__(kRedThreads) void ami_batch_colsum_kernel(const Col
     if (threadIdx.x == 0) *j.dst = r;
 }
 
+// Branches of the recorded items' graph.  Side by side the kernels of small
+// diagrams fill the chip, a third off the time of a chain, but every node of a
+// graph with branches takes 7-10 us of the host against 3.5 in a chain, and 20 us
+// more for the fork.  So a chain for little work in all or per item, two
+// branches up to 2 ms or so, then four.  Eight diagrams of orders 2 to 5 in one, two
+// and four branches: 1000 samples 38, 81 and 109 us; 5 10^4 samples, one row 42, 76
+// and 100, 16 rows 106, 88 and 104; 2 10^5 samples, 16 rows 250, 206 and 192.
+// work: the items' sample_cost times samples.
+int graph_branches(double work, size_t n_items) {
+    if (work < 1.1e9 || work < 1.2e8 * static_cast<double>(n_items)) return 1;
+    return work < 1e10 ? 2 : 4;
+}
+
 // The items on their specialized kernels: each item's forward (as an AUTO
 // evaluate call launches it) recorded from up to four streams -- items assigned
-// largest first to the least loaded stream, so small diagrams run side by side
-// -- and, after they have joined, one launch for the row sums of all of them,
-// into a graph added to the batch graph as a child node beside the persistent
-// kernels.  (A graph node costs 7-8 us of submission and more: eight diagrams of
-// orders 2 to 5, 16 rows of 5 10^4 samples each, took 130 us with a row-sum node
-// each, 99 us with one.)  One eager run first sizes the items' per-stream
+// largest first to the least loaded stream, the streams one after another or side
+// by side (graph_branches) -- and, after they have joined, one launch for the row
+// sums of all of them, into a graph added to the batch graph as a child node
+// beside the persistent kernels.  (Eight diagrams of orders 2 to 5, 16 rows of
+// 5 10^4 samples each, took 130 us with a row-sum node each on four branches, 99
+// us with one node for all.)  One eager run first sizes the items' per-stream
 // workspaces and loads their kernels, so the recorded launches allocate nothing;
 // the streams stay with the batch (its items' workspaces are keyed by them).
 AmiStatus capture_specialized(AmiBatch *b, const AmiBatchItem *items, const std::vector<char> &spec, bool hub) {
@@ -227,8 +240,9 @@ AmiStatus capture_specialized(AmiBatch *b, const AmiBatchItem *items, const std:
         load[k] += cost[i];
     }
     std::vector<RowSums> sums(spec.size());
-    auto launch_all = [&]() -> AmiStatus {
+    auto launch_all = [&](int stream) -> AmiStatus {    // the items of one stream, -1: of all
         for (int i : ids) {
+            if (stream >= 0 && stream_of[i] != stream) continue;
             const AmiBatchItem &it = items[i];
             KArgs a;
             std::memset(&a, 0, sizeof(a));
@@ -241,7 +255,7 @@ AmiStatus capture_specialized(AmiBatch *b, const AmiBatchItem *items, const std:
         }
         return AMI_OK;
     };
-    AmiStatus st = launch_all();   // eager: workspaces sized, kernels loaded
+    AmiStatus st = launch_all(-1);   // eager: workspaces sized, kernels loaded
     for (int k = 0; k < b->n_streams && st == AMI_OK; ++k) {
         const hipError_t e = hipStreamSynchronize(b->streams[k]);
         if (e != hipSuccess) st = hip_fail(e, "hipStreamSynchronize");
@@ -257,34 +271,42 @@ AmiStatus capture_specialized(AmiBatch *b, const AmiBatchItem *items, const std:
         e = hipMemcpy(b->spec_jobs, jobs.data(), sizeof(ColJob) * jobs.size(), hipMemcpyHostToDevice);
         if (e != hipSuccess) return hip_fail(e, "batch row sums");
     }
+    // stream k's launches follow those of stream k - branches; ev[k]: its end
+    double work = 0.0;
+    for (int i : ids) work += cost[i];
+    const int n = b->n_streams, branches = std::min(n, graph_branches(work, ids.size()));
     hipEvent_t ev[5] = {};
-    for (int k = 0; k <= b->n_streams; ++k) {
+    for (int k = 0; k <= n; ++k) {
         const hipError_t e = hipEventCreateWithFlags(&ev[k], hipEventDisableTiming);
         if (e != hipSuccess) {
             for (int j = 0; j < k; ++j) (void)hipEventDestroy(ev[j]);
             return hip_fail(e, "hipEventCreateWithFlags");
         }
     }
-    hipStream_t s0 = b->streams[0];
+    hipStream_t s0 = b->streams[0], last = b->streams[n - branches];   // last: the row sums'
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamBeginCapture(s0, hipStreamCaptureModeRelaxed);
     if (e == hipSuccess) {
-        e = hipEventRecord(ev[0], s0);                                  // fork
-        for (int k = 1; k < b->n_streams && e == hipSuccess; ++k) e = hipStreamWaitEvent(b->streams[k], ev[0], 0);
-        if (e == hipSuccess) st = launch_all();
-        for (int k = 1; k < b->n_streams && e == hipSuccess; ++k) {   // join
-            e = hipEventRecord(ev[k], b->streams[k]);
-            if (e == hipSuccess) e = hipStreamWaitEvent(s0, ev[k], 0);
+        e = hipEventRecord(ev[n], s0);                                  // fork
+        for (int k = 0; k < n && e == hipSuccess && st == AMI_OK; ++k) {
+            if (k > 0) e = hipStreamWaitEvent(b->streams[k], ev[k < branches ? n : k - branches], 0);
+            if (e == hipSuccess) st = launch_all(k);
+            if (e == hipSuccess) e = hipEventRecord(ev[k], b->streams[k]);
         }
+        for (int k = n - branches + 1; k < n && e == hipSuccess; ++k) e = hipStreamWaitEvent(last, ev[k], 0);   // join
         if (e == hipSuccess && st == AMI_OK && !jobs.empty()) {
-            hipLaunchKernelGGL(ami_batch_colsum_kernel, dim3(static_cast<unsigned>(jobs.size())), dim3(kRedThreads), 0, s0,
-                               static_cast<const ColJob *>(b->spec_jobs));
+            hipLaunchKernelGGL(ami_batch_colsum_kernel, dim3(static_cast<unsigned>(jobs.size())), dim3(kRedThreads), 0,
+                               last, static_cast<const ColJob *>(b->spec_jobs));
             e = hipGetLastError();
+        }
+        if (last != s0 && e == hipSuccess) {
+            e = hipEventRecord(ev[n], last);
+            if (e == hipSuccess) e = hipStreamWaitEvent(s0, ev[n], 0);
         }
         const hipError_t e2 = hipStreamEndCapture(s0, &g);                // always ends the capture
         if (e == hipSuccess) e = e2;
     }
-    for (int k = 0; k <= b->n_streams; ++k) (void)hipEventDestroy(ev[k]);
+    for (int k = 0; k <= n; ++k) (void)hipEventDestroy(ev[k]);
     if (e == hipSuccess && st == AMI_OK) {
         hipGraphNode_t node = nullptr;
         e = hipGraphAddChildGraphNode(&node, b->graph, nullptr, 0, g);
