@@ -68,7 +68,10 @@ struct DeviceTables {
         void *stream = nullptr;
         void *ptr = nullptr;
         size_t bytes = 0;
-        unsigned *ticket = nullptr;     // of calls whose last block adds the partial sums (zero between launches)
+        // the count of calls whose last block adds the partial sums, behind the first
+        // buffer; counting: set to zero, which it is between launches
+        unsigned *ticket = nullptr;
+        bool counting = false;
     };
     std::vector<Workspace> ws;
     std::vector<void *> retired;

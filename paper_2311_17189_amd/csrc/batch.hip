@@ -201,7 +201,7 @@ __global__ __launch_bounds__(kRedThreads) void ami_batch_colsum_kernel(const Col
 // diagrams fill the chip, a third off the time of a chain, but every node of a
 // graph with branches takes 7-10 us of the host against 3.5 in a chain, and 20 us
 // more for the fork.  So a chain for little work in all or per item, two
-// branches up to 2 ms or so, then four.  Eight diagrams of orders 2 to 5 in one, two
+// branches up to 0.2 ms or so, then four.  Eight diagrams of orders 2 to 5 in one, two
 // and four branches: 1000 samples 38, 81 and 109 us; 5 10^4 samples, one row 42, 76
 // and 100, 16 rows 106, 88 and 104; 2 10^5 samples, 16 rows 250, 206 and 192.
 // work: the items' sample_cost times samples.

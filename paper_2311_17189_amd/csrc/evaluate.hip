@@ -461,10 +461,11 @@ AmiStatus workspace(AmiTerms *t, DeviceTables *dt, hipStream_t stream, size_t by
         w->stream = static_cast<void *>(stream);
     }
     if (w->bytes < bytes) {
-        const size_t want = std::max(bytes, 2 * w->bytes);
+        const size_t want = align256(std::max(bytes, 2 * w->bytes));
         void *p = nullptr;
-        const hipError_t e = hipMalloc(&p, want);
+        const hipError_t e = hipMalloc(&p, want + (w->ptr ? 0 : 256));   // the first holds the ticket
         if (e != hipSuccess) return fail(AMI_E_OOM, std::string("workspace: ") + hipGetErrorString(e));
+        if (!w->ptr) w->ticket = reinterpret_cast<unsigned *>(static_cast<char *>(p) + want);
         if (w->ptr) dt->retired.push_back(w->ptr);     // a launch already queued may still read it
         w->ptr = p;
         w->bytes = want;
@@ -516,19 +517,13 @@ bool finish_small(AmiTerms *t, DeviceTables *dt, hipStream_t stream, KArgs &a, c
         DeviceTables::Workspace *w = nullptr;
         for (auto &x : dt->ws)
             if (x.stream == static_cast<void *>(stream)) w = &x;
-        if (!w) return false;
-        if (!w->ticket) {
-            void *p = nullptr;
-            if (hipMalloc(&p, 256) != hipSuccess) {
-                (void)hipGetLastError();
-                return false;
-            }
-            dt->retired.push_back(p);     // freed with the handle
-            if (fill(static_cast<double *>(p), 32, stream) != AMI_OK) {
+        if (!w || !w->ticket) return false;
+        if (!w->counting) {
+            if (fill(reinterpret_cast<double *>(w->ticket), 32, stream) != AMI_OK) {
                 clear_error();
                 return false;
             }
-            w->ticket = static_cast<unsigned *>(p);
+            w->counting = true;
         }
         a.fin_ticket = w->ticket;
     }
