@@ -1485,12 +1485,16 @@ AmiStatus amiTermsSpecialize(AmiTerms *t, int32_t momentum) {
         kinds.push_back(kJitForward);
     }
     if (t->tab.T <= kJitAutoAdjointTerms) kinds.push_back(kJitAdjoint);
-    if (t->tab.T > kJitAutoAdjointTerms && jit_adjoint_passes_supported(t, hub, nullptr)) {
+    // the adjoint in passes where AUTO takes it, or a variant was set (its kernels
+    // compile as long as the block adjoint's)
+    const bool block_adj = jit_prefers_block_adjoint(t) && jit_block_waves_of(t, hub) > 0;
+    if (t->tab.T > kJitAutoAdjointTerms && (!block_adj || t->variant != AMI_VARIANT_AUTO) &&
+        jit_adjoint_passes_supported(t, hub, nullptr)) {
         if (!jit_prefers_two_pass(t)) kinds.push_back(kJitSumsPass);
         kinds.push_back(kJitAdjFreq);
         kinds.push_back(kJitAdjLeaf);
     }
-    if (jit_prefers_block_adjoint(t) && jit_block_waves_of(t, hub) > 0) kinds.push_back(kJitBlockAdjoint);
+    if (block_adj) kinds.push_back(kJitBlockAdjoint);
     // the complex-energy kernels AUTO uses: forward in one pass up to 1024
     // terms, in two above; the adjoint in one pass up to 512 terms, in passes
     // above
