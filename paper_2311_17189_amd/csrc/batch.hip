@@ -170,6 +170,7 @@ struct AmiBatch {
     hipStream_t streams[4] = {};           // kept until the batch is freed (their workspaces)
     void *blob = nullptr;                  // descriptors, work list, jobs, counter, partial sums
     void *spec_jobs = nullptr;             // row sums of the items on their specialized kernels
+    void *spec_partial = nullptr;          // and the partial sums they add
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     std::vector<hipModule_t> modules;      // persistent specialized batch: its compiled groups
@@ -239,7 +240,23 @@ AmiStatus capture_specialized(AmiBatch *b, const AmiBatchItem *items, const std:
         stream_of[i] = k;
         load[k] += cost[i];
     }
+    // the partial sums of each item in a range of its own, since items of one
+    // handle on one stream share the handle's workspace and are added at the end
     std::vector<RowSums> sums(spec.size());
+    size_t n_partial = 0;
+    auto partials_of = [&](int i) {
+        return items[i].out_sum ? static_cast<size_t>(row_sum_rows(items[i].terms, hub, items[i].n_e)) * 2 *
+                                      static_cast<size_t>(items[i].n_f)
+                                : size_t(0);
+    };
+    for (int i : ids) n_partial += partials_of(i);
+    if (n_partial > 0 && hipMalloc(&b->spec_partial, sizeof(double) * n_partial) != hipSuccess)
+        return fail(AMI_E_OOM, "batch partial sums");
+    double *next = static_cast<double *>(b->spec_partial);
+    for (int i : ids) {
+        sums[i].partial = next;
+        next += partials_of(i);
+    }
     auto launch_all = [&](int stream) -> AmiStatus {    // the items of one stream, -1: of all
         for (int i : ids) {
             if (stream >= 0 && stream_of[i] != stream) continue;
@@ -321,6 +338,7 @@ AmiStatus batch_fail_free(AmiBatch *b, AmiStatus st) {
     if (b->graph) (void)hipGraphDestroy(b->graph);
     if (b->blob) (void)hipFree(b->blob);
     if (b->spec_jobs) (void)hipFree(b->spec_jobs);
+    if (b->spec_partial) (void)hipFree(b->spec_partial);
     for (hipModule_t m : b->modules) (void)hipModuleUnload(m);
     for (int k = 0; k < b->n_streams; ++k)
         if (b->streams[k]) (void)hipStreamDestroy(b->streams[k]);
@@ -1052,6 +1070,7 @@ void amiBatchFree(AmiBatch *b) {
     if (b->graph) (void)hipGraphDestroy(b->graph);
     if (b->blob) (void)hipFree(b->blob);
     if (b->spec_jobs) (void)hipFree(b->spec_jobs);
+    if (b->spec_partial) (void)hipFree(b->spec_partial);
     for (hipModule_t m : b->modules) (void)hipModuleUnload(m);
     for (int k = 0; k < b->n_streams; ++k)
         if (b->streams[k]) (void)hipStreamDestroy(b->streams[k]);

@@ -619,12 +619,12 @@ AmiStatus launch_two_pass(AmiTerms *t, DeviceTables *dt, bool hub, KArgs &a, dou
     ld = std::min<int64_t>(ld, int64_t(1) << 28);   // the kernels address a chunk with 32-bit byte offsets
     double *ws = nullptr;
     const int ncols = a.mc ? 4 * a.n_f : 2 * a.n_f;   // per-wave sums (Monte Carlo: with squares)
-    const size_t n_part = out_sum ? static_cast<size_t>(rows) * ncols : 0;
+    const size_t n_part = out_sum && !sums ? static_cast<size_t>(rows) * ncols : 0;
     AmiStatus st = workspace(t, dt, stream, (static_cast<size_t>(cols) * ld + n_part) * sizeof(double), &ws);
     if (st != AMI_OK) return st;
     a.work = ws;
     a.ld = ld;
-    a.partial = out_sum ? ws + static_cast<size_t>(cols) * ld : nullptr;
+    a.partial = sums ? sums->partial : out_sum ? ws + static_cast<size_t>(cols) * ld : nullptr;
     a.nrows = rows;
     // the largest chunk's frequency pass: a block per tile and frequency row
     if ((std::min<int64_t>(ld, a.n_e) + B - 1) / B * a.n_f + 7 * a.n_f > 0x7fffffffLL)
@@ -682,7 +682,9 @@ AmiStatus launch_forward(AmiTerms *t, bool hub, KArgs &a, double *out_sum, hipSt
     const int64_t rows = path == Path::SPECIALIZED ? nblocks * (ls.block / 64) : nblocks;
     double *partial = nullptr;
     hipError_t e;
-    if (out_sum) {
+    if (sums && path == Path::SPECIALIZED) {
+        partial = sums->partial;
+    } else if (out_sum) {
         st = workspace(t, dt, stream, static_cast<size_t>(rows) * a.n_f * 2 * sizeof(double), &partial);
         if (st != AMI_OK) return st;
     }
@@ -1041,6 +1043,11 @@ void set_common(KArgs &a, const double *ext_freqs, int64_t n_f, double beta, dou
 AmiStatus launch_forward_as(AmiTerms *t, bool hub, KArgs &a, double *out_sum, hipStream_t stream, int variant,
                             RowSums *sums) {
     return launch_forward(t, hub, a, out_sum, stream, variant, sums);
+}
+
+int64_t row_sum_rows(const AmiTerms *t, bool hub, int64_t n_e) {
+    const int B = jit_block(t, hub);      // the block forward's tiles of 64 samples are no more
+    return (n_e + B - 1) / B * (B / 64);
 }
 
 bool specialized_forward_ready(AmiTerms *t, bool hub, int n_f) {

@@ -59,16 +59,21 @@ PackedTabs packed_tabs(const AmiTerms *t, const DeviceTables *dt);
 int fwd_slots(const Tables &tb);
 
 // The per-wave partial sums of a forward whose row sums the caller reduces:
-// column c (of ncols) holds `rows` values at partial + c * rows.
+// column c (of ncols) holds `rows` values at partial + c * rows.  partial is the
+// caller's own device memory, at least row_sum_rows * 2 n_f doubles: the handle's
+// workspace holds another call's sums as soon as one follows on the stream.
 struct RowSums {
-    const double *partial = nullptr;
+    double *partial = nullptr;
     int64_t rows = 0;
     int ncols = 0;
 };
 
+// The most rows of partial sums a forward of n_e samples leaves per column.
+int64_t row_sum_rows(const AmiTerms *t, bool hub, int64_t n_e);
+
 // The forward of one handle as an evaluate call with the given variant
 // (AMI_VARIANT_*) would launch it on `stream`, row sums included; with `sums`
-// the specialized kernels' row sums are left to the caller.
+// (its partial set) the specialized kernels' row sums are left to the caller.
 AmiStatus launch_forward_as(AmiTerms *t, bool hub, KArgs &a, double *out_sum, hipStream_t stream, int variant,
                             RowSums *sums = nullptr);
 // Whether AUTO would run the specialized (one- or two-pass) forward of t for
