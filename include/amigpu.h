@@ -448,9 +448,10 @@ AmiStatus amiIntegrateHubbard(AmiTerms *terms, int64_t n_samples, uint64_t seed,
  * AMIGPU_JIT_NESTED_COTANGENTS (terms per part of the one-pass adjoints'
  * nested leaf-cotangent sweep, 0 for per-term products; by default both forms
  * are compiled and the one whose code object spills no more and keeps the
- * occupancy is kept), AMIGPU_JIT_CADJ_PART and AMIGPU_JIT_CADJL_WAVES (terms
+ * occupancy is kept), AMIGPU_JIT_CADJ_PART, AMIGPU_JIT_CADJL_WAVES (terms
  * per part and waves floor of the complex adjoint's leaf pass, defaults 64
- * and 1).
+ * and 1) and AMIGPU_JIT_BLOCK_WAVES (2, 4 or 8 waves per block of the block
+ * adjoints; read once per handle and input).
  */
 enum { AMI_VARIANT_AUTO = 0, AMI_VARIANT_TABLES = 1, AMI_VARIANT_PACKED = 2, AMI_VARIANT_SPECIALIZED = 3,
        AMI_VARIANT_TWO_PASS = 4 };

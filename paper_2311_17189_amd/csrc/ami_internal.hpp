@@ -126,8 +126,10 @@ struct AmiTerms {
     std::mutex jit_mu;
     std::vector<char> jit_code[32];           // [2 inputs][kJitKinds]
     std::string jit_error[32];                // why a compilation failed (not retried)
-    // waves per block of the block adjoints: energies, momenta, complex energies (-1: not computed)
-    int block_waves[3] = {-1, -1, -1};
+    // waves per block of the block adjoints: energies, momenta, complex energies
+    // (-1: not computed), under plan_mu
+    mutable std::mutex plan_mu;
+    mutable int block_waves[3] = {-1, -1, -1};
     struct JitModule {
         int device = -1, kind = 0;
         void *module = nullptr, *fn = nullptr;

@@ -12,6 +12,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <sstream>
 #include <string>
 #include <tuple>
@@ -606,7 +607,7 @@ int jit_block_forward_waves(const AmiTerms *t) {
 // energies, whose parts are twice as large: four (136 terms 78.7 and 65.8, 560
 // terms 168, 134 and with eight 172).  Eight, alone on its CU, where the columns
 // of four do not fit half its LDS.
-int jit_block_waves(const AmiTerms *t, bool hub, bool cplx) {
+static int choose_block_waves(const AmiTerms *t, bool hub, bool cplx) {
     for (int o : t->tab.leaf_order)
         if (o > 0) return 0;              // Taylor-coefficient leaves: the passes over a workspace
     if (t->tab.T > kJitTwoPassMaxTerms) return 0;
@@ -620,6 +621,13 @@ int jit_block_waves(const AmiTerms *t, bool hub, bool cplx) {
         if (p.waves > 0 && p.imbalance <= 1.6) return w;
     }
     return 0;
+}
+
+int jit_block_waves(const AmiTerms *t, bool hub, bool cplx) {
+    std::lock_guard<std::mutex> lock(t->plan_mu);
+    int &w = t->block_waves[cplx ? 2 : hub ? 1 : 0];
+    if (w < 0) w = choose_block_waves(t, hub, cplx);
+    return w;
 }
 
 namespace {

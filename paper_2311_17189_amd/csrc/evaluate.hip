@@ -372,7 +372,7 @@ AmiStatus choose_path(AmiTerms *t, bool hub, bool adjoint, Path &p, void **jit_f
         return fail(AMI_E_UNSUPPORTED, adjoint ? "the two-pass variant of the adjoint runs in passes only"
                                                : "the two-pass variant takes at most 65535 frequency rows");
     if (adjoint && jit_fn3 && v == AMI_VARIANT_AUTO && jit_prefers_block_adjoint(t) &&
-        jit_block_waves_of(t, hub) > 0) {
+        jit_block_waves(t, hub) > 0) {
         const AmiStatus st = get(kJitBlockAdjoint, jit_fn);
         if (st == AMI_OK) {
             p = Path::ADJ_BLOCK;
@@ -884,7 +884,7 @@ AmiStatus launch_adjoint_block(AmiTerms *t, DeviceTables *dt, bool hub, KArgs &a
     a.gpartial = ws;
     a.partial = o.out_sum ? ws + static_cast<size_t>(rows) * ncols : nullptr;
     a.nrows = rows;
-    const int waves = jit_block_waves_of(t, hub, cplx);
+    const int waves = jit_block_waves(t, hub, cplx);
     const bool fin = !fixed_ws && finish_small(t, dt, stream, a, kFinishBlockAdjoint, rows, waves, ncols, nval, o);
     hipError_t e = launch_block(fn, rows, waves, stream, a);
     if (e == hipSuccess) e = hipGetLastError();
@@ -1215,7 +1215,7 @@ AmiStatus amiEvaluateComplexAdjoint(AmiTerms *t, const double *energies, int64_t
     // AUTO: the block adjoint where the solution splits over the waves of a block
     if (t->variant == AMI_VARIANT_AUTO && n_e > 0 &&
         t->tab.T > (n_f == 1 ? kJitAutoComplexBlockTermsOneRow : kJitAutoComplexBlockTerms) &&
-        jit_block_waves_of(t, false, true) > 0) {
+        jit_block_waves(t, false, true) > 0) {
         void *fb = nullptr;
         st = jit_get(t, false, kJitComplexBlockAdjoint, &fb);
         if (st == AMI_OK) return launch_adjoint_block(t, dt, false, ba, bo, fb, stream, nullptr, true);
@@ -1494,7 +1494,7 @@ AmiStatus amiTermsSpecialize(AmiTerms *t, int32_t momentum) {
     if (t->tab.T <= kJitAutoAdjointTerms) kinds.push_back(kJitAdjoint);
     // the adjoint in passes where AUTO takes it, or a variant was set (its kernels
     // compile as long as the block adjoint's)
-    const bool block_adj = jit_prefers_block_adjoint(t) && jit_block_waves_of(t, hub) > 0;
+    const bool block_adj = jit_prefers_block_adjoint(t) && jit_block_waves(t, hub) > 0;
     if (t->tab.T > kJitAutoAdjointTerms && (!block_adj || t->variant != AMI_VARIANT_AUTO) &&
         jit_adjoint_passes_supported(t, hub, nullptr)) {
         if (!jit_prefers_two_pass(t)) kinds.push_back(kJitSumsPass);
@@ -1512,7 +1512,7 @@ AmiStatus amiTermsSpecialize(AmiTerms *t, int32_t momentum) {
             kinds.push_back(kJitComplexSums);
             kinds.push_back(kJitComplexFreq);
         }
-        const bool block = jit_block_waves_of(t, false, true) > 0;
+        const bool block = jit_block_waves(t, false, true) > 0;
         if (block && t->tab.T > kJitAutoComplexBlockTermsOneRow) kinds.push_back(kJitComplexBlockAdjoint);
         if (block && t->tab.T > kJitAutoComplexBlockTerms) {
             // for any number of rows

@@ -250,13 +250,6 @@ AmiStatus code_from_source(const std::string &src, std::vector<char> &code, std:
     return AMI_OK;
 }
 
-int jit_block_waves_of(AmiTerms *t, bool hub, bool cplx) {
-    std::lock_guard<std::mutex> lock(t->jit_mu);
-    int &w = t->block_waves[cplx ? 2 : hub ? 1 : 0];
-    if (w < 0) w = jit_block_waves(t, hub, cplx);
-    return w;
-}
-
 AmiStatus jit_compile(AmiTerms *t, bool hub, int kind) {
     if (kind < kJitForward || kind >= kJitKinds || (kind == kJitMonteCarlo && !hub) ||
         (jit_kind_complex(kind) && hub))

@@ -47,10 +47,10 @@ bool jit_adjoint_passes_supported(const AmiTerms *t, bool hub, std::string *why)
 
 // Waves per block of the block adjoint for this input, 0 when the solution has
 // none (Taylor-coefficient leaves, too few groups to split evenly, or more
-// columns than the LDS of a CU holds).  jit_block_waves computes it;
-// jit_block_waves_of keeps it with the handle.
-int jit_block_waves(const AmiTerms *t, bool hub, bool cplx);
-int jit_block_waves_of(AmiTerms *t, bool hub, bool cplx = false);
+// columns than the LDS of a CU holds).  Chosen once per handle and input: the
+// source and every launch of a handle take the same count, whatever becomes of the
+// environment's override in between.
+int jit_block_waves(const AmiTerms *t, bool hub, bool cplx = false);
 int jit_block_forward_waves(const AmiTerms *t);   // of the block forward, 0: none
 
 // Whether the diagram can be specialized for the energy (hub = false) or
