@@ -1478,9 +1478,10 @@ __device__ __forceinline__ void badj_wave(const KArgs &a, int64_t tile, double *
 
     double gmu = 0.0, gt = 0.0;
     const int64_t n_rows = a.n_e - s0 < 64 ? a.n_e - s0 : 64;
-    // the staged gradient rows lie over the first columns (energies, a row's
-    // sums), which nothing reads any more: one column more than a row's length
-    static_assert(kBE == 0 && (HUB ? 2 * NI : NE) + 1 <= kBlockCols && (HUB || NE + 1 <= kBU), "staging area");
+    // the staged gradient rows (one column more than a row's length) lie over the
+    // first columns, which nothing reads any more: energies and a row's sums, and
+    // for momenta the energies' cotangents too, up to beta's at kBU + NE NW
+    static_assert(kBE == 0 && (HUB ? 2 * NI + 1 <= kBU + NE * NW : NE + 1 <= kBU), "staging area");
     double *const stage = sm;
     if constexpr (HUB) {
         blk_energy_grads<HUB, WV>(a, sc, lane, col, nullptr, gmu, gt);
