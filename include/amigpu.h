@@ -302,7 +302,7 @@ AmiStatus amiEvaluateComplexAdjoint(AmiTerms *terms,
  * denominators, at most 8 of each per term, no leaf twice in one term):
  * AMI_E_UNSUPPORTED when none applies.
  * out / out_sum (device, or NULL): the forward values, as amiEvaluate would
- * return them (up to rounding when the adjoint does not run in one pass), computed on
+ * return them (up to rounding above 128 terms), computed on
  * the way -- a value-and-gradient pass when the cotangents do not depend on
  * the values (e.g. grad_sum for a Monte-Carlo estimate).
  */

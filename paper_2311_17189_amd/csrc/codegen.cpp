@@ -449,6 +449,9 @@ struct BlockPlan {
     std::vector<int> first;
     int max_groups = 0;
     double imbalance = 1.0;               // largest wave's cost over the mean
+    // the wave that forms every value whole, as the forward does (-1: each wave
+    // its groups' part, added up at the end of a row)
+    int value_wave = -1;
     // reduction of the leaf cotangents over the waves, in rounds: round r holds
     // the leaves [round[r], round[r + 1]); slot[l][w] is wave w's column of leaf l
     // in its round (-1: the wave does not read the leaf)
@@ -530,6 +533,25 @@ BlockPlan block_plan(const AmiTerms *t, bool hub, bool cplx, int waves) {
         p.max_groups = std::max(p.max_groups, p.first[w + 1] - p.first[w]);
     }
     p.imbalance = most * waves / total;
+    // Real solutions whose forward adds the values group by group (up to the
+    // one-pass adjoint's automatic size): the values are the forward's bit for bit,
+    // formed by one wave from every group's sum in its column (its own groups'
+    // products it has anyway), the wave with the least work of its own.  76 terms, a
+    // step of 2 10^5 momenta: 39.0 us with the values added up from the waves'
+    // parts, 39.7 this way (four rows 59.0 and 60.4).
+    const bool exact = !cplx && tb.T <= kJitAutoAdjointTerms;
+    if (exact) {
+        if (p.max_groups > kBlockRegisterGroups) return p;
+        double least = total;
+        for (int w = 0; w < waves; ++w) {
+            double c = 0.0;
+            for (int g = p.first[w]; g < p.first[w + 1]; ++g) c += cost[g];
+            if (c < least) {
+                least = c;
+                p.value_wave = w;
+            }
+        }
+    }
     // Two blocks per CU hide each other's barriers and start, so four waves in
     // half the LDS where the solution fits there, else eight in all of it.
     // Columns that are optional, in the order of what they save: the group sums
@@ -538,7 +560,7 @@ BlockPlan block_plan(const AmiTerms *t, bool hub, bool cplx, int waves) {
     bool fits = false;
     for (int option = 3; option >= 0 && !fits; --option) {
         const bool group = option & 2, slope = option & 1;
-        if (!group && p.max_groups > kBlockRegisterGroups) continue;
+        if (!group && (exact || p.max_groups > kBlockRegisterGroups)) continue;
         p.c_e = 0;
         p.c_acc = cw * ne;
         p.c_slope = slope ? p.c_acc + (2 + 2 * nx) * waves : -1;
@@ -1382,6 +1404,7 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
     if (kernels & (8192 | 16384)) {
         o << "constexpr int NW = " << bp.waves << ", GW = " << bp.max_groups << ", kRounds = " << bp.round.size() - 1
           << ", kBlockCols = " << bp.columns << ";\n";
+        if (!blk_cplx) o << "constexpr int kValueWave = " << bp.value_wave << ";\n";
         o << "constexpr int kBE = " << bp.c_e << ", kBS = " << bp.c_slope << ", kBU = " << bp.c_union << ", kBF = "
           << bp.c_leaf << ", kBT = " << bp.c_group << ", kBA = " << bp.c_acc << ";\n";
         o << "__device__ __forceinline__ void blk_rho(double dr, double di, double &xr, double &xi) {\n"
@@ -1394,7 +1417,10 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
         // it at [64 c]).
         const int W = bp.waves;
         const bool group_cols = bp.c_group >= 0, slope_cols = bp.c_slope >= 0;
-        // group g's sum (before the leaf sweep) or cotangent (in it) of wave w
+        // the group sums' columns serve the cotangents too, unless the value
+        // wave may still read them
+        const bool exact = bp.value_wave >= 0, keep_cols = group_cols && !exact;
+        // group g's sum of wave w
         auto gsum = [&](int w, int g, const char *reg) {
             return group_cols ? "sT[" + std::to_string(64 * g) + "]" : idx(reg, g - bp.first[w]);
         };
@@ -1421,6 +1447,19 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
                 o << "    " << gsum(w, g, "ft") << " = " << href_expr(v, fname) << "; }\n";
             }
         });
+        if (exact)
+            for (int k = 0; k < tb.D; ++k) {
+                Lin re, im;
+                for (int i = 0; i < ne; ++i) re.add(tb.den_coef[static_cast<size_t>(k) * nc + i], idx("E", i));
+                for (int x = 0; x < nx; ++x) {
+                    const double a = tb.den_coef[static_cast<size_t>(k) * nc + ne + x];
+                    re.add(a, idx("wr", x));
+                    im.add(a, idx("wi", x));
+                }
+                o << "__device__ __forceinline__ void blk_den" << k << "(const double (&E)[NE], const double (&wr)[" << NXA
+                  << "], const double (&wi)[" << NXA << "], double &xr, double &xi) {\n  blk_rho(" << re.str() << ", "
+                  << im.str() << ", xr, xi);\n}\n";
+            }
         // one frequency row of the wave's groups: the reciprocals of their
         // denominators, R_g, the value's part sum FT_g R_g, FTB_g +=
         // Re(conj(c) R_g), and per denominator -conj(c) rho_k sum FT_g R_g,
@@ -1432,10 +1471,23 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
                     "double &acc_im, double (&gE)[NE], double (&gwr)[" + NXA + "], double (&gwi)[" + NXA + "]",
                 true, [&](int w) {
             const std::vector<int> ks = dens_of(w);
+            const bool all = w == bp.value_wave;      // the other waves' groups too, for the values
             // the columns through an empty asm: the sums are read here, not
             // held in registers since they were written
             o << "    AMI_OPAQUE(sT); (void)ft; (void)ftb;\n    double E[NE];\n#pragma unroll\n    for (int i = 0; i < NE; ++i) E[i] = sE[64 * i];\n";
+            if (exact) {
+                // the forward's reciprocals, formed outside this function's contraction
+                if (all)
+                    for (int k = 0; k < tb.D; ++k)
+                        if (!std::binary_search(ks.begin(), ks.end(), k))
+                            o << "    double xr" << k << ", xi" << k << ";\n    blk_den" << k << "(E, wr, wi, xr" << k
+                              << ", xi" << k << ");\n";
+                for (int k : ks)
+                    o << "    double xr" << k << ", xi" << k << ", Ur" << k << " = 0.0, Ui" << k << " = 0.0;\n    blk_den"
+                      << k << "(E, wr, wi, xr" << k << ", xi" << k << ");\n";
+            }
             for (int k : ks) {
+                if (exact) break;
                 Lin re, im;
                 for (int i = 0; i < ne; ++i) re.add(tb.den_coef[static_cast<size_t>(k) * nc + i], idx("E", i));
                 for (int x = 0; x < nx; ++x) {
@@ -1446,7 +1498,8 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
                 o << "    double xr" << k << ", xi" << k << ", Ur" << k << " = 0.0, Ui" << k << " = 0.0;\n    blk_rho("
                   << re.str() << ", " << im.str() << ", xr" << k << ", xi" << k << ");\n";
             }
-            for (int g = bp.first[w]; g < bp.first[w + 1]; ++g) {
+            for (int g = all ? 0 : bp.first[w]; g < (all ? G : bp.first[w + 1]); ++g) {
+                const bool own = g >= bp.first[w] && g < bp.first[w + 1];
                 const std::string j0 = std::to_string(g - bp.first[w]);
                 o << "    { double rr = 1.0, ri = 0.0, nr = 0.0;\n";
                 for (int j = gbegin(g); j < gend(g); ++j) {
@@ -1456,10 +1509,18 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
                         o << "      nr = fma(rr, xr" << k << ", -ri * xi" << k << "); ri = fma(rr, xi" << k << ", ri * xr"
                           << k << "); rr = nr;\n";
                 }
+                if (all)
+                    o << "      acc_re = fma(sT[" << 64 * g << "], rr, acc_re); acc_im = fma(sT[" << 64 * g
+                      << "], ri, acc_im);\n";
+                if (!own) {
+                    o << "      (void)nr;\n    }\n";
+                    continue;
+                }
                 o << "      (void)nr;\n      const double t = " << gsum(w, g, "ft")
                   << ", qr = t * rr, qi = t * ri, tb = fma(cr, rr, ci * ri);\n";
-                if (group_cols) o << "      if constexpr (ONE) sT[" << 64 * g << "] = tb;\n      else ";
-                o << "ftb[" << j0 << "] += tb;\n      acc_re += qr; acc_im += qi;\n";
+                if (keep_cols) o << "      if constexpr (ONE) sT[" << 64 * g << "] = tb;\n      else ";
+                o << "ftb[" << j0 << "] += tb;\n";
+                if (!exact) o << "      acc_re += qr; acc_im += qi;\n";
                 for (int j = gbegin(g); j < gend(g); ++j) {
                     const std::string k = std::to_string(tb.group_den_list[j]);
                     o << "      Ur" << k << " += qr; Ui" << k << " += qi;\n";
@@ -1488,7 +1549,7 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
         });
         // leaf cotangents of the wave's groups by the reverse sweep of each
         // group's nested sum, in parts of at most kBlockPartTerms terms
-        if (group_cols)
+        if (keep_cols)
             wave_fn("blk_keep", "ami::lds sT, const double (&ftb)[GW]", false, [&](int w) {
                 for (int g = bp.first[w]; g < bp.first[w + 1]; ++g)
                     o << "    sT[" << 64 * g << "] = ftb[" << g - bp.first[w] << "];\n";
@@ -1513,7 +1574,7 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
                         else if (r.kind == HRef::LEAF)
                             o << "    FB[" << r.idx << "]" << (r.neg ? " -= " : " += ") << c << ";\n";
                     };
-                    pass(root, gsum(w, g, "ftb"));
+                    pass(root, keep_cols ? gsum(w, g, "ftb") : idx("ftb", g - bp.first[w]));
                     for (size_t kk = nn; kk-- > 0;) {
                         const HNode &n = nodes[kk];
                         const std::string hb = "hb" + std::to_string(kk), fa = fname(n.a),

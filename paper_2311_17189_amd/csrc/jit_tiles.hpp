@@ -1393,11 +1393,20 @@ __device__ __forceinline__ void badj_wave(const KArgs &a, int64_t tile, double *
 #pragma unroll
     for (int i = 0; i < NE; ++i) gE[i] = 0.0;
     blk_sums<WV>(col + 64 * kBF, col + 64 * kBT, ft);
+    if constexpr (kValueWave >= 0) __syncthreads();  // the value wave reads every group's sum
 
     double *gp = a.gpartial + tile;                  // column c at gp[c * nrows]
-    // a row's values and sums from the waves' parts
+    // a row's values and sums from the waves' parts (the values from the value
+    // wave's alone, if there is one)
     auto finish_row = [&](int f) __attribute__((always_inline)) {
-                    const double re = blk_wave_total(col, kBA), im = blk_wave_total(col, kBA + NW);
+                    double re, im;
+                    if constexpr (kValueWave >= 0) {
+                        re = col[64 * (kBA + kValueWave)];
+                        im = col[64 * (kBA + NW + kValueWave)];
+                    } else {
+                        re = blk_wave_total(col, kBA);
+                        im = blk_wave_total(col, kBA + NW);
+                    }
                     if (active && a.out) {
                         double2 v;
                         v.x = re;
