@@ -126,6 +126,9 @@ struct AmiTerms {
     std::mutex jit_mu;
     std::vector<char> jit_code[32];           // [2 inputs][kJitKinds]
     std::string jit_error[32];                // why a compilation failed (not retried)
+    // nodes of each group's nested sum (group_nest_sizes)
+    mutable std::once_flag nest_once;
+    mutable std::vector<int> nest_sizes;
     // waves per block of the block adjoints: energies, momenta, complex energies
     // (-1: not computed), under plan_mu
     mutable std::mutex plan_mu;

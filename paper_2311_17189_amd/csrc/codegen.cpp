@@ -16,6 +16,7 @@
 #include <sstream>
 #include <string>
 #include <tuple>
+#include <unordered_map>
 #include <vector>
 
 #include "ami_internal.hpp"
@@ -53,17 +54,24 @@ std::string num(double v) {
 // and a sub-sum met again (or its negative) reuses the node that holds it.
 // The nodes are built first (horner_build), then written out (horner_emit:
 // const double h<k> of the enclosing block).
+// Nesting is most of what generating a large solution's source costs (2804 terms:
+// ordered maps of printed keys, merging anew at every step, took 12 ms for all
+// group sums, this form 2), so leaf lists are u16strings (up to seven
+// leaves without an allocation) and the keys of sub-sums their bits.
 struct HornerTerm {
     double c;
-    std::vector<int> leaves;   // a multiset (a leaf may repeat)
+    std::u16string leaves;   // a multiset (a leaf may repeat)
 };
+
+bool leaves_less(const HornerTerm &x, const HornerTerm &y) { return x.leaves < y.leaves; }
 
 // The terms with their leaf multisets sorted, equal multisets merged and
 // zero coefficients dropped.
 std::vector<HornerTerm> merged_terms(std::vector<HornerTerm> ts) {
     for (HornerTerm &t : ts) std::sort(t.leaves.begin(), t.leaves.end());
-    std::sort(ts.begin(), ts.end(), [](const HornerTerm &x, const HornerTerm &y) { return x.leaves < y.leaves; });
+    std::sort(ts.begin(), ts.end(), leaves_less);
     std::vector<HornerTerm> m;
+    m.reserve(ts.size());
     for (HornerTerm &t : ts) {
         if (!m.empty() && m.back().leaves == t.leaves) m.back().c += t.c;
         else m.push_back(std::move(t));
@@ -73,41 +81,63 @@ std::vector<HornerTerm> merged_terms(std::vector<HornerTerm> ts) {
 }
 
 // The merged sum's key up to sign (`flip`: its first coefficient is negative
-// and the key is that of the negated sum).
-std::string sum_key(const std::vector<HornerTerm> &m, bool &flip) {
+// and the key is that of the negated sum): every coefficient's bits, the number
+// of leaves and the leaves.
+std::u16string sum_key(const std::vector<HornerTerm> &m, bool &flip) {
     flip = m[0].c < 0.0;
-    std::string key;
+    std::u16string key;
+    key.reserve(m.size() * (5 + m[0].leaves.size()));
     for (const HornerTerm &t : m) {
-        key += num(flip ? -t.c : t.c) + ":";
-        for (int l : t.leaves) key += std::to_string(l) + ",";
-        key += ";";
+        const double c = flip ? -t.c : t.c;
+        char16_t bits[4];
+        std::memcpy(bits, &c, sizeof(c));
+        key.append(bits, 4);
+        key.push_back(static_cast<char16_t>(t.leaves.size()));
+        key += t.leaves;
     }
     return key;
 }
 
-// One step of the nesting: the leaf in the most terms (the lowest index among
-// equals) and the terms split into those holding it (one occurrence removed)
-// and the others.
-int split_on_shared_leaf(std::vector<HornerTerm> m, std::vector<HornerTerm> &with, std::vector<HornerTerm> &without) {
-    std::map<int, int> count;   // terms holding each leaf
-    for (const HornerTerm &t : m)
-        for (size_t j = 0; j < t.leaves.size(); ++j)
-            if (j == 0 || t.leaves[j] != t.leaves[j - 1]) ++count[t.leaves[j]];
+// The sub-sums of one nesting met so far (up to sign), and its counts per leaf
+// (zero between uses).
+template <typename Value>
+struct NestMemo {
+    std::unordered_map<std::u16string, Value> found;
+    std::vector<int> count;
+};
+
+// One step of the nesting of merged terms: the leaf in the most terms (the lowest
+// index among equals) and the terms split into those holding it (one occurrence
+// removed, sorted again) and the others.  Both parts are merged: terms that
+// differ still differ without one leaf.
+int split_on_shared_leaf(std::vector<HornerTerm> m, std::vector<int> &count, std::vector<HornerTerm> &with,
+                         std::vector<HornerTerm> &without) {
     int a = -1, best = 0;
-    for (const auto &kv : count)
-        if (kv.second > best) {
-            a = kv.first;
-            best = kv.second;
+    for (const HornerTerm &t : m)
+        for (size_t j = 0; j < t.leaves.size(); ++j) {
+            if (j > 0 && t.leaves[j] == t.leaves[j - 1]) continue;
+            const int l = t.leaves[j];
+            if (static_cast<size_t>(l) >= count.size()) count.resize(static_cast<size_t>(l) + 1, 0);
+            const int n = ++count[l];               // terms holding l
+            if (n > best || (n == best && l < a)) {
+                a = l;
+                best = n;
+            }
         }
+    for (HornerTerm &t : m)
+        for (char16_t l : t.leaves) count[l] = 0;
+    with.reserve(static_cast<size_t>(best));
+    without.reserve(m.size() - static_cast<size_t>(best));
     for (HornerTerm &t : m) {
-        auto it = std::find(t.leaves.begin(), t.leaves.end(), a);
-        if (it == t.leaves.end()) {
+        const size_t at = t.leaves.find(static_cast<char16_t>(a));
+        if (at == std::u16string::npos) {
             without.push_back(std::move(t));
         } else {
-            t.leaves.erase(it);
+            t.leaves.erase(at, 1);
             with.push_back(std::move(t));
         }
     }
+    std::sort(with.begin(), with.end(), leaves_less);
     return a;
 }
 
@@ -131,11 +161,8 @@ HRef href_negated(HRef r) {
     return r;
 }
 
-// Sub-sums already built (up to sign) for the current nesting.
-using HMemo = std::map<std::string, HRef>;
-
-HRef horner_nodes(std::vector<HornerTerm> ts, std::vector<HNode> &nodes, HMemo &memo) {
-    std::vector<HornerTerm> m = merged_terms(std::move(ts));
+// The nodes of the merged terms m.
+HRef horner_nodes(std::vector<HornerTerm> m, std::vector<HNode> &nodes, NestMemo<HRef> &memo) {
     HRef r;
     if (m.empty()) return r;
     if (m.size() == 1 && m[0].leaves.empty()) {
@@ -144,12 +171,13 @@ HRef horner_nodes(std::vector<HornerTerm> ts, std::vector<HNode> &nodes, HMemo &
         return r;
     }
     bool flip;
-    const std::string key = sum_key(m, flip);
-    if (const auto it = memo.find(key); it != memo.end()) return flip ? href_negated(it->second) : it->second;
+    std::u16string key = sum_key(m, flip);
+    if (const auto it = memo.found.find(key); it != memo.found.end())
+        return flip ? href_negated(it->second) : it->second;
     std::vector<HornerTerm> with, without;
-    const int a = split_on_shared_leaf(std::move(m), with, without);
-    const HRef w = horner_nodes(with, nodes, memo);
-    const HRef u = horner_nodes(without, nodes, memo);
+    const int a = split_on_shared_leaf(std::move(m), memo.count, with, without);
+    const HRef w = horner_nodes(std::move(with), nodes, memo);
+    const HRef u = horner_nodes(std::move(without), nodes, memo);
     if (w.kind == HRef::ZERO) {
         r = u;
     } else if (w.kind == HRef::CONST && (w.c == 1.0 || w.c == -1.0) && u.kind == HRef::ZERO) {
@@ -161,14 +189,14 @@ HRef horner_nodes(std::vector<HornerTerm> ts, std::vector<HNode> &nodes, HMemo &
         r.kind = HRef::NODE;
         r.idx = static_cast<int>(nodes.size()) - 1;
     }
-    memo[key] = flip ? href_negated(r) : r;
+    memo.found.emplace(std::move(key), flip ? href_negated(r) : r);
     return r;
 }
 
 // The nesting of sum_t c_t prod F over the given terms: its nodes and value.
 HRef horner_build(std::vector<HornerTerm> ts, std::vector<HNode> &nodes) {
-    HMemo memo;
-    return horner_nodes(std::move(ts), nodes, memo);
+    NestMemo<HRef> memo;
+    return horner_nodes(merged_terms(std::move(ts)), nodes, memo);
 }
 
 template <typename LeafName>
@@ -240,12 +268,12 @@ std::string fused(const std::vector<std::tuple<bool, std::string, std::string>> 
     return acc;
 }
 
-using CMemo = std::map<std::string, CVal>;
+using CMemo = NestMemo<CVal>;
 
-// leaf(a) gives the value of factor a (a REAL or CPLX CVal of names)
+// leaf(a) gives the value of factor a (a REAL or CPLX CVal of names); the terms
+// m are merged
 template <typename Leaf>
-CVal horner_c(std::vector<HornerTerm> ts, const Leaf &leaf, std::ostream &o, int &temps, CMemo &memo) {
-    std::vector<HornerTerm> m = merged_terms(std::move(ts));
+CVal horner_c_merged(std::vector<HornerTerm> m, const Leaf &leaf, std::ostream &o, int &temps, CMemo &memo) {
     CVal r;
     if (m.empty()) return r;
     if (m.size() == 1 && m[0].leaves.empty()) {
@@ -254,12 +282,12 @@ CVal horner_c(std::vector<HornerTerm> ts, const Leaf &leaf, std::ostream &o, int
         return r;
     }
     bool flip;
-    const std::string key = sum_key(m, flip);
-    if (const auto it = memo.find(key); it != memo.end()) return flip ? cnegated(it->second) : it->second;
+    std::u16string key = sum_key(m, flip);
+    if (const auto it = memo.found.find(key); it != memo.found.end()) return flip ? cnegated(it->second) : it->second;
     std::vector<HornerTerm> with, without;
-    const int a = split_on_shared_leaf(std::move(m), with, without);
-    const CVal w = horner_c(with, leaf, o, temps, memo);
-    const CVal u = horner_c(without, leaf, o, temps, memo);
+    const int a = split_on_shared_leaf(std::move(m), memo.count, with, without);
+    const CVal w = horner_c_merged(std::move(with), leaf, o, temps, memo);
+    const CVal u = horner_c_merged(std::move(without), leaf, o, temps, memo);
     const CVal L = leaf(a);
     if (w.kind == CVal::ZERO) {
         r = u;
@@ -320,8 +348,13 @@ CVal horner_c(std::vector<HornerTerm> ts, const Leaf &leaf, std::ostream &o, int
         r.re = temp(ere);
         if (cplx) r.im = temp(eim);
     }
-    memo[key] = flip ? cnegated(r) : r;
+    memo.found.emplace(std::move(key), flip ? cnegated(r) : r);
     return r;
+}
+
+template <typename Leaf>
+CVal horner_c(std::vector<HornerTerm> ts, const Leaf &leaf, std::ostream &o, int &temps, CMemo &memo) {
+    return horner_c_merged(merged_terms(std::move(ts)), leaf, o, temps, memo);
 }
 
 // sum_i c_i v[i] over the non-zero coefficients, in index order: "+-v" for
@@ -503,6 +536,27 @@ bool split_groups(const std::vector<double> &cost, int waves, std::vector<int> &
     return ranges(hi, out);
 }
 
+// Nodes of each group's nested sum, what its share of a wave's work is judged by;
+// counted once per handle (every plan and every block kernel's source asks).
+const std::vector<int> &group_nest_sizes(const AmiTerms *t) {
+    std::call_once(t->nest_once, [t] {
+        const Tables &tb = t->tab;
+        for (int g = 0; g < tb.G; ++g) {
+            std::vector<HornerTerm> ts;
+            for (int ti = tb.group_start[g]; ti < tb.group_start[g + 1]; ++ti) {
+                HornerTerm h{tb.term_sign[ti], {}};
+                for (int j = 0; j < t->n_int; ++j)
+                    h.leaves.push_back(tb.term_leaf[static_cast<size_t>(ti) * t->n_int + j]);
+                ts.push_back(std::move(h));
+            }
+            std::vector<HNode> nodes;
+            horner_build(std::move(ts), nodes);
+            t->nest_sizes.push_back(static_cast<int>(nodes.size()));
+        }
+    });
+    return t->nest_sizes;
+}
+
 BlockPlan block_plan(const AmiTerms *t, bool hub, bool cplx, int waves) {
     const Tables &tb = t->tab;
     const int G = tb.G, L = tb.L, ni = t->n_int, ne = t->n_eps, nx = t->n_ext;
@@ -511,17 +565,10 @@ BlockPlan block_plan(const AmiTerms *t, bool hub, bool cplx, int waves) {
     if (waves < 2 || G < waves) return p;
     std::vector<double> cost(static_cast<size_t>(G));
     double total = 0.0;
+    const std::vector<int> &nest_sizes = group_nest_sizes(t);
     for (int g = 0; g < G; ++g) {
-        std::vector<HornerTerm> ts;
-        for (int ti = tb.group_start[g]; ti < tb.group_start[g + 1]; ++ti) {
-            HornerTerm h{tb.term_sign[ti], {}};
-            for (int j = 0; j < ni; ++j) h.leaves.push_back(tb.term_leaf[static_cast<size_t>(ti) * ni + j]);
-            ts.push_back(std::move(h));
-        }
-        std::vector<HNode> nodes;
-        horner_build(std::move(ts), nodes);
         const int dens = tb.group_den_start[g + 1] - tb.group_den_start[g];
-        cost[g] = 3.6 * (cplx ? 3.5 : 1.0) * static_cast<double>(nodes.size()) + 3.0 * dens + 8.0;
+        cost[g] = 3.6 * (cplx ? 3.5 : 1.0) * static_cast<double>(nest_sizes[g]) + 3.0 * dens + 8.0;
         total += cost[g];
     }
     if (!split_groups(cost, waves, p.first)) return p;
@@ -1890,11 +1937,7 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
         // own groups into theirs; then every wave takes whole frequency rows.
         const int W = jit_block_forward_waves(t);
         std::vector<double> cost(static_cast<size_t>(G));
-        for (int g = 0; g < G; ++g) {
-            std::vector<HNode> nodes;
-            horner_build(terms_of(tb.group_start[g], tb.group_start[g + 1]), nodes);
-            cost[g] = static_cast<double>(nodes.size()) + 4.0;
-        }
+        for (int g = 0; g < G; ++g) cost[g] = static_cast<double>(group_nest_sizes(t)[g]) + 4.0;
         bp = BlockPlan();
         bp.waves = W;
         (void)split_groups(cost, W, bp.first);

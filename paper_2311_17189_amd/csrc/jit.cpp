@@ -17,7 +17,6 @@
 #include <cstdlib>
 #include <cstring>
 #include <fstream>
-#include <iterator>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -36,24 +35,36 @@ const char *const kOptions[] = {"--offload-arch=gfx950", "-O3", "-std=c++17", "-
                                 "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"};
 constexpr int kNumOptions = static_cast<int>(sizeof(kOptions) / sizeof(kOptions[0]));
 
-uint64_t fnv1a(const std::string &s, uint64_t h) {
-    for (unsigned char c : s) {
-        h ^= c;
-        h *= 1099511628211ull;
+// Two FNV-1a hashes side by side.
+struct Hash2 {
+    uint64_t a = 1469598103934665603ull, b = 0x9e3779b97f4a7c15ull;
+    void add(const std::string &s) {
+        uint64_t x = a, y = b;
+        for (unsigned char c : s) {
+            x = (x ^ c) * 1099511628211ull;
+            y = (y ^ c) * 1099511628211ull;
+        }
+        a = x;
+        b = y;
     }
-    return h;
-}
+};
 
 std::string cache_key(const std::string &src) {
-    int major = 0, minor = 0;
-    (void)hiprtcVersion(&major, &minor);
-    std::string all = "amigpu-jit-1|" + std::to_string(major) + "." + std::to_string(minor) + "|";
-    for (int i = 0; i < kNumOptions; ++i) all += std::string(kOptions[i]) + "|";
-    for (int i = 0; i < kJitHeaderCount; ++i) all += std::string(kJitHeaderNames[i]) + "|" + kJitHeaderTexts[i] + "|";
-    all += src;
+    // compiler, options and headers are the same for every source: hashed once
+    static const Hash2 common = [] {
+        int major = 0, minor = 0;
+        (void)hiprtcVersion(&major, &minor);
+        Hash2 h;
+        h.add("amigpu-jit-1|" + std::to_string(major) + "." + std::to_string(minor) + "|");
+        for (int i = 0; i < kNumOptions; ++i) h.add(std::string(kOptions[i]) + "|");
+        for (int i = 0; i < kJitHeaderCount; ++i) h.add(std::string(kJitHeaderNames[i]) + "|" + kJitHeaderTexts[i] + "|");
+        return h;
+    }();
+    Hash2 h = common;
+    h.add(src);
     char b[40];
-    std::snprintf(b, sizeof(b), "%016llx%016llx", static_cast<unsigned long long>(fnv1a(all, 1469598103934665603ull)),
-                  static_cast<unsigned long long>(fnv1a(all, 0x9e3779b97f4a7c15ull)));
+    std::snprintf(b, sizeof(b), "%016llx%016llx", static_cast<unsigned long long>(h.a),
+                  static_cast<unsigned long long>(h.b));
     return b;
 }
 
@@ -82,10 +93,13 @@ std::string cache_dir() {
 }
 
 bool read_file(const std::string &path, std::vector<char> &out) {
-    std::ifstream f(path, std::ios::binary);
+    std::ifstream f(path, std::ios::binary | std::ios::ate);
     if (!f) return false;
-    out.assign(std::istreambuf_iterator<char>(f), std::istreambuf_iterator<char>());
-    return static_cast<bool>(f) || f.eof();
+    const std::streamoff n = f.tellg();
+    if (n < 0) return false;
+    out.resize(static_cast<size_t>(n));
+    f.seekg(0);
+    return n == 0 || static_cast<bool>(f.read(out.data(), n));
 }
 
 void write_file_atomic(const std::string &path, const char *data, size_t n) {
@@ -236,8 +250,8 @@ AmiStatus code_from_source(const std::string &src, std::vector<char> &code, std:
     const std::string base = dir.empty() ? std::string() : dir + "/" + cache_key(src);
     if (!base.empty()) {
         std::vector<char> stored_src;
-        if (read_file(base + ".hip", stored_src) && std::string(stored_src.begin(), stored_src.end()) == src &&
-            read_file(base + ".hsaco", code) && !code.empty())
+        if (read_file(base + ".hip", stored_src) && stored_src.size() == src.size() &&
+            std::memcmp(stored_src.data(), src.data(), src.size()) == 0 && read_file(base + ".hsaco", code) && !code.empty())
             return AMI_OK;
         code.clear();
     }
