@@ -390,6 +390,14 @@ constexpr int kAdjLeafPartTerms = 32;
 constexpr int kAdjLeafFenceParts = 1;
 // Terms per nested part of a group in the block adjoint's leaf sweep.
 constexpr int kBlockPartTerms = 32;
+// The block adjoints' waves for one frequency row and for several are copies apart
+// above this many terms: the rows' cotangents of group sums overflow the registers
+// there, and one copy for both spills in the one-row path too (2804 terms, 2 10^5
+// samples: one row 189 us apart and 204 in one, four rows 607 and 658).  Below,
+// one copy takes two thirds of the compilation (560 terms at complex energies 11
+// -> 6 s) and of the code, and no more time (560 terms: 77 and 77 us, four rows 136
+// and 134; complex 137 and 135, 217 and 204; 264 terms complex 105 and 98).
+constexpr int kBlockRowsApartTerms = 1024;
 
 }  // namespace
 
@@ -1451,6 +1459,7 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
     if (kernels & (8192 | 16384)) {
         o << "constexpr int NW = " << bp.waves << ", GW = " << bp.max_groups << ", kRounds = " << bp.round.size() - 1
           << ", kBlockCols = " << bp.columns << ";\n";
+        o << "constexpr bool kRowsApart = " << (tb.T > kBlockRowsApartTerms ? "true" : "false") << ";\n";
         if (!blk_cplx) o << "constexpr int kValueWave = " << bp.value_wave << ";\n";
         o << "constexpr int kBE = " << bp.c_e << ", kBS = " << bp.c_slope << ", kBU = " << bp.c_union << ", kBF = "
           << bp.c_leaf << ", kBT = " << bp.c_group << ", kBA = " << bp.c_acc << ";\n";

@@ -262,8 +262,12 @@ extern "C" __global__ __launch_bounds__(AMI_JIT_BLOCK) void ami_jit_cadjl(ami::K
 extern "C" __global__ __launch_bounds__(64 * amijit::NW) __attribute__((amdgpu_waves_per_eu(2))) void ami_jit_badj(ami::KArgs a) {
     __shared__ double sm[64 * amijit::kBlockCols];
     const int64_t tile = (a.s0 >> 6) + blockIdx.x;      // s0: the launch's first sample
-    if (a.n_f == 1) amijit::badj_tile<AMI_JIT_HUB, true>(a, tile, sm);
-    else amijit::badj_tile<AMI_JIT_HUB, false>(a, tile, sm);
+    if constexpr (amijit::kRowsApart) {
+        if (a.n_f == 1) amijit::badj_tile<AMI_JIT_HUB, amijit::ONE_ROW>(a, tile, sm);
+        else amijit::badj_tile<AMI_JIT_HUB, amijit::SEVERAL_ROWS>(a, tile, sm);
+    } else {
+        amijit::badj_tile<AMI_JIT_HUB, amijit::ANY_ROWS>(a, tile, sm);
+    }
     finish_sums<amijit::NW>(a, sm);
 }
 #endif
@@ -272,8 +276,12 @@ extern "C" __global__ __launch_bounds__(64 * amijit::NW) __attribute__((amdgpu_w
 extern "C" __global__ __launch_bounds__(64 * amijit::NW) __attribute__((amdgpu_waves_per_eu(2))) void ami_jit_bcadj(ami::KArgs a) {
     __shared__ double sm[64 * amijit::kBlockCols];
     const int64_t tile = (a.s0 >> 6) + blockIdx.x;      // s0: the launch's first sample
-    if (a.n_f == 1) amijit::bcadj_tile<true>(a, tile, sm);
-    else amijit::bcadj_tile<false>(a, tile, sm);
+    if constexpr (amijit::kRowsApart) {
+        if (a.n_f == 1) amijit::bcadj_tile<amijit::ONE_ROW>(a, tile, sm);
+        else amijit::bcadj_tile<amijit::SEVERAL_ROWS>(a, tile, sm);
+    } else {
+        amijit::bcadj_tile<amijit::ANY_ROWS>(a, tile, sm);
+    }
     finish_sums<amijit::NW>(a, sm);
 }
 #endif

@@ -1259,6 +1259,15 @@ __device__ __forceinline__ double blk_wave_total(ami::clds col, int first) {
     return v;
 }
 
+template <bool B>
+struct BoolConst {
+    static constexpr bool value = B;
+};
+
+// The rows a copy of the block adjoints serves: one, several, or both (the host's
+// rule: kRowsApart).
+enum Rows { ANY_ROWS, ONE_ROW, SEVERAL_ROWS };
+
 // rows of W doubles staged at a stride of W + 1, the first n of them to dst
 template <int W>
 __device__ __forceinline__ void blk_store_rows(const double *stage, double *dst, int64_t n) {
@@ -1373,8 +1382,7 @@ __device__ __forceinline__ void blk_momentum_grads(int lane, ami::clds col, doub
 
 // Wave WV of the block.  The waves run copies of this function of their own
 // (badj_tile's uniform switch), which pass the same barriers.
-// ONE: one frequency row.
-template <bool HUB, int WV, bool ONE>
+template <bool HUB, int WV, Rows ROWS>
 __device__ __forceinline__ void badj_wave(const KArgs &a, int64_t tile, double *sm) {
     constexpr int wv = WV;
     const int lane = threadIdx.x & 63;
@@ -1438,8 +1446,8 @@ __device__ __forceinline__ void badj_wave(const KArgs &a, int64_t tile, double *
                     for (int c = 0; c < NV4; c += 4)
                         ami::wave_store4(vv[c], vv[c + 1], vv[c + 2], vv[c + 3], lane, pp[c], pp[c + 1], pp[c + 2], pp[c + 3]);
     };
-    const int nf = ONE ? 1 : a.n_f;
-    for (int f = 0; f < nf; ++f) {
+    auto row = [&](int f, auto one_row) __attribute__((always_inline)) {
+        constexpr bool ONE = decltype(one_row)::value;
         double cr = 0.0, ci = 0.0;
         if (active) {
             if (a.g_out) {
@@ -1456,7 +1464,7 @@ __device__ __forceinline__ void badj_wave(const KArgs &a, int64_t tile, double *
 #pragma unroll
         for (int x = 0; x < NXA; ++x) gwr[x] = gwi[x] = 0.0;
         blk_freq<WV, ONE>(col + 64 * kBE, wr, wi, col + 64 * kBT, ft, cr, ci, ftb, acc_re, acc_im, gE, gwr, gwi);
-        if (f > 0) __syncthreads();                  // the last row's sums have been read
+        if (!ONE && f > 0) __syncthreads();          // the last row's sums have been read
         col[64 * (kBA + wv)] = acc_re;
         col[64 * (kBA + NW + wv)] = acc_im;
 #pragma unroll
@@ -1468,17 +1476,25 @@ __device__ __forceinline__ void badj_wave(const KArgs &a, int64_t tile, double *
             __syncthreads();
             if (wv == f % NW) finish_row(f);
         }
-    }
+    };
+    const bool one = ROWS == ANY_ROWS ? a.n_f == 1 : ROWS == ONE_ROW;
+    if constexpr (ROWS != SEVERAL_ROWS)
+        if (one) row(0, BoolConst<true>());
+    if constexpr (ROWS != ONE_ROW)
+        if (!one) {
+            for (int f = 0; f < a.n_f; ++f) row(f, BoolConst<false>());
+            blk_keep<WV>(col + 64 * kBT, ftb);
+        }
 
     double FB[L], gbeta = 0.0;
 #pragma unroll
     for (int l = 0; l < L; ++l) FB[l] = 0.0;
-    if constexpr (!ONE) blk_keep<WV>(col + 64 * kBT, ftb);
     blk_leaf<WV>(col + 64 * kBF, col + 64 * kBT, ftb, FB);
     blk_rounds<WV>(FB, a.beta, a.e_reg, col + 64 * kBE, col + 64 * kBU, col + 64 * kBS, gE, gbeta);
     // one row: its parts have waited in their columns, so that a wave goes from
     // its groups' products to their leaf sweep without meeting the others
-    if constexpr (ONE && WV == 0) finish_row(0);
+    if constexpr (WV == 0 && ROWS != SEVERAL_ROWS)
+        if (one) finish_row(0);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < NE; ++i) col[64 * (kBU + i * NW + wv)] = gE[i];
@@ -1515,17 +1531,17 @@ __device__ __forceinline__ void badj_wave(const KArgs &a, int64_t tile, double *
     }
 }
 
-template <bool HUB, bool ONE>
+template <bool HUB, Rows ROWS>
 __device__ __forceinline__ void badj_tile(const KArgs &a, int64_t tile, double *sm) {
     switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
-    case 0: badj_wave<HUB, 0, ONE>(a, tile, sm); break;
-    case 1: badj_wave<HUB, 1, ONE>(a, tile, sm); break;
-    case 2: if constexpr (NW > 2) badj_wave<HUB, 2, ONE>(a, tile, sm); break;
-    case 3: if constexpr (NW > 2) badj_wave<HUB, 3, ONE>(a, tile, sm); break;
-    case 4: if constexpr (NW > 4) badj_wave<HUB, 4, ONE>(a, tile, sm); break;
-    case 5: if constexpr (NW > 4) badj_wave<HUB, 5, ONE>(a, tile, sm); break;
-    case 6: if constexpr (NW > 4) badj_wave<HUB, 6, ONE>(a, tile, sm); break;
-    case 7: if constexpr (NW > 4) badj_wave<HUB, 7, ONE>(a, tile, sm); break;
+    case 0: badj_wave<HUB, 0, ROWS>(a, tile, sm); break;
+    case 1: badj_wave<HUB, 1, ROWS>(a, tile, sm); break;
+    case 2: if constexpr (NW > 2) badj_wave<HUB, 2, ROWS>(a, tile, sm); break;
+    case 3: if constexpr (NW > 2) badj_wave<HUB, 3, ROWS>(a, tile, sm); break;
+    case 4: if constexpr (NW > 4) badj_wave<HUB, 4, ROWS>(a, tile, sm); break;
+    case 5: if constexpr (NW > 4) badj_wave<HUB, 5, ROWS>(a, tile, sm); break;
+    case 6: if constexpr (NW > 4) badj_wave<HUB, 6, ROWS>(a, tile, sm); break;
+    case 7: if constexpr (NW > 4) badj_wave<HUB, 7, ROWS>(a, tile, sm); break;
     }
 }
 #endif
@@ -1536,7 +1552,7 @@ __device__ __forceinline__ void badj_tile(const KArgs &a, int64_t tile, double *
 // end: NW per real and imaginary part of an energy's cotangent and for beta.
 // Gradient step at 2 10^5 samples, one row: 560 terms 302 us in passes, 134 here
 // (71 and 26 at 2 10^4 samples); 264 terms 201 us in one pass, 105 here.
-template <int WV, bool ONE>
+template <int WV, Rows ROWS>
 __device__ __forceinline__ void bcadj_wave(const KArgs &a, int64_t tile, double *sm) {
     const int lane = threadIdx.x & 63;
     const int64_t s0 = tile * 64, s = s0 + lane;
@@ -1617,8 +1633,8 @@ __device__ __forceinline__ void bcadj_wave(const KArgs &a, int64_t tile, double 
         for (int c = 0; c < NV4; c += 4)
             ami::wave_store4(vv[c], vv[c + 1], vv[c + 2], vv[c + 3], lane, pp[c], pp[c + 1], pp[c + 2], pp[c + 3]);
     };
-    const int nf = ONE ? 1 : a.n_f;
-    for (int f = 0; f < nf; ++f) {
+    auto row = [&](int f, auto one_row) __attribute__((always_inline)) {
+        constexpr bool ONE = decltype(one_row)::value;
         double cr = 0.0, ci = 0.0;
         if (active) {
             if (a.g_out) {
@@ -1636,7 +1652,7 @@ __device__ __forceinline__ void bcadj_wave(const KArgs &a, int64_t tile, double 
         for (int x = 0; x < NXA; ++x) gwr[x] = gwi[x] = 0.0;
         blk_freq<WV, ONE>(col + 64 * kBE, wr, wi, col + 64 * kBT, ftr, fti, cr, ci, ftbr, ftbi, acc_re, acc_im, gEr, gEi,
                           gwr, gwi);
-        if (f > 0) __syncthreads();                  // the last row's sums have been read
+        if (!ONE && f > 0) __syncthreads();          // the last row's sums have been read
         col[64 * (kBA + WV)] = acc_re;
         col[64 * (kBA + NW + WV)] = acc_im;
 #pragma unroll
@@ -1648,15 +1664,23 @@ __device__ __forceinline__ void bcadj_wave(const KArgs &a, int64_t tile, double 
             __syncthreads();
             if (WV == f % NW) finish_row(f);
         }
-    }
+    };
+    const bool one = ROWS == ANY_ROWS ? a.n_f == 1 : ROWS == ONE_ROW;
+    if constexpr (ROWS != SEVERAL_ROWS)
+        if (one) row(0, BoolConst<true>());
+    if constexpr (ROWS != ONE_ROW)
+        if (!one) {
+            for (int f = 0; f < a.n_f; ++f) row(f, BoolConst<false>());
+            blk_keep<WV>(col + 64 * kBT, ftbr, ftbi);
+        }
 
     double FBr[L], FBi[L], gbeta = 0.0;
 #pragma unroll
     for (int l = 0; l < L; ++l) FBr[l] = FBi[l] = 0.0;
-    if constexpr (!ONE) blk_keep<WV>(col + 64 * kBT, ftbr, ftbi);
     blk_leaf<WV>(col + 64 * kBF, col + 64 * kBT, ftbr, ftbi, FBr, FBi);
     blk_rounds<WV>(FBr, FBi, a.beta, a.e_reg, col + 64 * kBE, col + 64 * kBU, col + 64 * kBS, gEr, gEi, gbeta);
-    if constexpr (ONE && WV == 0) finish_row(0);
+    if constexpr (WV == 0 && ROWS != SEVERAL_ROWS)
+        if (one) finish_row(0);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < NE; ++i) {
@@ -1678,17 +1702,17 @@ __device__ __forceinline__ void bcadj_wave(const KArgs &a, int64_t tile, double 
     if (a.grad_e) blk_store_rows<2 * NE>(stage, a.grad_e + 2 * s0 * NE, n_rows);
 }
 
-template <bool ONE>
+template <Rows ROWS>
 __device__ __forceinline__ void bcadj_tile(const KArgs &a, int64_t tile, double *sm) {
     switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
-    case 0: bcadj_wave<0, ONE>(a, tile, sm); break;
-    case 1: bcadj_wave<1, ONE>(a, tile, sm); break;
-    case 2: if constexpr (NW > 2) bcadj_wave<2, ONE>(a, tile, sm); break;
-    case 3: if constexpr (NW > 2) bcadj_wave<3, ONE>(a, tile, sm); break;
-    case 4: if constexpr (NW > 4) bcadj_wave<4, ONE>(a, tile, sm); break;
-    case 5: if constexpr (NW > 4) bcadj_wave<5, ONE>(a, tile, sm); break;
-    case 6: if constexpr (NW > 4) bcadj_wave<6, ONE>(a, tile, sm); break;
-    case 7: if constexpr (NW > 4) bcadj_wave<7, ONE>(a, tile, sm); break;
+    case 0: bcadj_wave<0, ROWS>(a, tile, sm); break;
+    case 1: bcadj_wave<1, ROWS>(a, tile, sm); break;
+    case 2: if constexpr (NW > 2) bcadj_wave<2, ROWS>(a, tile, sm); break;
+    case 3: if constexpr (NW > 2) bcadj_wave<3, ROWS>(a, tile, sm); break;
+    case 4: if constexpr (NW > 4) bcadj_wave<4, ROWS>(a, tile, sm); break;
+    case 5: if constexpr (NW > 4) bcadj_wave<5, ROWS>(a, tile, sm); break;
+    case 6: if constexpr (NW > 4) bcadj_wave<6, ROWS>(a, tile, sm); break;
+    case 7: if constexpr (NW > 4) bcadj_wave<7, ROWS>(a, tile, sm); break;
     }
 }
 #endif
