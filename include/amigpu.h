@@ -456,6 +456,12 @@ AmiStatus amiIntegrateHubbard(AmiTerms *terms, int64_t n_samples, uint64_t seed,
 enum { AMI_VARIANT_AUTO = 0, AMI_VARIANT_TABLES = 1, AMI_VARIANT_PACKED = 2, AMI_VARIANT_SPECIALIZED = 3,
        AMI_VARIANT_TWO_PASS = 4 };
 
+/*
+ * amiSetVariant -- the variant of later calls.  Where AUTO's block kernels are
+ * ready (amiTermsSpecialize, or a call that used them), a forced specialized
+ * variant's own kernels in their place are compiled and loaded here, on the
+ * devices of the handle's kernels, so that no later call has to.
+ */
 AmiStatus amiSetVariant(AmiTerms *terms, int32_t variant);
 
 /*
@@ -475,12 +481,14 @@ AmiStatus amiSetTwoPassChunkBytes(int64_t bytes);
  * solution is outside the specialized form, AMI_E_HIP when compiling or loading
  * fails (amiLastError holds the compiler log).  The kernels are the forward
  * (its two passes and its block kernel where AUTO takes those), the adjoint
- * AUTO uses (one pass, block kernel or passes), and for solutions of at most 1024 terms
- * the complex-energy forward and the kernels of its adjoint that AUTO uses
- * (amiEvaluateComplex, amiEvaluateComplexAdjoint) for the energy input, above
- * that the two passes of the complex-energy forward; all are compiled before a
- * device is touched.  A solution with Taylor-coefficient leaves (AMI_MULTIPOLE)
- * gets no complex-energy kernels.
+ * AUTO uses (one pass, block kernel or passes), for the energy input the
+ * complex-energy forward and the kernels of its adjoint that AUTO uses
+ * (amiEvaluateComplex, amiEvaluateComplexAdjoint), and what the handle's variant
+ * takes in their place (the one-pass adjoints up to 128 terms, at complex
+ * energies 512, under AMI_VARIANT_SPECIALIZED; the adjoints in passes above under
+ * AMI_VARIANT_TWO_PASS; a later amiSetVariant makes those ready); all are
+ * compiled before a device is touched.  A solution with Taylor-coefficient
+ * leaves (AMI_MULTIPOLE) gets no complex-energy kernels.
  */
 AmiStatus amiTermsSpecialize(AmiTerms *terms, int32_t momentum);
 

@@ -3,6 +3,7 @@
 // evaluators; not part of the public ABI).
 #pragma once
 
+#include <atomic>
 #include <cstdint>
 #include <map>
 #include <mutex>
@@ -138,6 +139,7 @@ struct AmiTerms {
         void *module = nullptr, *fn = nullptr;
     };
     std::vector<JitModule> jit_mods;
+    std::atomic<bool> specialized[2] = {{false}, {false}};    // amiTermsSpecialize: energies, momenta
 };
 
 namespace ami {

@@ -1038,6 +1038,84 @@ void set_common(KArgs &a, const double *ext_freqs, int64_t n_f, double beta, dou
     a.n_e = n_e;
 }
 
+// The kernels that amiTermsSpecialize makes ready for this input under a variant:
+// AUTO's, or what a forced variant takes beside them -- the passes and one-pass
+// adjoints that AUTO leaves to the block kernels where a solution splits (their
+// compilation is as long as the block kernels').
+std::vector<int> kernels_of(const AmiTerms *t, bool hub, int variant) {
+    const bool forced = variant != AMI_VARIANT_AUTO;
+    const bool one_pass = variant == AMI_VARIANT_SPECIALIZED, passes = variant == AMI_VARIANT_TWO_PASS;
+    const int T = t->tab.T;
+    const bool small = T <= kJitMaxTerms;
+    bool taylor = false;                    // Taylor-coefficient leaves: no complex energies
+    for (int o : t->tab.leaf_order) taylor = taylor || o > 0;
+    std::vector<int> kinds;
+    if (!forced) {
+        if (jit_prefers_two_pass(t)) {      // the passes: Monte Carlo, and persistent batches
+            kinds.push_back(kJitSumsPass);
+            kinds.push_back(kJitFreqPass);
+            if (jit_block_forward_waves(t) > 0) kinds.push_back(kJitBlockForward);
+        } else {
+            kinds.push_back(kJitForward);
+        }
+    }
+    if ((one_pass || passes) && jit_prefers_two_pass(t)) {
+        kinds.push_back(kJitSumsPass);
+        kinds.push_back(kJitFreqPass);
+    }
+    const bool block = jit_prefers_block_adjoint(t) && jit_block_waves(t, hub) > 0;
+    if (!forced && block) kinds.push_back(kJitBlockAdjoint);
+    if (T <= kJitAutoAdjointTerms) {
+        if (forced ? one_pass : !block) kinds.push_back(kJitAdjoint);
+    } else if ((forced ? passes : !block) && jit_adjoint_passes_supported(t, hub, nullptr)) {
+        if (!jit_prefers_two_pass(t)) kinds.push_back(kJitSumsPass);
+        kinds.push_back(kJitAdjFreq);
+        kinds.push_back(kJitAdjLeaf);
+    }
+    if (taylor || hub || T > kJitTwoPassMaxTerms) return kinds;
+    // complex energies: the forward in one pass up to 1024 terms, in two above; the
+    // adjoint in a block, in one pass up to 512 terms, or in passes above
+    if (!forced) {
+        if (small) {
+            kinds.push_back(kJitComplex);
+        } else {
+            kinds.push_back(kJitComplexSums);
+            kinds.push_back(kJitComplexFreq);
+        }
+    }
+    const bool cblock = jit_block_waves(t, false, true) > 0;
+    if (!forced && cblock && T > kJitAutoComplexBlockTermsOneRow) kinds.push_back(kJitComplexBlockAdjoint);
+    const bool all_rows = cblock && T > kJitAutoComplexBlockTerms;      // the block for any number of rows
+    if (T <= kJitAutoComplexAdjointTerms) {
+        if (forced ? one_pass : !all_rows) kinds.push_back(kJitComplexAdj);
+    } else if (forced ? passes : !all_rows) {
+        if (forced || small) kinds.push_back(kJitComplexSums);
+        kinds.push_back(kJitComplexAdjFreq);
+        kinds.push_back(kJitComplexAdjLeaf);
+    }
+    return kinds;
+}
+
+// After amiSetVariant: loads what the new variant takes in place of AUTO's block
+// kernels, on the devices of the handle's kernels, so that no later call (under
+// capture, or the allocation-free one) finds it missing: for the inputs that
+// amiTermsSpecialize has made ready, else where a call has loaded the block kernel
+// that it stands for.  A kernel that is not to be had is reported by the call that needs it.
+void specialize_variant(AmiTerms *t) {
+    if (t->variant == AMI_VARIANT_AUTO) return;
+    for (int h = 0; h < 2; ++h) {
+        const bool hub = h != 0, all = t->specialized[h].load();
+        const bool fwd = all || jit_has_module(t, hub, kJitBlockForward);
+        const bool adj = all || jit_has_module(t, hub, kJitBlockAdjoint);
+        const bool cadj = !hub && (all || jit_has_module(t, hub, kJitComplexBlockAdjoint));
+        if (!fwd && !adj && !cadj) continue;
+        for (int k : kernels_of(t, hub, t->variant))
+            if (jit_kind_complex(k) ? cadj : k == kJitFreqPass ? fwd : k == kJitSumsPass ? fwd || adj : adj)
+                (void)jit_load_everywhere(t, hub, k);
+    }
+    clear_error();
+}
+
 }  // namespace
 
 AmiStatus launch_forward_as(AmiTerms *t, bool hub, KArgs &a, double *out_sum, hipStream_t stream, int variant,
@@ -1470,6 +1548,7 @@ AmiStatus amiSetVariant(AmiTerms *t, int32_t variant) {
     if (variant < AMI_VARIANT_AUTO || variant > AMI_VARIANT_TWO_PASS)
         return ami::fail(AMI_E_ARG, "variant must be one of AMI_VARIANT_*");
     t->variant = variant;
+    ami::specialize_variant(t);
     return AMI_OK;
 }
 
@@ -1478,52 +1557,10 @@ AmiStatus amiTermsSpecialize(AmiTerms *t, int32_t momentum) {
     if (!t) return ami::fail(AMI_E_ARG, "terms is NULL");
     using namespace ami;
     const bool hub = momentum != 0;
-    bool taylor = false;                    // Taylor-coefficient leaves: no complex energies
-    for (int o : t->tab.leaf_order) taylor = taylor || o > 0;
-    // the kernels for this input: forward, adjoint, and the complex-energy
-    // forward for the energy input; all compiled before any device is touched
-    const bool small = t->tab.T <= kJitMaxTerms;
-    std::vector<int> kinds;
-    if (jit_prefers_two_pass(t)) {
-        kinds.push_back(kJitSumsPass);
-        kinds.push_back(kJitFreqPass);
-        if (jit_block_forward_waves(t) > 0) kinds.push_back(kJitBlockForward);
-    } else {
-        kinds.push_back(kJitForward);
-    }
-    if (t->tab.T <= kJitAutoAdjointTerms) kinds.push_back(kJitAdjoint);
-    // the adjoint in passes where AUTO takes it, or a variant was set (its kernels
-    // compile as long as the block adjoint's)
-    const bool block_adj = jit_prefers_block_adjoint(t) && jit_block_waves(t, hub) > 0;
-    if (t->tab.T > kJitAutoAdjointTerms && (!block_adj || t->variant != AMI_VARIANT_AUTO) &&
-        jit_adjoint_passes_supported(t, hub, nullptr)) {
-        if (!jit_prefers_two_pass(t)) kinds.push_back(kJitSumsPass);
-        kinds.push_back(kJitAdjFreq);
-        kinds.push_back(kJitAdjLeaf);
-    }
-    if (block_adj) kinds.push_back(kJitBlockAdjoint);
-    // the complex-energy kernels AUTO uses: forward in one pass up to 1024
-    // terms, in two above; the adjoint in one pass up to 512 terms, in passes
-    // above
-    if (!taylor && !hub && t->tab.T <= kJitTwoPassMaxTerms) {
-        if (small) {
-            kinds.push_back(kJitComplex);
-        } else {
-            kinds.push_back(kJitComplexSums);
-            kinds.push_back(kJitComplexFreq);
-        }
-        const bool block = jit_block_waves(t, false, true) > 0;
-        if (block && t->tab.T > kJitAutoComplexBlockTermsOneRow) kinds.push_back(kJitComplexBlockAdjoint);
-        if (block && t->tab.T > kJitAutoComplexBlockTerms) {
-            // for any number of rows
-        } else if (t->tab.T <= kJitAutoComplexAdjointTerms) {
-            kinds.push_back(kJitComplexAdj);
-        } else {
-            if (small) kinds.push_back(kJitComplexSums);
-            kinds.push_back(kJitComplexAdjFreq);
-            kinds.push_back(kJitComplexAdjLeaf);
-        }
-    }
+    std::vector<int> kinds = kernels_of(t, hub, AMI_VARIANT_AUTO);
+    for (int k : kernels_of(t, hub, t->variant))
+        if (std::find(kinds.begin(), kinds.end(), k) == kinds.end()) kinds.push_back(k);
+    // all compiled before any device is touched
     for (int k : kinds) {
         const AmiStatus st = jit_compile(t, hub, k);
         if (st != AMI_OK) return st;
@@ -1533,6 +1570,7 @@ AmiStatus amiTermsSpecialize(AmiTerms *t, int32_t momentum) {
         const AmiStatus st = jit_get(t, hub, k, &fn);
         if (st != AMI_OK) return st;
     }
+    t->specialized[hub ? 1 : 0].store(true);
     return AMI_OK;
 }
 

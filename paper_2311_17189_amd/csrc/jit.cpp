@@ -12,6 +12,7 @@
 #include <sys/stat.h>
 #include <unistd.h>
 
+#include <algorithm>
 #include <cerrno>
 #include <cstdio>
 #include <cstdlib>
@@ -310,6 +311,39 @@ AmiStatus jit_get(AmiTerms *t, bool hub, int kind, void **fn) {
     t->jit_mods.push_back(m);
     *fn = m.fn;
     return AMI_OK;
+}
+
+bool jit_has_module(AmiTerms *t, bool hub, int kind) {
+    std::lock_guard<std::mutex> lock(t->jit_mu);
+    for (const auto &m : t->jit_mods)
+        if (m.kind == kJitKinds * (hub ? 1 : 0) + kind) return true;
+    return false;
+}
+
+AmiStatus jit_load_everywhere(AmiTerms *t, bool hub, int kind) {
+    std::vector<int> devices;
+    {
+        std::lock_guard<std::mutex> lock(t->jit_mu);
+        for (const auto &m : t->jit_mods)
+            if ((m.kind >= kJitKinds) == hub && std::find(devices.begin(), devices.end(), m.device) == devices.end())
+                devices.push_back(m.device);
+    }
+    int cur = 0;
+    hipError_t e = hipGetDevice(&cur);
+    if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
+    AmiStatus st = AMI_OK;
+    for (int d : devices) {
+        e = hipSetDevice(d);
+        if (e != hipSuccess) {
+            st = hip_fail(e, "hipSetDevice");
+            continue;
+        }
+        void *fn = nullptr;
+        const AmiStatus s = jit_get(t, hub, kind, &fn);
+        if (s != AMI_OK) st = s;
+    }
+    (void)hipSetDevice(cur);
+    return st;
 }
 
 AmiStatus jit_loaded(AmiTerms *t, bool hub, int kind, void **fn) {

@@ -163,6 +163,13 @@ inline bool jit_kind_complex(int kind) {
 // for the energy input only.
 AmiStatus jit_get(AmiTerms *t, bool hub, int kind, void **fn);
 
+// Whether any device holds this kernel of the handle.
+bool jit_has_module(AmiTerms *t, bool hub, int kind);
+
+// jit_get for every device that holds a kernel of the handle for this input
+// (the current device stays as it is).
+AmiStatus jit_load_everywhere(AmiTerms *t, bool hub, int kind);
+
 // The kernel of `kind` only if jit_get has already loaded it on the current
 // device (loads nothing, allocates nothing): AMI_E_UNSUPPORTED when its
 // compilation failed, AMI_E_ARG when it has not been loaded yet.
