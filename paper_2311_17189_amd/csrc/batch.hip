@@ -390,7 +390,8 @@ AmiStatus create_spec_persistent(const AmiBatchItem *items, int n_items, const A
     };
     for (int i = 0; i < n_items; ++i) {
         AmiTerms *t = items[i].terms;
-        if (!specialized_forward_ready(t, hub, static_cast<int>(items[i].n_f)))
+        // its tile functions are those of the one- or two-pass kernels
+        if (!specialized_forward_ready(t, hub, static_cast<int>(items[i].n_f), AMI_VARIANT_SPECIALIZED))
             return fail(AMI_E_UNSUPPORTED, "item " + std::to_string(i) + ": no specialized forward");
         two[i] = jit_prefers_two_pass(t) ? 1 : 0;
         if (two[i] && items[i].n_f > 65535) return fail(AMI_E_UNSUPPORTED, "more than 65535 frequency rows");

@@ -1128,11 +1128,11 @@ int64_t row_sum_rows(const AmiTerms *t, bool hub, int64_t n_e) {
     return (n_e + B - 1) / B * (B / 64);
 }
 
-bool specialized_forward_ready(AmiTerms *t, bool hub, int n_f) {
+bool specialized_forward_ready(AmiTerms *t, bool hub, int n_f, int variant) {
     Path p;
     void *f1 = nullptr, *f2 = nullptr;
     std::string note;
-    const AmiStatus st = choose_path(t, hub, false, p, &f1, note, &f2, n_f, AMI_VARIANT_AUTO);
+    const AmiStatus st = choose_path(t, hub, false, p, &f1, note, &f2, n_f, variant);
     clear_error();
     return st == AMI_OK && (p == Path::SPECIALIZED || p == Path::TWO_PASS || p == Path::FWD_BLOCK);
 }

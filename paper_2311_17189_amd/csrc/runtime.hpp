@@ -76,9 +76,11 @@ int64_t row_sum_rows(const AmiTerms *t, bool hub, int64_t n_e);
 // (its partial set) the specialized kernels' row sums are left to the caller.
 AmiStatus launch_forward_as(AmiTerms *t, bool hub, KArgs &a, double *out_sum, hipStream_t stream, int variant,
                             RowSums *sums = nullptr);
-// Whether AUTO would run the specialized (one- or two-pass) forward of t for
-// n_f frequency rows; compiles and loads its kernels on the current device.
-bool specialized_forward_ready(AmiTerms *t, bool hub, int n_f);
+// Whether AUTO would run the specialized forward of t for n_f frequency rows;
+// compiles and loads its kernels on the current device (variant
+// AMI_VARIANT_SPECIALIZED: those of the forward in one or two passes, without the
+// block kernel).
+bool specialized_forward_ready(AmiTerms *t, bool hub, int n_f, int variant = AMI_VARIANT_AUTO);
 // The argument block of an evaluate call: momenta (k non-NULL; q reduced
 // modulo 2 pi, its sin and cos) or energies, frequencies, beta, regulator.
 void set_inputs(KArgs &a, const AmiTerms *t, const double *k, int64_t stride_k, const double *q, double hop_t,
