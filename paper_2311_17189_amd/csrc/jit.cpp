@@ -292,7 +292,11 @@ AmiStatus jit_get(AmiTerms *t, bool hub, int kind, void **fn) {
         }
     hipModule_t mod = nullptr;
     e = hipModuleLoadData(&mod, t->jit_code[slot].data());
-    if (e != hipSuccess) return hip_fail(e, "hipModuleLoadData (specialized kernel)");
+    // the error is reported here: the launch of a fallback must not find it again
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return hip_fail(e, "hipModuleLoadData (specialized kernel)");
+    }
     hipFunction_t f = nullptr;
     static const char *const kNames[kJitKinds] = {"ami_jit_fwd",  "ami_jit_adj",   "ami_jit_mc",   "ami_jit_cfwd",
                                                   "ami_jit_sums", "ami_jit_freq",  "ami_jit_adjf", "ami_jit_adjl",
@@ -301,6 +305,7 @@ AmiStatus jit_get(AmiTerms *t, bool hub, int kind, void **fn) {
     e = hipModuleGetFunction(&f, mod, kNames[kind]);
     if (e != hipSuccess) {
         (void)hipModuleUnload(mod);
+        (void)hipGetLastError();
         return hip_fail(e, "hipModuleGetFunction (specialized kernel)");
     }
     AmiTerms::JitModule m;
