@@ -439,7 +439,10 @@ AmiStatus amiIntegrateHubbard(AmiTerms *terms, int64_t n_samples, uint64_t seed,
  *                            equal the forward's up to rounding
  * A forced variant that cannot serve a call fails it (AMI_E_UNSUPPORTED, or
  * AMI_E_HIP when the run-time compilation fails); AUTO falls back in the order
- * above and amiLastVariant names what ran and why.
+ * above and amiLastVariant names what ran and why.  It names the block kernels
+ * by the kernels they stand for (the forward's two passes, the adjoint in one
+ * pass or in passes, by the solution's size); where AUTO had to fall back from
+ * a block kernel the name says so ("... (not in a block: why)").
  *
  * Tuning overrides of the generated kernels, read from the environment when a
  * kernel is generated (each changes the source, so the disk cache keeps the

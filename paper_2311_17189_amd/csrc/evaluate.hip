@@ -403,6 +403,7 @@ AmiStatus choose_path(AmiTerms *t, bool hub, bool adjoint, Path &p, void **jit_f
             p = Path::FWD_BLOCK;
             return AMI_OK;
         }
+        note = std::string(" (not in a block: ") + amiLastError() + ")";
         clear_error();
     }
     if (two) {
@@ -663,8 +664,11 @@ AmiStatus launch_forward(AmiTerms *t, bool hub, KArgs &a, double *out_sum, hipSt
     std::string note;
     st = choose_path(t, hub, false, path, &jit_fn, note, &jit_fn2, a.n_f, variant);
     if (st != AMI_OK) return st;
-    if (path == Path::TWO_PASS)
-        return launch_two_pass(t, dt, hub, a, out_sum, jit_fn, jit_fn2, stream, false, sums);
+    if (path == Path::TWO_PASS) {
+        st = launch_two_pass(t, dt, hub, a, out_sum, jit_fn, jit_fn2, stream, false, sums);
+        g_last_variant += note;
+        return st;
+    }
     const bool block_fwd = path == Path::FWD_BLOCK;   // one row of partial sums per 64 samples
     if (block_fwd) path = Path::SPECIALIZED;
     LaunchShape ls;
@@ -703,7 +707,8 @@ AmiStatus launch_forward(AmiTerms *t, bool hub, KArgs &a, double *out_sum, hipSt
         }
         if (block_fwd) e = launch_block(jit_fn, nblocks, waves, stream, a, parts);
         else e = launch_jit(jit_fn, nblocks, ls.block, stream, a, parts);
-        // the block forward is named as the two passes it stands for
+        // the block forward is named as the two passes it stands for; those name
+        // why it did not run where AUTO falls back to them
         g_last_variant = block_fwd ? "specialized two-pass" : "specialized";
         if (e == hipSuccess) e = hipGetLastError();
     } else if (path == Path::PACKED) {
@@ -924,8 +929,11 @@ AmiStatus launch_adjoint(AmiTerms *t, bool hub, KArgs &a, const AdjOut &o, hipSt
     std::string note;
     st = choose_path(t, hub, true, path, &jit_fn, note, &jit_fn2, a.n_f, -1, fixed_ws != nullptr, &jit_fn3);
     if (st != AMI_OK) return st;
-    if (path == Path::ADJ_PASSES)
-        return launch_adjoint_passes(t, dt, hub, a, o, jit_fn, jit_fn2, jit_fn3, stream, fixed_ws);
+    if (path == Path::ADJ_PASSES) {
+        st = launch_adjoint_passes(t, dt, hub, a, o, jit_fn, jit_fn2, jit_fn3, stream, fixed_ws);
+        g_last_variant += note;
+        return st;
+    }
     if (path == Path::ADJ_BLOCK) return launch_adjoint_block(t, dt, hub, a, o, jit_fn, stream, fixed_ws);
     LaunchShape ls;
     if (path == Path::SPECIALIZED) {
@@ -962,7 +970,7 @@ AmiStatus launch_adjoint(AmiTerms *t, bool hub, KArgs &a, const AdjOut &o, hipSt
         fin = !fixed_ws && finish_small(t, dt, stream, a, kFinishOnePass, nblocks, ls.block / 64, ncols,
                                        o.out_sum ? 2 * a.n_f : 0, o);
         e = launch_jit(jit_fn, nblocks, ls.block, stream, a);
-        g_last_variant = "specialized";
+        g_last_variant = "specialized" + note;
         if (e == hipSuccess) e = hipGetLastError();
     } else {
         a.tb = packed_tabs(t, dt);
@@ -1290,6 +1298,7 @@ AmiStatus amiEvaluateComplexAdjoint(AmiTerms *t, const double *energies, int64_t
     bo.grad_beta = grad_beta;
     bo.grad_freqs = grad_freqs;
     bo.out_sum = out_sum;
+    std::string note;
     // AUTO: the block adjoint where the solution splits over the waves of a block
     if (t->variant == AMI_VARIANT_AUTO && n_e > 0 &&
         t->tab.T > (n_f == 1 ? kJitAutoComplexBlockTermsOneRow : kJitAutoComplexBlockTerms) &&
@@ -1297,6 +1306,7 @@ AmiStatus amiEvaluateComplexAdjoint(AmiTerms *t, const double *energies, int64_t
         void *fb = nullptr;
         st = jit_get(t, false, kJitComplexBlockAdjoint, &fb);
         if (st == AMI_OK) return launch_adjoint_block(t, dt, false, ba, bo, fb, stream, nullptr, true);
+        note = std::string(" (not in a block: ") + amiLastError() + ")";
         clear_error();
     }
     // above the one-pass complex adjoint's automatic size (unless the handle
@@ -1315,7 +1325,9 @@ AmiStatus amiEvaluateComplexAdjoint(AmiTerms *t, const double *energies, int64_t
             if (st == AMI_OK) st = fill(grad_freqs, 2 * n_f * t->n_ext, stream);
             return st;
         }
-        return launch_adjoint_passes(t, dt, false, ba, bo, fs, ff, fl, stream, nullptr, true);
+        st = launch_adjoint_passes(t, dt, false, ba, bo, fs, ff, fl, stream, nullptr, true);
+        g_last_variant += note;
+        return st;
     }
     void *fn = nullptr;
     st = jit_get(t, false, kJitComplexAdj, &fn);
@@ -1354,7 +1366,7 @@ AmiStatus amiEvaluateComplexAdjoint(AmiTerms *t, const double *energies, int64_t
     const bool fin = finish_small(t, dt, stream, a, kFinishComplexAdjoint, nblocks, block / 64, ncols, nval, bo);
     hipError_t e = launch_jit(fn, nblocks, block, stream, a);
     if (e == hipSuccess) e = hipGetLastError();
-    g_last_variant = "specialized complex";
+    g_last_variant = "specialized complex" + note;
     if (e != hipSuccess) return hip_fail(e, "complex-energy adjoint launch");
     if (fin) return AMI_OK;
     const int n_red = ncols + nval;
