@@ -475,6 +475,16 @@ AmiStatus workspace(AmiTerms *t, DeviceTables *dt, hipStream_t stream, size_t by
     return AMI_OK;
 }
 
+// Whether a capture of the stream is under way (or that is not known).
+bool capturing(hipStream_t stream) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return cap != hipStreamCaptureStatusNone;
+}
+
 // Where the totals of a call's partial sums go (finish_small): a's gradient
 // columns, then the row sums of the values.
 struct AdjOut {
@@ -507,12 +517,7 @@ bool finish_small(AmiTerms *t, DeviceTables *dt, hipStream_t stream, KArgs &a, c
     const int64_t chunks = (a.nrows + 63) / 64;
     if (chunks > 16 || blocks > lim.blocks || (ncols + nval + waves - 1) / waves * chunks > lim.loads) return false;
     if (stream == hipStreamPerThread) return false;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &cap) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    if (cap != hipStreamCaptureStatusNone) return false;
+    if (capturing(stream)) return false;
     {
         std::lock_guard<std::mutex> lk(t->dev_mu);
         DeviceTables::Workspace *w = nullptr;
@@ -1300,9 +1305,20 @@ AmiStatus amiEvaluateComplexAdjoint(AmiTerms *t, const double *energies, int64_t
     bo.out_sum = out_sum;
     std::string note;
     // AUTO: the block adjoint where the solution splits over the waves of a block
-    if (t->variant == AMI_VARIANT_AUTO && n_e > 0 &&
-        t->tab.T > (n_f == 1 ? kJitAutoComplexBlockTermsOneRow : kJitAutoComplexBlockTerms) &&
-        jit_block_waves(t, false, true) > 0) {
+    bool to_block = t->variant == AMI_VARIANT_AUTO && n_e > 0 &&
+                    t->tab.T > (n_f == 1 ? kJitAutoComplexBlockTermsOneRow : kJitAutoComplexBlockTerms) &&
+                    jit_block_waves(t, false, true) > 0;
+    // where the number of rows decides, earlier calls with other rows may have left
+    // this call's kernel unloaded: under capture, which is no place to compile, the
+    // one that is loaded serves
+    if (t->variant == AMI_VARIANT_AUTO && n_e > 0 && t->tab.T > kJitAutoComplexBlockTermsOneRow &&
+        t->tab.T <= kJitAutoComplexBlockTerms && capturing(stream)) {
+        void *fn = nullptr;
+        const bool block = jit_loaded(t, false, kJitComplexBlockAdjoint, &fn) == AMI_OK;
+        if (block != (jit_loaded(t, false, kJitComplexAdj, &fn) == AMI_OK)) to_block = block;
+        clear_error();
+    }
+    if (to_block) {
         void *fb = nullptr;
         st = jit_get(t, false, kJitComplexBlockAdjoint, &fb);
         if (st == AMI_OK) return launch_adjoint_block(t, dt, false, ba, bo, fb, stream, nullptr, true);
