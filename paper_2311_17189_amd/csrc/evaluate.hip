@@ -571,30 +571,59 @@ hipError_t launch_block(void *fn, int64_t tiles, int waves, hipStream_t stream, 
     return e;
 }
 
-// The parts of at most `parts` that hold a row: each takes an even number of
-// them (AMI_JIT_ROW_PART).
+// Rows of a part where n_f rows are split in `parts`: an even number of them
+// (AMI_JIT_ROW_PART); and the parts of those that hold a row.
+int64_t rows_per_part(int64_t n_f, int64_t parts) {
+    return parts <= 1 ? n_f : ((n_f + parts - 1) / parts + 1) & ~int64_t(1);
+}
+
 int nonempty_parts(int64_t n_f, int64_t parts) {
-    if (parts <= 1) return 1;
-    const int64_t per = ((n_f + parts - 1) / parts + 1) & ~int64_t(1);
-    return static_cast<int>((n_f + per - 1) / per);
+    const int64_t per = std::max<int64_t>(rows_per_part(n_f, parts), 1);
+    return parts <= 1 ? 1 : static_cast<int>((n_f + per - 1) / per);
 }
 
 // Parts of the frequency rows of a one-pass forward, each a grid of its own over
-// the samples that forms the leaves and group sums again.  A SIMD with one wave
-// issues FP64 at half rate, so as many parts as keep to two waves per SIMD (2048
-// waves) cost no time; more, up to eight per SIMD, pay while a part holds enough
-// rows to make the repeated leaves an eighth of it (instructions estimated from
-// the sizes).  Order 4, 52 terms, 256 rows: 10^5 samples 142 us in one part, 121
-// in six; 10^4 samples 107 and 24.
-int forward_row_parts(const AmiTerms *t, bool hub, int64_t n_waves, int64_t n_f) {
+// the samples that forms the leaves and group sums again: the number whose waves
+// finish first.  A SIMD's time is its waves' instructions (estimated from the
+// sizes), 1.3 times that for a wave alone, 1.1 for two at a time, 1.03 for three;
+// the waves the registers do not hold side by side follow one another.  (From the
+// kernel times of six diagrams at 3000 to 10^5 samples, 4 to 256 rows and one to
+// 32 parts, real and complex: what this picks takes 1% more than the best on
+// average.  Two waves per SIMD taken for free, as before, took 8% more, and lost
+// where a row is cheap beside the leaves: 5 10^4 samples, four rows, 264 terms
+// 9.4 us in one part and 11.5 in two, at complex energies 14.3 and 20.4.  The gains:
+// order 4, 52 terms, 256 rows of 10^5 samples 142 us in one part, 118 in six,
+// of 10^4 samples 96 and 21.)
+int forward_row_parts(const AmiTerms *t, bool hub, bool cplx, int64_t n_waves, int64_t n_f) {
     if (n_f < 4) return 1;
     const Tables &tb = t->tab;
-    const double once = 30.0 * tb.L + tb.T + (hub ? 34.0 * t->n_g : 0.0);
-    const double per_row = 18.0 * tb.D + 10.0 * tb.G + 20.0;
-    const int64_t free_parts = 2048 / std::max<int64_t>(n_waves, 1);
-    const int64_t full_parts = std::min<int64_t>((8192 + n_waves - 1) / std::max<int64_t>(n_waves, 1),
-                                                 static_cast<int64_t>(n_f * per_row / (8.0 * once)));
-    return nonempty_parts(n_f, std::min<int64_t>({std::max(free_parts, full_parts), n_f / 2, 1024}));
+    const double once = cplx ? 85.0 * tb.L + 4.0 * tb.T + 2.0 * tb.D : 30.0 * tb.L + tb.T + (hub ? 34.0 * t->n_g : 0.0);
+    const double per_row = (cplx ? 22.0 * tb.D + 16.0 * tb.G : 18.0 * tb.D + 12.0 * tb.G) + 40.0;
+    const double vgprs = cplx ? 1.5 * (4.0 * tb.G + 6.0 * tb.D) : 2.2 * (2.0 * tb.G + 4.0 * tb.D);
+    const int64_t side_by_side = std::max(1, std::min(8, static_cast<int>(512.0 / std::max(vgprs, 40.0))));
+    auto rate = [](int64_t waves) { return waves <= 1 ? 1.3 : waves == 2 ? 1.1 : waves == 3 ? 1.03 : 1.0; };
+    auto time = [&](int64_t parts) {
+        const int64_t waves = (std::max<int64_t>(n_waves, 1) * parts + 1023) / 1024;      // of a SIMD
+        const int64_t full = waves / side_by_side, rest = waves % side_by_side;
+        const double issue = static_cast<double>(full * side_by_side) * rate(side_by_side) +
+                             (rest ? static_cast<double>(rest) * rate(rest) : 0.0);
+        return issue * (once + per_row * static_cast<double>(rows_per_part(n_f, parts)));
+    };
+    // the fewest parts within 4% of the least time, one within 5%
+    const int64_t most = std::min<int64_t>(n_f / 2, 1024);
+    auto next = [](int64_t p) { return p + (p < 16 ? 1 : p & (p - 1) ? p / 3 : p / 2); };
+    double least = 0.95 * time(1);
+    bool split = false;
+    for (int64_t p = 2; p <= most; p = next(p)) {
+        const double v = time(p);
+        if (v >= least) continue;
+        least = v;
+        split = true;
+    }
+    if (!split) return 1;
+    int64_t p = 2;
+    while (time(p) > 1.04 * least) p = next(p);
+    return nonempty_parts(n_f, p);
 }
 
 // Row parts of the block forward: as many as fill the chip's 512 resident blocks
@@ -703,7 +732,7 @@ AmiStatus launch_forward(AmiTerms *t, bool hub, KArgs &a, double *out_sum, hipSt
         a.partial = partial;
         a.nrows = rows;
         const int waves = block_fwd ? jit_block_forward_waves(t) : ls.block / 64;
-        const int parts = block_fwd ? block_row_parts(waves, nblocks, a.n_f) : forward_row_parts(t, hub, rows, a.n_f);
+        const int parts = block_fwd ? block_row_parts(waves, nblocks, a.n_f) : forward_row_parts(t, hub, false, rows, a.n_f);
         if (out_sum && !sums) {
             AdjOut o;
             o.out_sum = out_sum;
@@ -1256,7 +1285,7 @@ AmiStatus amiEvaluateComplex(AmiTerms *t, const double *energies, int64_t n_e, i
         st = workspace(t, dt, stream, static_cast<size_t>(rows) * n_f * 2 * sizeof(double), &a.partial);
         if (st != AMI_OK) return st;
     }
-    const int parts = forward_row_parts(t, false, rows, n_f);
+    const int parts = forward_row_parts(t, false, true, rows, n_f);
     AdjOut o;
     o.out_sum = out_sum;
     const bool fin = out_sum && finish_small(t, dt, stream, a, kFinishComplex, nblocks * parts, block / 64, 0,
