@@ -399,6 +399,14 @@ constexpr int kBlockPartTerms = 32;
 // and 134; complex 137 and 135, 217 and 204; 264 terms complex 105 and 98).
 constexpr int kBlockRowsApartTerms = 1024;
 
+// Values a row of the one-pass forwards holds (group sums and reciprocals with
+// their arguments), up to which it takes two rows at a time.  Two rows' values
+// cost registers: at complex energies 264 terms (168 values) fell from two waves
+// per SIMD to one (252 -> 292 VGPRs; 16 rows of 2 10^5 samples 88 us a row at a time,
+// 100 two), and nothing above these sizes gained.  Below, 16 rows of 10^6 order-2
+// samples 57.4 us and 54.8.
+constexpr int kPairRowsValues = 40, kPairRowsValuesC = 64;
+
 }  // namespace
 
 bool jit_prefers_two_pass(const AmiTerms *t) {
@@ -755,6 +763,9 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
     // the forward values from sum_g FT_g R_g nested over the reciprocals
     // (groups_combine) above the adjoint's automatic size, group by group below
     const bool nested_groups = tb.T > kJitAutoAdjointTerms;
+    if (kernels & (1 | 8))
+        o << "constexpr bool kPairRows = " << (2 * G + 4 * D <= kPairRowsValues ? "true" : "false")
+          << ", kPairRowsC = " << (4 * G + 6 * D <= kPairRowsValuesC ? "true" : "false") << ";\n";
     o << "constexpr bool kNestedGroups = " << (nested_groups ? "true" : "false") << ";\n";
     o << "constexpr bool kBose[L] = {";
     for (int l = 0; l < L; ++l) o << (l ? ", " : "") << (tb.leaf_sigma[l] < 0 ? "true" : "false");

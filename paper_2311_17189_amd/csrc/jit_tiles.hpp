@@ -202,11 +202,10 @@ __device__ __forceinline__ void reciprocals(const double (&E)[NE], const double 
 }
 
 #if AMI_JIT_KERNELS & (1 | 8)
-// The rows [f0, f1) of one sample, two at a time: row(f, re, im) gives a row's
-// value, which goes to out; the wave sums of two rows leave in one wave_store4
-// (21 instructions for four sums; two wave_store2 take twice that, a sixth of a
-// row of an order-4 diagram).
-template <typename Row>
+// The rows [f0, f1) of one sample: row(f, re, im) gives a row's value, which goes
+// to out.  PAIR: two at a time, whose wave sums leave in one wave_store4 (21
+// instructions for four sums; two wave_store2 take twice that).
+template <bool PAIR, typename Row>
 __device__ __forceinline__ void forward_rows(const KArgs &a, int64_t s, bool active, int lane, int64_t row, int f0,
                                              int f1, Row row_value) {
     auto put = [&](int f, double re, double im) {
@@ -218,7 +217,7 @@ __device__ __forceinline__ void forward_rows(const KArgs &a, int64_t s, bool act
         }
     };
     int f = f0;
-    for (; f + 1 < f1; f += 2) {
+    for (; PAIR && f + 1 < f1; f += 2) {
         double re0, im0, re1, im1;
         row_value(f, re0, im0);
         put(f, re0, im0);
@@ -230,7 +229,7 @@ __device__ __forceinline__ void forward_rows(const KArgs &a, int64_t s, bool act
                              p + a.nrows, p + 2 * a.nrows, p + 3 * a.nrows);
         }
     }
-    if (f < f1) {
+    for (; f < f1; ++f) {
         double re, im;
         row_value(f, re, im);
         put(f, re, im);
@@ -268,13 +267,13 @@ __device__ __forceinline__ void fwd_tile(const KArgs &a, int64_t tile, int f0, i
     double FT[G];
     group_sums(F, FT);
 
-    forward_rows(a, s, active, lane, row, NF1 ? 0 : f0, NF1 ? 1 : f1,
-                 [&](int f, double &re, double &im) __attribute__((always_inline)) {
-                     double wr[NXA], wi[NXA], xr[D], xi[D];
-                     load_freq(a, f, wr, wi);
-                     reciprocals(E, wr, wi, xr, xi);
-                     groups_combine(xr, xi, FT, re, im);
-                 });
+    forward_rows<kPairRows>(a, s, active, lane, row, NF1 ? 0 : f0, NF1 ? 1 : f1,
+                            [&](int f, double &re, double &im) __attribute__((always_inline)) {
+                                double wr[NXA], wi[NXA], xr[D], xi[D];
+                                load_freq(a, f, wr, wi);
+                                reciprocals(E, wr, wi, xr, xi);
+                                groups_combine(xr, xi, FT, re, im);
+                            });
 }
 
 #endif
@@ -814,7 +813,8 @@ __device__ __forceinline__ void cfwd_tile(const KArgs &a, int64_t tile, int f0, 
         den_args(Ei, zr, zi, dEi, unused);          // e_k . Im E
     }
 
-    forward_rows(a, s, active, lane, row, f0, f1, [&](int f, double &re, double &im) __attribute__((always_inline)) {
+    forward_rows<kPairRowsC>(a, s, active, lane, row, f0, f1,
+                             [&](int f, double &re, double &im) __attribute__((always_inline)) {
         double wr[NXA], wi[NXA], dr[D], di[D], xr[D], xi[D], Rr[G], Ri[G];
         load_freq(a, f, wr, wi);
         den_args(Er, wr, wi, dr, di);
