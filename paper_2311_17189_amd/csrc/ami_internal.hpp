@@ -125,15 +125,15 @@ struct AmiTerms {
     // kJitKinds * momentum + JitKind -- and the modules loaded from them, one per
     // device
     std::mutex jit_mu;
-    std::vector<char> jit_code[32];           // [2 inputs][kJitKinds]
-    std::string jit_error[32];                // why a compilation failed (not retried)
+    std::vector<char> jit_code[34];           // [2 inputs][kJitKinds]
+    std::string jit_error[34];                // why a compilation failed (not retried)
     // nodes of each group's nested sum (group_nest_sizes)
     mutable std::once_flag nest_once;
     mutable std::vector<int> nest_sizes;
-    // waves per block of the block adjoints: energies, momenta, complex energies
-    // (-1: not computed), under plan_mu
+    // waves per block of the block adjoints: energies, momenta, complex energies, then
+    // energies and momenta with several rows (-1: not computed), under plan_mu
     mutable std::mutex plan_mu;
-    mutable int block_waves[3] = {-1, -1, -1};
+    mutable int block_waves[5] = {-1, -1, -1, -1, -1};
     struct JitModule {
         int device = -1, kind = 0;
         void *module = nullptr, *fn = nullptr;

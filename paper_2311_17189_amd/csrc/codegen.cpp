@@ -398,6 +398,12 @@ constexpr int kBlockPartTerms = 32;
 // -> 6 s) and of the code, and no more time (560 terms: 77 and 77 us, four rows 136
 // and 134; complex 137 and 135, 217 and 204; 264 terms complex 105 and 98).
 constexpr int kBlockRowsApartTerms = 1024;
+// Groups of a wave above which the real block adjoint for several rows takes eight
+// waves for four: their cotangents stay in registers through the rows, beside four
+// values for each denominator (2804 terms, 31 groups of a wave, 10^5 samples: two
+// rows 214 us with four waves, 170 with eight, 16 rows 1075 and 555, where the passes
+// take 861; 21 groups: four rows 181 and 166, 2054 terms 174 and 178).
+constexpr int kBlockRowGroups = 24;
 
 // Values a row of the one-pass forwards holds (group sums and reciprocals with
 // their arguments), up to which it takes two rows at a time.  Two rows' values
@@ -708,11 +714,18 @@ static int choose_block_waves(const AmiTerms *t, bool hub, bool cplx) {
     return 0;
 }
 
-int jit_block_waves(const AmiTerms *t, bool hub, bool cplx) {
+bool jit_block_rows_apart(const AmiTerms *t) { return t->tab.T > kBlockRowsApartTerms; }
+
+int jit_block_waves(const AmiTerms *t, bool hub, bool cplx, bool several) {
     std::lock_guard<std::mutex> lock(t->plan_mu);
     int &w = t->block_waves[cplx ? 2 : hub ? 1 : 0];
     if (w < 0) w = choose_block_waves(t, hub, cplx);
-    return w;
+    if (cplx || !several || w != 4 || !jit_block_rows_apart(t)) return w;
+    int &s = t->block_waves[hub ? 4 : 3];
+    if (s < 0 && std::getenv("AMIGPU_JIT_BLOCK_WAVES")) s = w;
+    if (s < 0)
+        s = block_plan(t, hub, false, 4).max_groups > kBlockRowGroups && block_plan(t, hub, false, 8).waves > 0 ? 8 : 4;
+    return s;
 }
 
 namespace {
@@ -1426,7 +1439,8 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
     // (wave WV of a block), a range of terms, and the reads of a range's leaves.
     const bool blk_cplx = (kernels & 16384) != 0;
     BlockPlan bp;
-    if (kernels & (8192 | 16384)) bp = block_plan(t, hub, blk_cplx, jit_block_waves(t, hub, blk_cplx));
+    if (kernels & (8192 | 65536 | 16384))
+        bp = block_plan(t, hub, blk_cplx, jit_block_waves(t, hub, blk_cplx, (kernels & 65536) != 0));
     auto wave_fn = [&](const std::string &name, const std::string &args, bool reverse, const auto &body) {
         o << "template <int WV" << (name == "blk_freq" ? ", bool ONE" : "") << "> __device__ __forceinline__ void " << name << "(" << args << ") {\n";
         if (reverse) o << kReverseContract;
@@ -1467,17 +1481,17 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
         o << "__device__ __forceinline__ void blk_cleaf(bool bose, double yr, double yi, double &fr, double &fi, double "
              "&Sr, double &Si) {\n  double mr, mi;\n  ami::leaf_complex_pair(bose, yr, yi, fr, fi, mr, mi);\n"
              "  Sr = -fma(fr, mr, -fi * mi);\n  Si = fma(fr, mi, fi * mr);\n}\n";
-    if (kernels & (8192 | 16384)) {
+    if (kernels & (8192 | 65536 | 16384)) {
         o << "constexpr int NW = " << bp.waves << ", GW = " << bp.max_groups << ", kRounds = " << bp.round.size() - 1
           << ", kBlockCols = " << bp.columns << ";\n";
-        o << "constexpr bool kRowsApart = " << (tb.T > kBlockRowsApartTerms ? "true" : "false") << ";\n";
+        o << "constexpr bool kRowsApart = " << (jit_block_rows_apart(t) ? "true" : "false") << ";\n";
         if (!blk_cplx) o << "constexpr int kValueWave = " << bp.value_wave << ";\n";
         o << "constexpr int kBE = " << bp.c_e << ", kBS = " << bp.c_slope << ", kBU = " << bp.c_union << ", kBF = "
           << bp.c_leaf << ", kBT = " << bp.c_group << ", kBA = " << bp.c_acc << ";\n";
         o << "__device__ __forceinline__ void blk_rho(double dr, double di, double &xr, double &xi) {\n"
              "  const double inv = ami::rcp_nr(fma(dr, dr, di * di));\n  xr = dr * inv;\n  xi = -di * inv;\n}\n";
     }
-    if (kernels & 8192) {
+    if (kernels & (8192 | 65536)) {
         // The block adjoint's per-wave functions (wave WV of a block of NW
         // waves that share 64 samples; LDS columns are passed as the address
         // of the lane's element in the first column of a region, column c of
@@ -2472,7 +2486,7 @@ std::string jit_source(const AmiTerms *t, bool hub, int kernels, int nested_part
 
     // the leaves' and lines' scatters: every adjoint kernel (one pass, or the
     // leaf pass of large solutions)
-    if (adj_fns || (kernels & (128 | 8192))) {
+    if (adj_fns || (kernels & (128 | 8192 | 65536))) {
     auto scatter = [&](std::ostream &os, double c, const std::string &dst, const std::string &v) {
         if (c == 0.0) return;
         if (c == 1.0) os << "  " << dst << " += " << v << ";\n";

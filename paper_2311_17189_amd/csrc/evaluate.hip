@@ -373,7 +373,13 @@ AmiStatus choose_path(AmiTerms *t, bool hub, bool adjoint, Path &p, void **jit_f
                                                : "the two-pass variant takes at most 65535 frequency rows");
     if (adjoint && jit_fn3 && v == AMI_VARIANT_AUTO && jit_prefers_block_adjoint(t) &&
         jit_block_waves(t, hub) > 0) {
-        const AmiStatus st = get(kJitBlockAdjoint, jit_fn);
+        // one row's kernel and several rows' are ready together
+        AmiStatus st = get(kJitBlockAdjoint, jit_fn);
+        if (st == AMI_OK && jit_block_rows_apart(t)) {
+            void *rows = nullptr;
+            st = get(kJitBlockAdjointRows, &rows);
+            if (n_f > 1) *jit_fn = rows;
+        }
         if (st == AMI_OK) {
             p = Path::ADJ_BLOCK;
             return AMI_OK;
@@ -923,7 +929,7 @@ AmiStatus launch_adjoint_block(AmiTerms *t, DeviceTables *dt, bool hub, KArgs &a
     a.gpartial = ws;
     a.partial = o.out_sum ? ws + static_cast<size_t>(rows) * ncols : nullptr;
     a.nrows = rows;
-    const int waves = jit_block_waves(t, hub, cplx);
+    const int waves = jit_block_waves(t, hub, cplx, a.n_f > 1);
     const bool fin = !fixed_ws && finish_small(t, dt, stream, a, kFinishBlockAdjoint, rows, waves, ncols, nval, o);
     hipError_t e = launch_block(fn, rows, waves, stream, a);
     if (e == hipSuccess) e = hipGetLastError();
@@ -1106,7 +1112,10 @@ std::vector<int> kernels_of(const AmiTerms *t, bool hub, int variant) {
         kinds.push_back(kJitFreqPass);
     }
     const bool block = jit_prefers_block_adjoint(t) && jit_block_waves(t, hub) > 0;
-    if (!forced && block) kinds.push_back(kJitBlockAdjoint);
+    if (!forced && block) {
+        kinds.push_back(kJitBlockAdjoint);
+        if (jit_block_rows_apart(t)) kinds.push_back(kJitBlockAdjointRows);
+    }
     if (T <= kJitAutoAdjointTerms) {
         if (forced ? one_pass : !block) kinds.push_back(kJitAdjoint);
     } else if ((forced ? passes : !block) && jit_adjoint_passes_supported(t, hub, nullptr)) {

@@ -178,12 +178,12 @@ AmiStatus code_object(AmiTerms *t, bool hub, int kind) {
     const bool passes = kind == kJitSumsPass || kind == kJitFreqPass || kind == kJitAdjFreq || kind == kJitAdjLeaf ||
                         kind == kJitComplexSums || kind == kJitComplexFreq || kind == kJitComplexAdjFreq ||
                         kind == kJitComplexAdjLeaf || kind == kJitBlockAdjoint ||
-                        kind == kJitComplexBlockAdjoint || kind == kJitBlockForward;
+                        kind == kJitComplexBlockAdjoint || kind == kJitBlockForward || kind == kJitBlockAdjointRows;
     if (!jit_supported(t, hub, &why, passes)) {
         err = "no specialized kernel: " + why;
         return fail(AMI_E_UNSUPPORTED, err);
     }
-    if ((kind == kJitBlockAdjoint || kind == kJitComplexBlockAdjoint) &&
+    if ((kind == kJitBlockAdjoint || kind == kJitComplexBlockAdjoint || kind == kJitBlockAdjointRows) &&
         jit_block_waves(t, hub, kind == kJitComplexBlockAdjoint) == 0) {
         err = "no block adjoint: the solution does not split over the waves of a block";
         return fail(AMI_E_UNSUPPORTED, err);
@@ -301,7 +301,7 @@ AmiStatus jit_get(AmiTerms *t, bool hub, int kind, void **fn) {
     static const char *const kNames[kJitKinds] = {"ami_jit_fwd",  "ami_jit_adj",   "ami_jit_mc",   "ami_jit_cfwd",
                                                   "ami_jit_sums", "ami_jit_freq",  "ami_jit_adjf", "ami_jit_adjl",
                                                   "ami_jit_cadj", "ami_jit_csums", "ami_jit_cfreq", "ami_jit_cadjf",
-                                                  "ami_jit_cadjl", "ami_jit_badj", "ami_jit_bcadj", "ami_jit_bfwd"};
+                                                  "ami_jit_cadjl", "ami_jit_badj", "ami_jit_bcadj", "ami_jit_bfwd", "ami_jit_badj"};
     e = hipModuleGetFunction(&f, mod, kNames[kind]);
     if (e != hipSuccess) {
         (void)hipModuleUnload(mod);

@@ -49,8 +49,12 @@ bool jit_adjoint_passes_supported(const AmiTerms *t, bool hub, std::string *why)
 // none (Taylor-coefficient leaves, too few groups to split evenly, or more
 // columns than the LDS of a CU holds).  Chosen once per handle and input: the
 // source and every launch of a handle take the same count, whatever becomes of the
-// environment's override in between.
-int jit_block_waves(const AmiTerms *t, bool hub, bool cplx = false);
+// environment's override in between.  several: of the kernel for several frequency
+// rows, where that is one of its own (jit_block_rows_apart).
+int jit_block_waves(const AmiTerms *t, bool hub, bool cplx = false, bool several = false);
+// Whether the real block adjoint has a kernel for one frequency row
+// (kJitBlockAdjoint) and another for several (kJitBlockAdjointRows), else one for both.
+bool jit_block_rows_apart(const AmiTerms *t);
 int jit_block_forward_waves(const AmiTerms *t);   // of the block forward, 0: none
 
 // Whether the diagram can be specialized for the energy (hub = false) or
@@ -79,7 +83,8 @@ int jit_block(const AmiTerms *t, bool hub);
 // passes of the adjoint at complex energies that follow the first of those
 // (kernels & 2048: per frequency, the complex group-sum and denominator
 // cotangents; kernels & 4096: the complex leaf cotangents and the gradients),
-// and the block adjoint (kernels & 8192; at complex energies 16384) or the block
+// and the block adjoint (kernels & 8192; its kernel for several frequency rows, where
+// that is apart, 65536; at complex energies 16384) or the block
 // forward (32768), each alone.
 // nested_part: terms per part of the one-pass adjoint's leaf cotangents as a
 // reverse sweep of the nested group sums (0: per-term prefix/suffix products;
@@ -129,7 +134,8 @@ int64_t code_meta(const std::vector<char> &code, const char *key);
 // energies (after kJitComplexSums); kJitBlockAdjoint the adjoint of large
 // solutions whose work the waves of a block split (no workspace),
 // kJitComplexBlockAdjoint the same at complex energies, kJitBlockForward the
-// forward of large solutions that way.
+// forward of large solutions that way, kJitBlockAdjointRows the block adjoint for
+// several frequency rows where that is a kernel of its own.
 enum JitKind {
     kJitForward = 0,
     kJitAdjoint = 1,
@@ -146,9 +152,10 @@ enum JitKind {
     kJitComplexAdjLeaf = 12,
     kJitBlockAdjoint = 13,
     kJitComplexBlockAdjoint = 14,
-    kJitBlockForward = 15
+    kJitBlockForward = 15,
+    kJitBlockAdjointRows = 16
 };
-constexpr int kJitKinds = 16;
+constexpr int kJitKinds = 17;
 
 // Kinds for the energy input only (complex energies).
 inline bool jit_kind_complex(int kind) {

@@ -35,8 +35,8 @@
 // large solutions (64, 128), the adjoint at complex energies (256), the two
 // passes of the forward at complex energies (512, 1024), the frequency and
 // leaf passes of the adjoint at complex energies (2048, 4096), or a sum of
-// them, or, alone, the block adjoint (8192; at complex energies 16384) or the
-// block forward (32768)
+// them, or, alone, the block adjoint (8192; for several rows, where that is apart,
+// 65536; at complex energies 16384) or the block forward (32768)
 
 // Small calls (a.fin_cols > 0): the last block to arrive adds the partial sums of
 // all blocks, in the order of the reduction kernel that large calls launch (64
@@ -255,19 +255,16 @@ extern "C" __global__ __launch_bounds__(AMI_JIT_BLOCK) void ami_jit_cadjl(ami::K
 }
 #endif
 
-#if AMI_JIT_KERNELS & 8192
+#if AMI_JIT_KERNELS & (8192 | 65536)
 // 64 samples per block of NW waves; two waves per SIMD (one alone issues an
 // FP64 instruction every eight cycles instead of four): two blocks of four
 // waves, or one of eight, on a CU
 extern "C" __global__ __launch_bounds__(64 * amijit::NW) __attribute__((amdgpu_waves_per_eu(2))) void ami_jit_badj(ami::KArgs a) {
     __shared__ double sm[64 * amijit::kBlockCols];
     const int64_t tile = (a.s0 >> 6) + blockIdx.x;      // s0: the launch's first sample
-    if constexpr (amijit::kRowsApart) {
-        if (a.n_f == 1) amijit::badj_tile<AMI_JIT_HUB, amijit::ONE_ROW>(a, tile, sm);
-        else amijit::badj_tile<AMI_JIT_HUB, amijit::SEVERAL_ROWS>(a, tile, sm);
-    } else {
-        amijit::badj_tile<AMI_JIT_HUB, amijit::ANY_ROWS>(a, tile, sm);
-    }
+    constexpr amijit::Rows rows = !amijit::kRowsApart ? amijit::ANY_ROWS
+                                  : AMI_JIT_KERNELS & 65536 ? amijit::SEVERAL_ROWS : amijit::ONE_ROW;
+    amijit::badj_tile<AMI_JIT_HUB, rows>(a, tile, sm);
     finish_sums<amijit::NW>(a, sm);
 }
 #endif

@@ -1236,7 +1236,7 @@ __device__ __forceinline__ void cadj_tile(const KArgs &a, int64_t blk, double *p
 }
 #endif
 
-#if AMI_JIT_KERNELS & (8192 | 32768)
+#if AMI_JIT_KERNELS & (8192 | 65536 | 32768)
 // The line momenta of a sample (a wave keeps those it uses).
 __device__ __forceinline__ void blk_lines(const KArgs &a, int64_t sc, double (&Kx)[NGA], double (&Ky)[NGA]) {
     double in[NIN], kx[NIA], ky[NIA];
@@ -1250,7 +1250,7 @@ __device__ __forceinline__ void blk_lines(const KArgs &a, int64_t sc, double (&K
 }
 #endif
 
-#if AMI_JIT_KERNELS & (8192 | 16384)
+#if AMI_JIT_KERNELS & (8192 | 65536 | 16384)
 // sum over the waves of the columns first, first + 1, ... (in wave order)
 __device__ __forceinline__ double blk_wave_total(ami::clds col, int first) {
     double v = col[64 * first];
@@ -1278,7 +1278,7 @@ __device__ __forceinline__ void blk_store_rows(const double *stage, double *dst,
 }
 #endif
 
-#if AMI_JIT_KERNELS & 8192
+#if AMI_JIT_KERNELS & (8192 | 65536)
 // Block adjoint of large solutions: NW waves share 64 samples (lane i of every
 // wave is sample i), each wave with its own part of the solution, and what the
 // waves exchange lives in LDS columns (column c of lane i at [64 c + i]):

@@ -3,7 +3,7 @@
 // construct.cpp, graph.cpp, codegen.cpp and abi.cpp).
 //
 // argv: "source KERNELS MOMENTUM" writes the generated source of the block
-// adjoint (KERNELS 8192; at complex energies 16384) or the block forward (32768)
+// adjoint (KERNELS 8192, several rows apart 65536; at complex energies 16384) or the block forward (32768)
 // to stdout; "override" takes a handle's waves per block, then changes
 // AMIGPU_JIT_BLOCK_WAVES and prints the count, the count asked for again and the
 // one in the source.  stdin: "n_g n_eps n_freq n_int" and the alpha and eps
@@ -43,7 +43,7 @@ int main(int argc, char **argv) {
         const int kernels = std::atoi(argv[2]);
         const bool hub = std::atoi(argv[3]) != 0;
         const int waves = kernels == 32768 ? ami::jit_block_forward_waves(t)
-                                           : ami::jit_block_waves(t, hub, kernels == 16384);
+                                           : ami::jit_block_waves(t, hub, kernels == 16384, kernels == 65536);
         if (waves > 0) std::fputs(ami::jit_source(t, hub, kernels).c_str(), stdout);
     } else {
         const int first = ami::jit_block_waves(t, true, false);

@@ -133,3 +133,11 @@ def test_generated_block_kernels_match_oracle(driver, tmp_path, order, seed, ker
     assert abs(rest[:, 0].sum() - float(db)) <= 1e-10 * sc["beta"]
     gw = rest[:, (1 if kernel == COMPLEX else 3):].sum(axis=0)
     assert np.max(np.abs(gw[0::2] + 1j * gw[1::2] - dw.astype(np.complex128).ravel())) <= 1e-10 * sc["w"]
+
+
+def test_several_rows_of_a_large_solution_take_eight_waves(driver):
+    """2804 terms: four waves for one row, whose groups' cotangents through several
+    would overflow the registers."""
+    d = random_self_energy(6, (5, 6, 2))
+    for kernel, waves in ((ADJOINT, 4), (65536, 8)):
+        assert f"constexpr int NW = {waves}," in driver(d, "source", kernel, 1)
