@@ -261,9 +261,9 @@ AmiStatus amiEvaluateComplex(AmiTerms *terms,
  * amiEvaluateComplex; out / out_sum (device, or NULL) receive the forward
  * values on the way.  The sums over samples are reduced in a fixed order.
  * Served by the specialized kernels (compiled on first use): one pass up to
- * 200 terms (50 with one frequency row, where under capture the kernel that is
- * loaded serves any number of rows; up to 1024 under
- * AMI_VARIANT_SPECIALIZED); above, a kernel whose waves split the solution,
+ * 200 terms (50 with one frequency row or where the kernel spills; where the rows
+ * decide, the kernel that is loaded serves any number of them under capture;
+ * up to 1024 under AMI_VARIANT_SPECIALIZED); above, a kernel whose waves split the solution,
  * or, where the solution does not split (one pass up to 512 terms) and under
  * AMI_VARIANT_TWO_PASS, passes over the chunked workspace of the two-pass
  * variant (complex group sums and energies stored; per frequency row the

@@ -425,6 +425,13 @@ bool jit_prefers_block_adjoint(const AmiTerms *t) {
     return tb.T > kJitAutoAdjointTerms || tb.L + 4 * tb.G + 4 * tb.D + 2 * t->n_eps > 100;
 }
 
+bool jit_prefers_complex_block(const AmiTerms *t, bool one_row) {
+    const Tables &tb = t->tab;
+    if (tb.T <= kJitAutoComplexBlockTermsOneRow) return false;
+    return one_row || tb.T > kJitAutoComplexBlockTerms ||
+           (tb.T <= kJitAutoAdjointTerms && 4 * tb.G + 6 * tb.D > 80);
+}
+
 bool jit_supported(const AmiTerms *t, bool hub, std::string *why, bool two_pass) {
     const Tables &tb = t->tab;
     auto no = [&](const std::string &m) {

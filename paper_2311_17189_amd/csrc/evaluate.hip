@@ -1135,8 +1135,8 @@ std::vector<int> kernels_of(const AmiTerms *t, bool hub, int variant) {
         }
     }
     const bool cblock = jit_block_waves(t, false, true) > 0;
-    if (!forced && cblock && T > kJitAutoComplexBlockTermsOneRow) kinds.push_back(kJitComplexBlockAdjoint);
-    const bool all_rows = cblock && T > kJitAutoComplexBlockTerms;      // the block for any number of rows
+    if (!forced && cblock && jit_prefers_complex_block(t, true)) kinds.push_back(kJitComplexBlockAdjoint);
+    const bool all_rows = cblock && jit_prefers_complex_block(t, false);      // the block for any number of rows
     if (T <= kJitAutoComplexAdjointTerms) {
         if (forced ? one_pass : !all_rows) kinds.push_back(kJitComplexAdj);
     } else if (forced ? passes : !all_rows) {
@@ -1343,14 +1343,13 @@ AmiStatus amiEvaluateComplexAdjoint(AmiTerms *t, const double *energies, int64_t
     bo.out_sum = out_sum;
     std::string note;
     // AUTO: the block adjoint where the solution splits over the waves of a block
-    bool to_block = t->variant == AMI_VARIANT_AUTO && n_e > 0 &&
-                    t->tab.T > (n_f == 1 ? kJitAutoComplexBlockTermsOneRow : kJitAutoComplexBlockTerms) &&
+    bool to_block = t->variant == AMI_VARIANT_AUTO && n_e > 0 && jit_prefers_complex_block(t, n_f == 1) &&
                     jit_block_waves(t, false, true) > 0;
     // where the number of rows decides, earlier calls with other rows may have left
     // this call's kernel unloaded: under capture, which is no place to compile, the
     // one that is loaded serves
-    if (t->variant == AMI_VARIANT_AUTO && n_e > 0 && t->tab.T > kJitAutoComplexBlockTermsOneRow &&
-        t->tab.T <= kJitAutoComplexBlockTerms && capturing(stream)) {
+    if (t->variant == AMI_VARIANT_AUTO && n_e > 0 && jit_prefers_complex_block(t, true) &&
+        !jit_prefers_complex_block(t, false) && capturing(stream)) {
         void *fn = nullptr;
         const bool block = jit_loaded(t, false, kJitComplexBlockAdjoint, &fn) == AMI_OK;
         if (block != (jit_loaded(t, false, kJitComplexAdj, &fn) == AMI_OK)) to_block = block;

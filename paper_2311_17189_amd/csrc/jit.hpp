@@ -25,13 +25,19 @@ constexpr int kJitAutoAdjointTerms = 128;
 // 0.91 ms, passes 1.75 ms; 380: 1.30 / 3.18 ms; 560: 2.21 / 1.91 ms).
 constexpr int kJitAutoComplexAdjointTerms = 512;
 // AUTO takes the block adjoint at complex energies above this many terms (2 10^5
-// samples, one row: 264 terms one pass 201 us, block 105; 560: passes 302, block
-// 134; four rows of 5 10^4: 88 and 52, 169 and 70), and with one frequency row
-// from fewer on (136 terms 84 and 66 us, 76: 76 and 63, 52: 56 and 48, 40: 48 and
-// 47; but 30 and 35, 29 and 33, 21 and 26 at four rows of 5 10^4 samples, where
-// each wave forms its denominators again for every row).
+// samples, one row: 264 terms one pass 205 us, block 110; 560: passes 302, block
+// 137; four rows of 5 10^4: 91 and 55, 170 and 72), and with one frequency row
+// from fewer on (136 terms 84 and 66 us, 76: 137 and 64, 52: 49.5 and 48.7, at 2 10^4
+// samples 21.4 and 19.3).  With several rows each wave forms its denominators again for
+// every row (136 terms, four rows of 5 10^4 samples 33 and 39, 16 of 10^5 104 and
+// 138), so one pass stays there unless it spills: up to the real adjoint's one-pass
+// size it runs at two waves per SIMD, whose registers more than 80 values of group
+// sums and denominators overflow (64 terms, 106 values: 76 and 36 us, 323 and 130; 112
+// terms, 104 values: 63 and 37, 235 and 132; 52 terms, 52 values: 24 and 27, 53 and 91).
 constexpr int kJitAutoComplexBlockTerms = 200;
 constexpr int kJitAutoComplexBlockTermsOneRow = 50;
+// whether it does with this many rows, where the solution splits over the waves
+bool jit_prefers_complex_block(const AmiTerms *t, bool one_row);
 
 // Whether AUTO's adjoint of a solution up to kJitAutoAdjointTerms terms takes the
 // block kernel: the one-pass kernel keeps a leaf and four values per group and
