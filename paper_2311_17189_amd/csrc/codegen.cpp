@@ -697,8 +697,8 @@ int jit_block_forward_waves(const AmiTerms *t) {
 }
 
 // Waves per block of the block adjoint (AMIGPU_JIT_BLOCK_WAVES overrides): as
-// few as leave each wave a part that fits its registers, since every wave more
-// is another partner at each barrier.  Real energies: two up to 200 terms (76
+// few as leave each wave a part that, with one row, fits its registers, since every
+// wave more is another partner at each barrier.  Real energies: two up to 200 terms (76
 // terms, 2 10^5 samples: 38.8 us a step, four waves 40.8; 136 terms 41.6 and
 // 50.4; 264 terms at four rows and 5 10^4 samples: 38.0 and 35.8), else four (560
 // terms 78.7, 76.9 and with eight 119; 2804 terms 233, 190 and 233).  Complex

@@ -260,8 +260,8 @@ __device__ __forceinline__ void exp_split(double z, double &t, double &m) {
 // slope 1.17 and 1.24 (1.49, 1.37); Bose-type f 0.66 and 0.60 (0.82, 0.63), f(-y)
 // 0.64 and 0.71 (0.82, 0.63; never a result by itself), slope 1.08 and 1.16 (1.61,
 // 1.29).  Without the correction the slopes were at 1.31 and 1.41, 1.43 and 1.34.
-// A leaf alone takes 26 (Fermi) and 28 (Bose-type) FP64 instructions, a pair three
-// more, where the form by e^-|y|, its Taylor series and two selections took 35-37
+// A leaf alone takes 24 (Fermi) and 25 (Bose-type) FP64 instructions, a pair 27 and
+// 29, where the form by e^-|y|, its Taylor series and two selections took 35-37
 // (order 4, 52 terms, 10^6 samples: forward call 40.6 -> 34.4 us).
 __device__ __forceinline__ void leaf_pair(bool bose, double y, double &f, double &fm) {
     const double z = fmin(fmax(y, -700.0), 700.0);

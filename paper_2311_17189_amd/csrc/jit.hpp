@@ -43,7 +43,7 @@ bool jit_prefers_complex_block(const AmiTerms *t, bool one_row);
 // block kernel: the one-pass kernel keeps a leaf and four values per group and
 // denominator, and two per energy, live at once; beyond 100 of the 128 doubles
 // that two waves per SIMD have, it spills (76 terms in 16 groups, 123 values,
-// 2 10^5 samples: 62 us a step, the block kernel 39; 40 terms in 8 groups, 81
+// 2 10^5 samples: 58 us a step, the block kernel 40; 40 terms in 8 groups, 81
 // values: 28 and 30; 52 terms in 4 groups, 68 values: 25 and 33).
 bool jit_prefers_block_adjoint(const AmiTerms *t);
 

@@ -1283,21 +1283,24 @@ __device__ __forceinline__ void blk_store_rows(const double *stage, double *dst,
 // wave is sample i), each wave with its own part of the solution, and what the
 // waves exchange lives in LDS columns (column c of lane i at [64 c + i]):
 //   energies and leaves   wave j mod NW forms line j and leaf j
-//   group sums, products, values and leaf sweep: each wave its own groups,
-//                         whose FT_g and FTB_g never leave its registers
+//   group sums, products, values and leaf sweep: each wave its own groups
 //   leaf cotangents       summed over the waves in rounds (blk_rounds), then
 //                         energies' cotangents, then the momenta's
 // What bounded the passes over a workspace that it replaces was not arithmetic
 // but waiting: the leaf pass held 50 leaves, their slopes and cotangents (1.4 KB
 // per lane more than its registers) and spent 82% of its wave cycles on spills,
 // the frequency pass 71% on one group's stored sum after another.  Split over
-// the waves, a wave's part fits its registers, the leaves come from LDS where
-// they are read, and nothing but inputs and results touches HBM; few samples
-// fill the chip, too.  Gradient step, one row (passes, here): 2804 terms 512 ->
-// 190 us at 2 10^5 samples, 142 -> 34 at 2 10^4, 87 -> 23 at 10^3; 560 terms
-// 113 -> 77 us, 264 terms 78 -> 64, 136 terms 57 -> 42 at 2 10^5.  What is left
-// of it is issue (2.1 10^4 VALU instructions per block, 115 us of the 190) and
-// the barriers of unequal waves.
+// the waves, one row's part of a wave fits its registers at every size measured,
+// the leaves come from LDS where they are read, and nothing but inputs and
+// results touches HBM; few samples fill the chip, too.  Through several rows a
+// wave also keeps its groups' cotangents: above 24 groups that spills
+// (kBlockRowGroups).  Gradient step, one row (passes, here): 2804 terms 510 ->
+// 190 us at 2 10^5 samples, 144 -> 36 at 2 10^4, 88 -> 24 at 10^3; 560 terms
+// 111 -> 78 us, 264 terms 80 -> 62, 136 terms 57 -> 42 at 2 10^5; four rows of 560
+// terms 205 -> 134.  What is left (2804 terms, one row): the VALU issues on 71% of
+// the CUs' busy cycles, waves wait for 31% of theirs (LDS, dependences at two waves
+// per SIMD, barriers); instruction fetches miss 0.5% of the time, the waves' parts
+// differ by 1%.
 // The wave's energies to their columns.
 template <bool HUB, int WV>
 __device__ __forceinline__ void blk_energies(const KArgs &a, int64_t sc, ami::lds col) {
@@ -1725,11 +1728,12 @@ __device__ __forceinline__ void bcadj_tile(const KArgs &a, int64_t tile, double 
 // reading the group sums where the nesting needs them.  The two kernels over a
 // workspace that it replaces moved every group sum through L2 once per row
 // (order 6, 2804 terms, 16 rows of 2 10^5 samples: 2.4 GB, at which the
-// frequency pass ran at half its issue rate).  Now issue bounds it, and LDS
-// reads in the sums of one row.  2 10^5 momenta: 2804 terms 211 -> 156 us (one
-// row 82 -> 77), 560 terms 114 -> 82 (38 -> 31); solutions whose one-pass forward
-// fits the registers stay there (264 terms: 48 against 54 us, one row 17 against
-// 22).  The values are the same bit for bit.
+// frequency pass ran at half its issue rate).  Now issue bounds it (on 76% of the
+// CUs' busy cycles), and LDS reads in the sums of one row.  2 10^5 momenta, 16 rows,
+// on one card: 2804 terms 220 us in passes, 159 here (one row 82 and 77), 560 terms
+// 123 and 85 (40 and 34); solutions whose one-pass forward fits the registers stay
+// there (264 terms: 48 against 54 us, one row 17 against 22).  The values are the
+// same bit for bit.
 template <bool HUB, int WV>
 __device__ __forceinline__ void bfwd_sums(const KArgs &a, int64_t sc, ami::lds col) {
     if constexpr (HUB) {

@@ -16,9 +16,10 @@ compares and conversions 0):
     reduction of a momentum component mod 2 pi        6
     e^z and e^z - 1 of one argument (both)           34
     reciprocal (estimate + one third-order step)      7
-    leaf f(y) with its mirror f(-y), Fermi / Bose    42 / 45
-    leaf derivative f'(y)                            43
-    leaf at a complex argument, Fermi / Bose         89 / 95
+    leaf f(y), Fermi / Bose                          41 / 42
+    leaf f(y) with its mirror f(-y), Fermi / Bose    46 / 49
+    leaf derivative f'(y), Fermi / Bose              47 / 50
+    leaf at a complex argument, Fermi / Bose         88 / 95
 
 Two models: ``forward_flops``/``adjoint_flops`` for the table-driven (packed)
 kernels and ``specialized_forward_flops``/``specialized_adjoint_flops`` for the
@@ -39,10 +40,11 @@ C_COS = 24
 C_RED2PI = 6
 C_EXP = 34
 C_RCP = 7
-C_LEAF_FERMI = 42
-C_LEAF_BOSE = 45
-C_LEAF_DERIV = 43
-C_LEAF_C_FERMI = 89    # leaf at a complex argument (leaf_complex), Fermi / Bose-type
+C_LEAF_FERMI = 41
+C_LEAF_BOSE = 42
+C_PAIR_FERMI = 46      # a leaf with its mirror (adjoints, Taylor-coefficient leaves)
+C_PAIR_BOSE = 49
+C_LEAF_C_FERMI = 88    # leaf at a complex argument (leaf_complex), Fermi / Bose-type
 C_LEAF_C_BOSE = 95
 
 PEAK_FP64_VECTOR = 78.6e12     # 256 CUs x 2.4 GHz x 128 FP64 FLOP/clk
@@ -204,7 +206,8 @@ def adjoint_flops(st: Structure, n_e: int, n_f: int, line_alpha=None, with_value
         per_sample += n_terms * (st.n_int + 1)              # group sums
         per_sample += n_terms * (1 + ni + (ni - 1) + 2 * ni)   # leaf cotangents
     for sigma, e in st.leaves:
-        per_sample += max(_nnz(e) - 1, 0) + 2 + C_LEAF_DERIV + 1 + _nnz(e) + 1 + 2
+        deriv = 1 + (C_PAIR_BOSE if sigma == -1 else C_PAIR_FERMI)
+        per_sample += max(_nnz(e) - 1, 0) + 2 + deriv + 1 + _nnz(e) + 1 + 2
     per_point = _den_flops(st)
     for n_terms, dpt in st.groups:
         per_point += 6 * max(dpt - 1, 0) + 3 + 2 + 6
@@ -229,7 +232,10 @@ def _spec_leaves(st: Structure, adjoint: bool) -> int:
     for code, e in st.leaves:
         sigma = 1 if code > 0 else -1
         total += max(_nnz(e) - 1, 0) + 1 + (1 if sigma == -1 else 0)    # x, beta x, + e_reg
-        total += C_LEAF_BOSE if sigma == -1 else C_LEAF_FERMI
+        if adjoint or abs(code) > 1:
+            total += C_PAIR_BOSE if sigma == -1 else C_PAIR_FERMI
+        else:
+            total += C_LEAF_BOSE if sigma == -1 else C_LEAF_FERMI
         total += _taylor_flops(abs(code) - 1)
         if adjoint:
             total += 1                                                   # f'(y) = -f(y) f(-y)
