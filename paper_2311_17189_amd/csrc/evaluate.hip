@@ -592,14 +592,14 @@ int nonempty_parts(int64_t n_f, int64_t parts) {
 // the samples that forms the leaves and group sums again: the number whose waves
 // finish first.  A SIMD's time is its waves' instructions (estimated from the
 // sizes), 1.3 times that for a wave alone, 1.1 for two at a time, 1.03 for three;
-// the waves the registers do not hold side by side follow one another.  (From the
-// kernel times of six diagrams at 3000 to 10^5 samples, 4 to 256 rows and one to
-// 32 parts, real and complex: what this picks takes 1% more than the best on
-// average.  Two waves per SIMD taken for free, as before, took 8% more, and lost
-// where a row is cheap beside the leaves: 5 10^4 samples, four rows, 264 terms
-// 9.4 us in one part and 11.5 in two, at complex energies 14.3 and 20.4.  The gains:
-// order 4, 52 terms, 256 rows of 10^5 samples 142 us in one part, 118 in six,
-// of 10^4 samples 96 and 21.)
+// the waves the registers do not hold side by side follow as others end.  (From the
+// times of six diagrams at 3000 to 10^6 samples, 4 to 256 rows and one to 32 parts,
+// real and complex: what this picks takes 1% more than the best on average.  Two
+// waves per SIMD taken for free, as before, took 4 to 8% more, and lost where a row
+// is cheap beside the leaves: 5 10^4 samples, four rows, 264 terms 9.4 us in one
+// part and 11.5 in two, at complex energies 14.3 and 20.4.  The gains: order 4, 52
+// terms, 256 rows of 10^5 samples 140 us in one part, 117 in five, of 10^4 samples
+// 96 and 21.)
 int forward_row_parts(const AmiTerms *t, bool hub, bool cplx, int64_t n_waves, int64_t n_f) {
     if (n_f < 4) return 1;
     const Tables &tb = t->tab;
@@ -607,18 +607,20 @@ int forward_row_parts(const AmiTerms *t, bool hub, bool cplx, int64_t n_waves, i
     const double per_row = (cplx ? 22.0 * tb.D + 16.0 * tb.G : 18.0 * tb.D + 12.0 * tb.G) + 40.0;
     const double vgprs = cplx ? 1.5 * (4.0 * tb.G + 6.0 * tb.D) : 2.2 * (2.0 * tb.G + 4.0 * tb.D);
     const int64_t side_by_side = std::max(1, std::min(8, static_cast<int>(512.0 / std::max(vgprs, 40.0))));
-    auto rate = [](int64_t waves) { return waves <= 1 ? 1.3 : waves == 2 ? 1.1 : waves == 3 ? 1.03 : 1.0; };
+    auto rate = [](int64_t waves) {
+        return waves <= 1 ? 1.3 : waves == 2 ? 1.1 : waves == 3 ? 1.03 : waves <= 5 ? 1.015 : 1.0;
+    };
     auto time = [&](int64_t parts) {
         const int64_t waves = (std::max<int64_t>(n_waves, 1) * parts + 1023) / 1024;      // of a SIMD
         const int64_t full = waves / side_by_side, rest = waves % side_by_side;
         const double issue = static_cast<double>(full * side_by_side) * rate(side_by_side) +
-                             (rest ? static_cast<double>(rest) * rate(rest) : 0.0);
+                             static_cast<double>(rest) * (full ? 1.0 : rate(rest));
         return issue * (once + per_row * static_cast<double>(rows_per_part(n_f, parts)));
     };
-    // the fewest parts within 4% of the least time, one within 5%
+    // the fewest parts within 2% of the least time, one within 3%
     const int64_t most = std::min<int64_t>(n_f / 2, 1024);
     auto next = [](int64_t p) { return p + (p < 16 ? 1 : p & (p - 1) ? p / 3 : p / 2); };
-    double least = 0.95 * time(1);
+    double least = 0.97 * time(1);
     bool split = false;
     for (int64_t p = 2; p <= most; p = next(p)) {
         const double v = time(p);
@@ -628,7 +630,7 @@ int forward_row_parts(const AmiTerms *t, bool hub, bool cplx, int64_t n_waves, i
     }
     if (!split) return 1;
     int64_t p = 2;
-    while (time(p) > 1.04 * least) p = next(p);
+    while (time(p) > 1.02 * least) p = next(p);
     return nonempty_parts(n_f, p);
 }
 
