@@ -41,16 +41,35 @@
 // Small calls (a.fin_cols > 0): the last block to arrive adds the partial sums of
 // all blocks, in the order of the reduction kernel that large calls launch (64
 // rows at a time, then those totals in row order: the same bits).  NW waves per
-// block, each with its columns, 16 loads in flight.  lds: a word of the kernel's
+// block, each with its columns, 16 loads in flight.  last: a word of the kernel's
 // LDS.  The second launch this saves bounds such calls on
 // the host: order 2, 300 samples 14.4 -> 11.3 us, the adjoint of 10^4 21.5 -> 18.5.
 // Every wave's rows are in L2 before the barrier, and released to the device before
-// the block is counted; the block that completes the count resets it for the
-// next launch on the stream.
+// the block is counted (ROCm 7.2's compiler counts without waiting for the
+// write-back, so the wait is explicit); the block that completes the count resets it
+// for the next launch on the stream.
+typedef __attribute__((address_space(3))) unsigned *LdsWord;
+typedef __attribute__((address_space(1))) double *GlobalDouble;
+
+// Where the total of column c goes (null: nowhere).  By selections alone: ROCm 7.2's
+// compiler loses fin_t from the branches of the nested conditional.
+__device__ __forceinline__ GlobalDouble finish_target(const ami::KArgs &a, int c) {
+    const uint64_t scalar[3] = {reinterpret_cast<uint64_t>(a.fin_beta), reinterpret_cast<uint64_t>(a.fin_mu),
+                                reinterpret_cast<uint64_t>(a.fin_t)};
+    uint64_t p = 0;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) p |= scalar[j] & (0 - static_cast<uint64_t>(c == j));
+    const uint64_t w = reinterpret_cast<uint64_t>(a.fin_w), sum = reinterpret_cast<uint64_t>(a.fin_sum);
+    const uint64_t in_w = 0 - static_cast<uint64_t>(c >= ami::kAdjScalars && w != 0);
+    const uint64_t in_sum = 0 - static_cast<uint64_t>(c >= a.fin_grad);
+    p |= (w + 8 * static_cast<int64_t>(c - ami::kAdjScalars)) & in_w;
+    p = (p & ~in_sum) | ((sum + 8 * static_cast<int64_t>(c - a.fin_grad)) & in_sum);
+    return reinterpret_cast<GlobalDouble>(p);
+}
+
 template <int NW>
-__device__ __forceinline__ void finish_sums(const ami::KArgs &a, void *lds) {
+__device__ __forceinline__ void finish_sums(const ami::KArgs &a, LdsWord last) {
     if (a.fin_cols == 0) return;
-    volatile unsigned &last = *static_cast<volatile unsigned *>(lds);
     const unsigned blocks = gridDim.x * gridDim.y;
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
@@ -58,13 +77,15 @@ __device__ __forceinline__ void finish_sums(const ami::KArgs &a, void *lds) {
         unsigned before = 0;
         if (blocks > 1) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            __builtin_amdgcn_s_waitcnt(0);
             before = __hip_atomic_fetch_add(a.fin_ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
         }
-        last = before == blocks - 1;
-        if (last && blocks > 1) __hip_atomic_store(a.fin_ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const bool whole = before == blocks - 1;
+        *last = whole;
+        if (whole && blocks > 1) __hip_atomic_store(a.fin_ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    if (!last) return;
+    if (!__builtin_amdgcn_readfirstlane(*last)) return;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const double *cols = a.gpartial ? a.gpartial : a.partial;
@@ -88,10 +109,7 @@ __device__ __forceinline__ void finish_sums(const ami::KArgs &a, void *lds) {
             if (p + u >= todo) break;
             total += ami::wave_sum(0.0 + v[u]);
             if (++k < chunks) continue;
-            double *dst = nullptr;
-            if (c >= a.fin_grad) dst = a.fin_sum + (c - a.fin_grad);
-            else if (c >= ami::kAdjScalars) dst = a.fin_w ? a.fin_w + (c - ami::kAdjScalars) : nullptr;
-            else if (c < 3) dst = c == 0 ? a.fin_beta : c == 1 ? a.fin_mu : a.fin_t;
+            const GlobalDouble dst = finish_target(a, c);
             if (lane == 0 && dst) *dst = total;
             total = 0.0;
             k = 0;
@@ -117,7 +135,7 @@ extern "C" __global__ __launch_bounds__(AMI_JIT_BLOCK) void ami_jit_fwd(ami::KAr
         AMI_JIT_ROW_PART(f0, f1)
         amijit::fwd_tile<AMI_JIT_HUB, false>(a, blockIdx.x, f0, f1);
     }
-    finish_sums<AMI_JIT_BLOCK / 64>(a, &word);
+    finish_sums<AMI_JIT_BLOCK / 64>(a, (LdsWord)&word);
 }
 #endif
 
@@ -136,7 +154,7 @@ extern "C" __global__ __launch_bounds__(AMI_JIT_BLOCK) AMI_JIT_ADJ_ATTR void ami
     amijit::load_inputs<AMI_JIT_HUB>(a, s < a.n_e ? s : a.n_e - 1, in);
     if (a.n_f == 1) amijit::adj_tile<AMI_JIT_HUB, true>(a, blockIdx.x, park, in);
     else amijit::adj_tile<AMI_JIT_HUB, false>(a, blockIdx.x, park, in);
-    finish_sums<AMI_JIT_BLOCK / 64>(a, park);
+    finish_sums<AMI_JIT_BLOCK / 64>(a, (LdsWord)park);
 }
 #endif
 
@@ -151,7 +169,7 @@ extern "C" __global__ __launch_bounds__(AMI_JIT_BLOCK) void ami_jit_cfwd(ami::KA
     __shared__ unsigned word;
     AMI_JIT_ROW_PART(f0, f1)
     amijit::cfwd_tile(a, blockIdx.x, f0, f1);
-    finish_sums<AMI_JIT_BLOCK / 64>(a, &word);
+    finish_sums<AMI_JIT_BLOCK / 64>(a, (LdsWord)&word);
 }
 #endif
 
@@ -162,7 +180,7 @@ __attribute__((amdgpu_waves_per_eu(AMI_JIT_CADJ_WAVES)))
 extern "C" __global__ __launch_bounds__(AMI_JIT_BLOCK) void ami_jit_cadj(ami::KArgs a) {
     __shared__ double park[amijit::kParkS ? 2 * amijit::L * AMI_JIT_BLOCK : 1];
     amijit::cadj_tile(a, blockIdx.x, park);
-    finish_sums<AMI_JIT_BLOCK / 64>(a, park);
+    finish_sums<AMI_JIT_BLOCK / 64>(a, (LdsWord)park);
 }
 #endif
 
@@ -265,7 +283,7 @@ extern "C" __global__ __launch_bounds__(64 * amijit::NW) __attribute__((amdgpu_w
     constexpr amijit::Rows rows = !amijit::kRowsApart ? amijit::ANY_ROWS
                                   : AMI_JIT_KERNELS & 65536 ? amijit::SEVERAL_ROWS : amijit::ONE_ROW;
     amijit::badj_tile<AMI_JIT_HUB, rows>(a, tile, sm);
-    finish_sums<amijit::NW>(a, sm);
+    finish_sums<amijit::NW>(a, (LdsWord)sm);
 }
 #endif
 
@@ -279,7 +297,7 @@ extern "C" __global__ __launch_bounds__(64 * amijit::NW) __attribute__((amdgpu_w
     } else {
         amijit::bcadj_tile<amijit::ANY_ROWS>(a, tile, sm);
     }
-    finish_sums<amijit::NW>(a, sm);
+    finish_sums<amijit::NW>(a, (LdsWord)sm);
 }
 #endif
 
@@ -289,6 +307,6 @@ extern "C" __global__ __launch_bounds__(64 * amijit::NW) __attribute__((amdgpu_w
     const int64_t tile = (a.s0 >> 6) + blockIdx.x;      // s0: the launch's first sample
     AMI_JIT_ROW_PART(f0, f1)
     amijit::bfwd_tile<AMI_JIT_HUB>(a, tile, f0, f1, sm);
-    finish_sums<amijit::NW>(a, sm);
+    finish_sums<amijit::NW>(a, (LdsWord)sm);
 }
 #endif
